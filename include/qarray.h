@@ -75,7 +75,7 @@ typedef enum {
 typedef enum { QA_OPEN = 0, QA_CLOSED = 1 } qa_mode;
 
 /* Arithmetic used to score the candidate states.
- *  QA_PREC_FP64   : every candidate energy in FP64 on the vector ALUs.
+ *  QA_PREC_FP64   : candidate energies in FP64 on the vector ALUs.
  *  QA_PREC_FP32   : b^T g on FP32 matrix cores, FP64 re-score of near ties.
  *  QA_PREC_BF16X3 : b^T g on BF16 matrix cores with g split exactly into
  *                   three BF16 parts (FP32 accumulation), FP64 re-score of
@@ -84,11 +84,12 @@ typedef enum { QA_OPEN = 0, QA_CLOSED = 1 } qa_mode;
  *                   bits), FP64 re-score of near ties.
  * The integer result is the same for all four: the near-tie re-score
  * replaces the approximate argmin by the FP64 one whenever the approximate
- * runner-up lies within the certified error band.  The matrix-core forms are
- * used at T = 0 with n_dot >= 9: for open arrays over the dense box (t = 1)
- * or the thresholded sub-box of each pixel (t < 1, Sec. 3.2.2), for closed
- * arrays over the subsets of the free dots that raise the charge to N_hat
- * (Sec. 3.2); elsewhere the FP64 form runs regardless of the request. */
+ * runner-up lies within the certified error band.  The matrix-core forms run
+ * where they are the faster ones: the split-BF16 forms over the dense box
+ * (t = 1, open) of 16 dots and at most 16000 pixels, and every matrix-core
+ * form (n_dot >= 9: dense boxes, thresholded sub-boxes, closed subsets) when
+ * all candidate energies are asked for (QA_FLAG_EXHAUSTIVE).  Elsewhere the
+ * FP64 form runs regardless of the request. */
 typedef enum {
     QA_PREC_FP64 = 0,
     QA_PREC_FP32 = 1,
@@ -112,15 +113,17 @@ typedef struct {
 } qa_problem;
 
 /* qa_problem.flags.
- *  QA_FLAG_EXHAUSTIVE : the matrix-core scorer computes the energy of every
- *      state of the candidate set.  By default the candidate sets of N >= 13
- *      dots (the dense box, the thresholded sub-boxes and the closed subsets)
- *      are searched in bound order: a lower bound of the 256 states that
- *      share a high part (the low part minimised over the reals, whose value
- *      is the Schur complement of the low block of C_dd^{-1}, i.e. the inverse
- *      of the high block of C_dd; closed arrays with the low part's sum fixed)
- *      discards high parts that cannot hold the argmin or a state of the
- *      near-tie band.  Both give the argmin over the whole candidate set
+ *  QA_FLAG_EXHAUSTIVE : the ground-state scorer computes the energy of every
+ *      state of the candidate set.  By default the candidate sets (the dense
+ *      box, the thresholded sub-boxes and the closed subsets) of N >= 9 dots
+ *      are searched in bound order: a lower bound of the states that share a
+ *      high part (64 states in FP64, 256 on the matrix cores; the low part
+ *      minimised over the reals around the continuous minimum, whose value is
+ *      the Schur complement of the low block of C_dd^{-1}, i.e. the inverse of
+ *      the high block of C_dd; closed arrays with the low part's sum fixed)
+ *      discards high parts that cannot hold the argmin, a state within 1e-9 of
+ *      it, or a state of the near-tie band.  Both give the argmin over the
+ *      whole candidate set
  *      (Sec. 3.2); qa_stats.scored tells how many energies were computed. */
 #define QA_FLAG_EXHAUSTIVE 1
 
@@ -132,7 +135,8 @@ typedef struct {
     int64_t near_tie_pixels;   /* approximate scoring flagged -> FP64 re-score */
     int64_t fp64_gap_below_1e9;/* pixels whose FP64 best/runner-up gap < 1e-9 */
     int64_t candidates;        /* states of the candidate sets (Sec. 3.2) */
-    int64_t scored;            /* states whose energy the scorer computed */
+    int64_t scored;            /* states whose energy the scorer computed (the
+                                  closed forms count whole rows) */
 } qa_stats;
 
 /* Ground state at T = 0 (Sec. 3, Eq. argmin) of P pixels.
@@ -176,7 +180,7 @@ qa_status qa_ground_state_grid(const qa_problem *prob, const qa_grid *grid, int3
  * but the call allocates nothing (no hipMalloc, hipHostMalloc or hipFree,
  * no host heap) and issues no copy: the problem's inputs travel as kernel
  * arguments, and every intermediate (diagram record, per-pixel records,
- * counters) lives in a static device array of about 15 MB that each GPU the
+ * counters) lives in a static device array of about 17 MB that each GPU the
  * library runs on holds until the process ends.
  *   P : 0..QA_NOALLOC_MAX_PIXELS; larger P returns QA_E_SHAPE (nothing is
  *       enqueued).  Split larger sweeps into several calls.

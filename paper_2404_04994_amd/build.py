@@ -38,6 +38,7 @@ PER_FILE = {
     "qa_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # energies are finite: fmin/fmax without NaN canonicalisation
     "qa_batch.hip": ["-fno-honor-nans"],
+    "qa_rows.hip": ["-fno-honor-nans"],
     # the first kernel arguments arrive in SGPRs at wave start (no scalar load
     # before the first address): the short softargmin and adjoint kernels
     # here gain about 0.2 us each

@@ -52,6 +52,8 @@ struct Workspace {
     hipStream_t stream = nullptr;
     DiagRec *dr = nullptr;
     int64_t dr_cap = 0;
+    RowTab *rt = nullptr;               // tables of the row kernels (N >= 9)
+    int64_t rt_cap = 0;
     PixRec *pr = nullptr;
     int64_t pr_cap = 0;
     int32_t *bstats = nullptr;          // per-block counts of the setup kernel
@@ -313,15 +315,11 @@ qa_status grow_single(Workspace *w, int64_t P)
     DiagRec *dr0 = w->dr;
     if ((st = grow(w, w->dr, w->dr_cap, 1))) return st;
     if (w->dr != dr0) w->dr_inputs.clear();
+    if ((st = grow(w, w->rt, w->rt_cap, 1))) return st;
     if ((st = grow(w, w->pr, w->pr_cap, P))) return st;
     // four counts per setup block; N = 16 has the most blocks
     if ((st = grow(w, w->bstats, w->bstats_cap, 4 * setup_blocks(P, kMaxDot)))) return st;
     return QA_OK;
-}
-
-bool use_matrix_cores(const qa_problem *pb)
-{
-    return pb->precision != QA_PREC_FP64 && pb->n_dot >= 9;
 }
 
 // candidate family of the matrix-core scorer: dense box, thresholded
@@ -331,36 +329,74 @@ int scorer_mode(const qa_problem *pb)
     return pb->mode == QA_CLOSED ? 2 : (pb->threshold < 1.0 ? 1 : 0);
 }
 
-// the T = 0 scorer of the problem's candidate family and precision
-hipError_t launch_scorer(const DiagRec *dr, const PixRec *pr, int64_t *counters,
-                         const qa_problem *pb, int64_t P, int32_t *n_out, hipStream_t s)
+// Which T = 0 scorer a problem of P pixels takes.
+//   kTable       N <= 8: the whole-box table (FP64).
+//   kRows        N >= 9: FP64 rows in bound order, whatever precision is asked
+//                for (all four return the same states).
+//   kMatrixBound the split-BF16 matrix-core search in bound order, where it is
+//                the faster one: dense boxes of 16 dots and few pixels, when the
+//                caller asks for it.  Scorer and setup, BF16x3 / rows, 16 dots:
+//                4x4 array 23.3 / 24.1 us at 10^4 pixels, 32.9 / 32.5 at
+//                1.6*10^4, 264 / 216 at 2*10^5; random capacitances 32.7 / 38.1,
+//                40.7 / 46.2, 319 / 296 (13 dots: 29.0 / 25.7 at 10^4).  Closed
+//                and thresholded sets and the FP32 form measured slower than
+//                rows everywhere (16 dots, 10^4: closed 52.6 / 48.7, t = 1/2
+//                23.2 / 19.8, FP32 dense 32.1 / 24.1; 12 dots 26.7 / 18.7).
+//   kMatrixAll, kFp64All  every energy of the set (QA_FLAG_EXHAUSTIVE).
+enum class Scorer { kTable, kRows, kMatrixBound, kMatrixAll, kFp64All };
+constexpr int64_t kMatrixBoundPixels = 16000;
+
+Scorer scorer_of(const qa_problem *pb, int64_t P)
 {
-    if (use_matrix_cores(pb))
-        return launch_score_mfma(dr, pr, P, pb->precision, scorer_mode(pb),
-                                 (pb->flags & QA_FLAG_EXHAUSTIVE) != 0, n_out, counters,
-                                 pb->n_dot, s);
-    if (pb->n_dot <= 8) return launch_score_tab(dr, pr, P, n_out, counters, pb->n_dot, s);
-    return launch_score_fp64(dr, pr, P, n_out, counters, pb->n_dot, s);
+    if (pb->n_dot <= 8) return Scorer::kTable;
+    if (pb->flags & QA_FLAG_EXHAUSTIVE)
+        return pb->precision == QA_PREC_FP64 ? Scorer::kFp64All : Scorer::kMatrixAll;
+    const bool split_bf16 = pb->precision == QA_PREC_BF16X3 || pb->precision == QA_PREC_BF16X2;
+    if (split_bf16 && pb->n_dot == 16 && scorer_mode(pb) == 0 && P <= kMatrixBoundPixels)
+        return Scorer::kMatrixBound;
+    return Scorer::kRows;
+}
+
+// the bound terms that scorer reads
+BoundSplit scorer_split(Scorer sc)
+{
+    return sc == Scorer::kRows ? kBoundLow6
+                               : (sc == Scorer::kMatrixBound ? kBoundLow8 : kBoundNone);
+}
+
+hipError_t launch_scorer(Scorer sc, const DiagRec *dr, const RowTab *rt, const PixRec *pr,
+                         int64_t *counters, const qa_problem *pb, int64_t P, int32_t *n_out,
+                         hipStream_t s)
+{
+    switch (sc) {
+    case Scorer::kTable: return launch_score_tab(dr, pr, P, n_out, counters, pb->n_dot, s);
+    case Scorer::kRows: return launch_rows_gs(rt, pr, P, scorer_mode(pb), n_out, counters, pb->n_dot, s);
+    case Scorer::kFp64All: return launch_score_fp64(dr, pr, P, n_out, counters, pb->n_dot, s);
+    default:
+        return launch_score_mfma(dr, pr, P, pb->precision, scorer_mode(pb), sc == Scorer::kMatrixAll,
+                                 n_out, counters, pb->n_dot, s);
+    }
 }
 
 // The device work of one single-diagram call on stream s, with the inputs
 // already in dr: prologue, setup and QP in one kernel, then either the T = 0
 // scoring (n_out) or the softargmin (nbar, saved).  pr holds P pixel records,
 // bstats 4 * setup_blocks(P, n_dot) counts.  ev: optional stage events.
-qa_status enqueue_path(DiagRec *dr, PixRec *pr, int64_t *counters, int32_t *bstats, hipStream_t s,
-                       const qa_problem *pb, const double *V, int64_t P, int32_t *n_out,
+qa_status enqueue_path(DiagRec *dr, RowTab *rt, PixRec *pr, int64_t *counters, int32_t *bstats,
+                       hipStream_t s, const qa_problem *pb, const double *V, int64_t P, int32_t *n_out,
                        double *nbar, SavedRec *saved, std::array<hipEvent_t, 4> *ev,
                        const VGrid *sweep = nullptr)
 {
     const bool closed = pb->mode == QA_CLOSED;
+    const Scorer sc = scorer_of(pb, P);
     if (ev) QA_HIP(hipEventRecord((*ev)[0], s));
-    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed, s, nullptr, nullptr,
-                        sweep));
+    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed,
+                        nbar ? kBoundNone : scorer_split(sc), rt, s, nullptr, nullptr, sweep));
     if (ev) QA_HIP(hipEventRecord((*ev)[1], s));
     if (nbar)
         QA_HIP(launch_soft_fwd(dr, pr, P, nbar, saved, counters, pb->n_dot, s));
     else
-        QA_HIP(launch_scorer(dr, pr, counters, pb, P, n_out, s));
+        QA_HIP(launch_scorer(sc, dr, rt, pr, counters, pb, P, n_out, s));
     if (ev) QA_HIP(hipEventRecord((*ev)[2], s));
     if (ev) QA_HIP(hipEventRecord((*ev)[3], s));
     return QA_OK;
@@ -371,7 +407,7 @@ qa_status enqueue_single(Workspace *w, hipStream_t s, const qa_problem *pb, cons
                          int64_t P, int32_t *n_out, double *nbar, SavedRec *saved,
                          std::array<hipEvent_t, 4> *ev, const VGrid *sweep = nullptr)
 {
-    qa_status st = enqueue_path(w->dr, w->pr, w->counters, w->bstats, s, pb, V, P, n_out, nbar,
+    qa_status st = enqueue_path(w->dr, w->rt, w->pr, w->counters, w->bstats, s, pb, V, P, n_out, nbar,
                                 saved, ev, sweep);
     if (!st) w->dr_derived = true;
     return st;
@@ -390,10 +426,11 @@ qa_status run_single(Workspace *w, const qa_problem *pb, const double *V, int64_
     std::array<hipEvent_t, 4> *ev = timing_slot(w);
     if (ev || !g_graphs || sweep)
         return enqueue_single(w, w->stream, pb, V, P, n_out, nbar, saved, ev, sweep);
-    const int path = nbar ? 2 : (use_matrix_cores(pb) ? 10 + 3 * pb->precision + scorer_mode(pb) : 1);
+    const int path = nbar ? 2 : 10 + 16 * (int)scorer_of(pb, P) + 3 * pb->precision + scorer_mode(pb);
     std::vector<int64_t> key = {pb->n_dot, pb->mode, path, pb->flags, P, (int64_t)(uintptr_t)V,
                                 (int64_t)(uintptr_t)n_out, (int64_t)(uintptr_t)nbar,
                                 (int64_t)(uintptr_t)saved, (int64_t)(uintptr_t)w->dr,
+                                (int64_t)(uintptr_t)w->rt,
                                 (int64_t)(uintptr_t)w->pr,
                                 (int64_t)(uintptr_t)w->bstats};
     auto it = w->graphs.find(key);
@@ -506,7 +543,8 @@ qa_status backward(const qa_problem *prob, const double *V_dev, const VGrid *vg,
 namespace {
 constexpr size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr size_t kScrDiag = 0;
-constexpr size_t kScrCounters = kScrDiag + align256(sizeof(DiagRec));
+constexpr size_t kScrRows = kScrDiag + align256(sizeof(DiagRec));
+constexpr size_t kScrCounters = kScrRows + align256(sizeof(RowTab));
 constexpr size_t kScrBstats = kScrCounters + align256(sizeof(int64_t) * kCounterWords);
 constexpr int64_t kScrBstatsWords = 4 * setup_blocks_max(QA_NOALLOC_MAX_PIXELS);
 constexpr size_t kScrPix = kScrBstats + align256(sizeof(int32_t) * kScrBstatsWords);
@@ -612,12 +650,13 @@ qa_status qa_ground_state_noalloc(const qa_problem *prob, const double *V_dev, i
     unsigned char *base;
     if ((st = scratch_address(&base))) return st;
     DiagRec *dr = reinterpret_cast<DiagRec *>(base + kScrDiag);
+    RowTab *rt = reinterpret_cast<RowTab *>(base + kScrRows);
     int64_t *counters = reinterpret_cast<int64_t *>(base + kScrCounters);
     int32_t *bstats = reinterpret_cast<int32_t *>(base + kScrBstats);
     PixRec *pr = reinterpret_cast<PixRec *>(base + kScrPix);
     hipStream_t s = (hipStream_t)hip_stream;
     if ((st = put_inputs(dr, prob, s))) return st;
-    return enqueue_path(dr, pr, counters, bstats, s, prob, V_dev, P, n_out_dev, nullptr, nullptr,
+    return enqueue_path(dr, rt, pr, counters, bstats, s, prob, V_dev, P, n_out_dev, nullptr, nullptr,
                         nullptr);
 }
 
@@ -655,7 +694,8 @@ qa_status qa_continuous_min(const qa_problem *prob, const double *V_dev, int64_t
     if ((st = grow_single(w, P))) return st;
     if ((st = upload_diag(w, prob))) return st;
     QA_HIP(launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
-                        prob->mode == QA_CLOSED, w->stream, x_out_dev, flags_out_dev));
+                        prob->mode == QA_CLOSED, kBoundNone, nullptr, w->stream, x_out_dev,
+                        flags_out_dev));
     w->bstats_used = setup_blocks(P, prob->n_dot);
     return read_stats(w, stats);
 }
@@ -1080,9 +1120,10 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
         for (auto &e : ev) (void)hipEventDestroy(e);
         return r;
     };
+    const Scorer sc = scorer_of(prob, P);
     auto setup = [&]() {
         return launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
-                            prob->mode == QA_CLOSED, s) == hipSuccess;
+                            prob->mode == QA_CLOSED, scorer_split(sc), w->rt, s) == hipSuccess;
     };
     // reps setup launches, then reps (setup, scorer) pairs: the scorer of a
     // pair reads what its setup has just written, as in a call
@@ -1092,7 +1133,7 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
     if (hipEventRecord(ev[1], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
     for (int r = 0; r < reps; ++r) {
         if (!setup()) return done(fail(QA_E_DEVICE, "setup launch failed"));
-        if (launch_scorer(w->dr, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
+        if (launch_scorer(sc, w->dr, w->rt, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
             return done(fail(QA_E_DEVICE, "scorer launch failed"));
     }
     if (hipEventRecord(ev[2], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
@@ -1123,6 +1164,7 @@ void qa_release(void *hip_stream)
     }
     (void)hipStreamSynchronize(w->stream);
     (void)hipFree(w->dr);
+    (void)hipFree(w->rt);
     (void)hipFree(w->pr);
     (void)hipFree(w->bstats);
     (void)hipFree(w->counters);

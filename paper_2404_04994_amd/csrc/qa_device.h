@@ -455,13 +455,15 @@ __device__ __forceinline__ double row_bcast_block(double x)
 // waves of the block may be doing anything meanwhile; the caller's next
 // block barrier publishes M.
 //
-// The pivots run over the high dots 8..n-1 first, then 0..7: after the high
-// pivots the working matrix holds (C_dd,HH)^{-1} in its high block, the Schur
-// complement C_LL - C_LH C_HH^{-1} C_HL = (A_LL)^{-1} in its low block and
-// C_HH^{-1} C_HL in its high-low block; the whole 16 x 16 matrix is copied to
-// S when S is given (identity rows and columns past n).
+// The pivots run over the high dots 8..n-1 first, then 6 and 7, then 0..5:
+// after the pivots on a high set H the working matrix holds (C_dd,HH)^{-1} in
+// its high block, the Schur complement C_LL - C_LH C_HH^{-1} C_HL = (A_LL)^{-1}
+// in its low block and C_HH^{-1} C_HL in its high-low block; the whole 16 x 16
+// matrix is copied to S after H = 8..n-1 and to S6 after H = 6..n-1, when they
+// are given (identity rows and columns past n).
 __device__ __forceinline__ void prep_inverse_wave(const double (&m0)[4], int n, double *M,
-                                                  double *red, double *S = nullptr)
+                                                  double *red, double *S = nullptr,
+                                                  double *S6 = nullptr)
 {
     // lane = 16 b + j: column j of rows 4 b .. 4 b + 3 (a DPP row of the
     // wave holds four matrix rows), so the pivot column of a lane's rows is a
@@ -473,10 +475,14 @@ __device__ __forceinline__ void prep_inverse_wave(const double (&m0)[4], int n, 
     double m[4] = {m0[0], m0[1], m0[2], m0[3]};
     static_for_dev<0, kMaxDot>([&](auto kc) {
         constexpr int kk = decltype(kc)::value;
-        constexpr int k = (kk + 8) & (kMaxDot - 1);
+        constexpr int k = kk < 8 ? kk + 8 : (kk < 10 ? kk - 2 : kk - 10);
         if (kk == 8 && S) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) S[(4 * b + q) * kMaxDot + j] = m[q];
+        }
+        if (kk == 10 && S6) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) S6[(4 * b + q) * kMaxDot + j] = m[q];
         }
         if (k < n) {
             // M[k][j] (pivot row) and M[4 b + q][k] (pivot column)
@@ -582,19 +588,7 @@ __device__ __forceinline__ void prep_tables_spread(DiagRec *dr, const double *M,
         if (lane == 0) {
             if (n >= 9 && S) {
                 dr->Hs[e] = (e < (1 << nh)) ? (float)(0.5 * hs) : 1e30f;
-                if (e == 0) {
-                    dr->sabsS = (float)(0.5 * sa);
-                    // closed-array terms: w = C_HH^{-1} C_HL 1, gamma = 1^T A_LL^{-1} 1
-                    double gam = 0.0;
-                    for (int i = 0; i < 8; ++i)
-                        for (int jj = 0; jj < 8; ++jj) gam += S[i * kMaxDot + jj];
-                    for (int jj = 0; jj < 8; ++jj) {
-                        double w = 0.0;
-                        for (int i = 0; i < 8; ++i) w += S[(8 + jj) * kMaxDot + i];
-                        dr->wB[jj] = (jj < nh) ? (float)w : 0.0f;
-                    }
-                    dr->inv2g = (float)(0.5 / gam);
-                }
+                if (e == 0) dr->sabsS = (float)(0.5 * sa);
             }
             if (n >= 9) {
                 dr->hlo[e] = (float)(0.5 * hl);
@@ -617,6 +611,99 @@ __device__ __forceinline__ void prep_tables_spread(DiagRec *dr, const double *M,
             } else {
                 dr->hs[e] = 0.5 * hl;
             }
+        }
+    }
+}
+
+// The row kernels' tables, from A and the elimination after the high pivots S
+// (both in LDS), in kRowUnits units of about a hundred instructions, one wave
+// each: eight rows of T, 64 entries of hs (a lane each, the quadratic form by
+// rows), or the rest.  Every read of A or S is a broadcast.
+constexpr int kRowUnits = 8 + 16 + 1;
+__device__ __forceinline__ void prep_row_unit(RowTab *rt, const double *A, const double *S, int n,
+                                              int unit)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    double bit[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) bit[i] = (lane >> i & 1) ? 1.0 : 0.0;
+    // sum of A_i0+i,col over the lane's bits i
+    auto dots = [&](int i0, int col) {
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) v = fma(bit[i], A[(i0 + i) * kMaxDot + col], v);
+        return v;
+    };
+    if (unit < 8) {
+        double al[6], base = 0.0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) al[j] = dots(0, 6 + j);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (unit >> j & 1) base += al[3 + j];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            double v = base;
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (r >> j & 1) v += al[j];
+            rt->T[8 * unit + r][lane] = v;
+        }
+    } else if (unit < 24) {
+        const int k = unit - 8, nh = n - 6;
+        if ((k * 64) >> nh) return;  // past the last high part
+        double h = 0.0;
+#pragma unroll
+        for (int x = 0; x < 10; ++x) {
+            if (x < nh) {
+                const double *row = S + (6 + x) * kMaxDot + 6;
+                double r = 0.5 * row[x];
+#pragma unroll
+                for (int y = 0; y < x; ++y)
+                    r = y < 6 ? fma(bit[y], row[y], r) : ((k >> (y - 6) & 1) ? r + row[y] : r);
+                h = x < 6 ? fma(bit[x], r, h) : ((k >> (x - 6) & 1) ? h + r : h);
+            }
+        }
+        rt->hs[k][lane] = (float)h;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            rt->lo[j][lane] = dots(0, 12 + j);
+            rt->hi[j][lane] = dots(6, 12 + j);
+        }
+        double lo = 0.0, hi = 0.0, hk = 0.0;
+#pragma unroll
+        for (int x = 0; x < 6; ++x) {
+            double r = 0.5 * A[x * kMaxDot + x], q = 0.5 * A[(6 + x) * kMaxDot + 6 + x];
+            double u = x < 4 ? 0.5 * A[(12 + (x & 3)) * kMaxDot + 12 + (x & 3)] : 0.0;
+#pragma unroll
+            for (int y = 0; y < x; ++y) {
+                r = fma(bit[y], A[x * kMaxDot + y], r);
+                q = fma(bit[y], A[(6 + x) * kMaxDot + 6 + y], q);
+                if (x < 4) u = fma(bit[y], A[(12 + x) * kMaxDot + 12 + y], u);
+            }
+            lo = fma(bit[x], r, lo);
+            hi = fma(bit[x], q, hi);
+            if (x < 4) hk = fma(bit[x], u, hk);
+        }
+        rt->hlo[lane] = lo;
+        rt->hhi[lane] = hi;
+        if (lane < 16) rt->hk[lane] = hk;
+        // w = C_HH^{-1} C_HL 1 (lane j < 10), sum|S| / 2, gamma = 1^T A_LL^{-1} 1
+        const int nh = n - 6;
+        double w = 0.0, sa = 0.0, gam = 0.0;
+        if (lane < nh) {
+            for (int i = 0; i < 6; ++i) w += S[(6 + lane) * kMaxDot + i];
+            for (int i = 0; i < nh; ++i) sa += fabs(S[(6 + lane) * kMaxDot + 6 + i]);
+        }
+        if (lane < 6)
+            for (int i = 0; i < 6; ++i) gam += S[lane * kMaxDot + i];
+        sa = row_sum(sa);
+        gam = row_sum(gam);
+        if (lane < 10) rt->wB[lane] = (float)w;
+        if (lane == 0) {
+            rt->sabsS = (float)(0.5 * sa);
+            rt->inv2g = (float)(0.5 / gam);
         }
     }
 }

@@ -133,6 +133,33 @@ __device__ __forceinline__ double wave_sum(double x)
     return x;
 }
 
+// C(m, k), the size of a closed candidate set of m free dots with k raised (a
+// table: the 64-bit divisions of the product form had cost the closed scorers
+// some hundred instructions per pixel)
+static __constant__ const uint16_t kBinomial[17][17] = {
+    {1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 3, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 4, 6, 4, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 5, 10, 10, 5, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 6, 15, 20, 15, 6, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 7, 21, 35, 35, 21, 7, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 8, 28, 56, 70, 56, 28, 8, 1, 0, 0, 0, 0, 0, 0, 0, 0},
+    {1, 9, 36, 84, 126, 126, 84, 36, 9, 1, 0, 0, 0, 0, 0, 0, 0},
+    {1, 10, 45, 120, 210, 252, 210, 120, 45, 10, 1, 0, 0, 0, 0, 0, 0},
+    {1, 11, 55, 165, 330, 462, 462, 330, 165, 55, 11, 1, 0, 0, 0, 0, 0},
+    {1, 12, 66, 220, 495, 792, 924, 792, 495, 220, 66, 12, 1, 0, 0, 0, 0},
+    {1, 13, 78, 286, 715, 1287, 1716, 1716, 1287, 715, 286, 78, 13, 1, 0, 0, 0},
+    {1, 14, 91, 364, 1001, 2002, 3003, 3432, 3003, 2002, 1001, 364, 91, 14, 1, 0, 0},
+    {1, 15, 105, 455, 1365, 3003, 5005, 6435, 6435, 5005, 3003, 1365, 455, 105, 15, 1, 0},
+    {1, 16, 120, 560, 1820, 4368, 8008, 11440, 12870, 11440, 8008, 4368, 1820, 560, 120, 16, 1},
+};
+__device__ __forceinline__ int64_t closed_states(int m, int k)
+{
+    return (k >= 0 && k <= m) ? kBinomial[m][k] : 0;
+}
+
 struct alignas(16) DiagRec {
     // inputs (written by the host, or by k_prep_batch): everything up to Cgd
     int32_t n, g, closed, nhat;
@@ -156,23 +183,36 @@ struct alignas(16) DiagRec {
     // FP64 copies of the matrix-core tables (the near-tie re-score)
     double T1d[16][8], T2d[16][8];
     double Hhid[256], hlod[256];
-    // bound-ordered search (N >= 9): with S = (C_dd,HH)^{-1}, the Schur
+    // bound-ordered search on the matrix cores (N >= 13): with S = (C_dd,HH)^{-1}, the Schur
     // complement of the low block in A, Hs = 1/2 b_hi^T S b_hi (1e30 past
     // 2^(N-8))
     float Hs[256];
     float sabsS;                  // sum |S_ij| / 2
-    // closed arrays: the low part's sum is fixed, which adds
-    // (m - mu - w^T b_hi)^2 / (2 gamma) to the bound (m = k - popc(b_hi)),
-    // w = S C_HL 1, gamma = 1^T A_LL^{-1} 1
-    float wB[8];
-    float inv2g;                  // 1 / (2 gamma)
-    float pad2[2];
+    float pad2[3];
 };
+
+// Tables of the FP64 row kernels (qa_rows.hip), one per diagram (N >= 9): the
+// low part is dots 0..5 (index lane, 64 values), the high part dots 6..N-1
+// (index c = c6 + 64 k, c6 over dots 6..11).  Written by the setup; the part up
+// to hs is copied to LDS as it is.
+struct alignas(16) RowTab {
+    double T[64][64];   // [c6][lane]: b_lo^T A_LH b_hi over dots 6..11
+    double lo[4][64];   // sum of A_i,12+j over the lane's dots among 0..5
+    double hi[4][64];   // the same over the lane's dots among 6..11
+    float hs[16][64];   // 1/2 b_hi^T S b_hi, S = C_dd^{-1} over the high dots
+    double hlo[64];     // 1/2 b^T A b over dots 0..5
+    double hhi[64];     // the same over dots 6..11
+    double hk[16];      // the same over dots 12..15
+    float wB[10];       // closed arrays: w and 1 / (2 gamma) of the low-sum term
+    float inv2g;
+    float sabsS;        // sum |S_ij| / 2
+};
+constexpr size_t kRowTabLdsBytes = offsetof(RowTab, hlo);
 
 // bytes of a DiagRec the host uploads (the inputs)
 constexpr size_t kDiagInputBytes = offsetof(DiagRec, one_c);
 
-struct alignas(8) PixRec {
+struct alignas(64) PixRec {  // 256 bytes, two 128-byte lines
     double g0[kMaxDot];   // A (n0 - x_u)
     double u0;            // U(n0)
     int16_t n0[kMaxDot];  // base state of the candidate set
@@ -182,12 +222,14 @@ struct alignas(8) PixRec {
     uint32_t guess;       // a state of the candidate set: the free dots whose x* rounds up,
                           // then the best single flip of a free dot if it lowers the energy
                           // (closed: the k free dots with the largest fractional parts)
-    // lower bound of the states of a high part b_hi (N >= 13, open):
-    // K + b_hi^T s + 1/2 b_hi^T S b_hi, s = S (n0 - x_u)_hi
-    float s[8];
+    // lower bound of the states of a high part b_hi (N >= 9):
+    // K + b_hi^T s + 1/2 b_hi^T S b_hi, s = S (n0 - x_u)_hi; the high part is
+    // dots 8..N-1 or 6..N-1, as the setup was asked for (BoundSplit)
+    float s[10];
     float K;
     float mu;             // closed: -1^T A_LL^{-1} g_lo (the low sum of the free minimiser)
     float eg;             // N = 16 lanes: U(n0 + guess) - U(n0), from FP64
+    float slack;          // margin of the row kernels' bound test (see the setup)
 };
 
 struct alignas(8) SavedRec {
@@ -273,6 +315,11 @@ struct InputChunk {
     double v[kChunkDoubles];  // part 0: C_dd, n x n; part 1: rows row0.. of C_gd, each g long
 };
 
+// which lower bound of a high part the setup forms per pixel (N >= 9): none,
+// with eight low dots (the matrix-core scorer) or with six (the FP64 row
+// kernels)
+enum BoundSplit : int { kBoundNone = 0, kBoundLow6 = 6, kBoundLow8 = 8 };
+
 // the setup kernel: one wave for the prologue, seven for the pixels
 constexpr int kSetupPixThreads = 7 * kWave;
 // its grid is largest for 16-lane pixel groups
@@ -295,23 +342,29 @@ hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s
 // prologue (every block; block 0 also stores A and the tables into dr and
 // clears the kCounterWords counters) and setup of every pixel; the per-block
 // counts {pixels, QP, doubled, QP failures} go to bstats[4 * block] for
-// setup_blocks(P, n_dot) blocks; x_out (P x N) / flags_out (P) are optional
+// setup_blocks(P, n_dot) blocks; split: the bound terms the scorer of this call
+// reads (kBoundNone for N <= 8); rt: the row kernels' tables (kBoundLow6); x_out (P x N) / flags_out (P) are optional
 // copies of x*; grid, when given and on, replaces the voltages V.  P >= 1.
 int64_t setup_blocks(int64_t P, int n_dot);
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
-                        int32_t *bstats, int n_dot, bool closed, hipStream_t s,
-                        double *x_out = nullptr, int32_t *flags_out = nullptr,
+                        int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
+                        hipStream_t s, double *x_out = nullptr, int32_t *flags_out = nullptr,
                         const VGrid *grid = nullptr);
 // T = 0 argmin in FP64 over the candidate set of every pixel
 hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                              int64_t *counters, int n_dot, hipStream_t s);
+// the same for N >= 9 in bound order (qa_rows.hip; setup split kBoundLow6);
+// mode as for launch_score_mfma
+hipError_t launch_rows_gs(const RowTab *rt, const PixRec *pr, int64_t P, int mode, int32_t *n_out,
+                          int64_t *counters, int n_dot, hipStream_t s);
 // the same in the table form (n_dot <= 8; the whole-box table from the setup)
 hipError_t launch_score_tab(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                             int64_t *counters, int n_dot, hipStream_t s);
 // matrix-core scorer at T = 0; mode 0: the dense box, 1: the sub-box of each
 // pixel's free dots (thresholded), 2: closed arrays (subsets of the free
-// dots with k raised); near ties re-scored in FP64 inside the kernel.  For
-// N >= 13 dots the candidate sets are searched in bound order unless exhaustive.
+// dots with k raised); near ties re-scored in FP64 inside the kernel.  Every
+// state of the set, or (exhaustive false: mode 0, N >= 13, split BF16, setup
+// split kBoundLow8) searched in bound order.
 hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int prec, int mode,
                              bool exhaustive, int32_t *n_out, int64_t *counters, int n_dot,
                              hipStream_t s);

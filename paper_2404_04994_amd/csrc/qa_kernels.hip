@@ -238,20 +238,24 @@ constexpr int kSetupThreads = kWave + kSetupPixThreads;
 static_assert(kSetupThreads >= kMaxDot * kMaxDot, "C_dd staging: one entry per thread");
 
 template <int NM, bool CLOSED>
-__global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec *__restrict__ dr,
+__global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict__ dr,
                                                          const double *__restrict__ V, int64_t P,
                                                          PixRec *__restrict__ pr,
                                                          int64_t *__restrict__ counters,
                                                          int32_t *__restrict__ bstats,
                                                          double *__restrict__ x_out,
                                                          int32_t *__restrict__ flags_out,
-                                                         const VGrid vg)
+                                                         const int split,
+                                                         RowTab *__restrict__ rt, const VGrid vg)
 {
     __shared__ double sCdd[kMaxDot * kMaxDot];  // C_dd (input)
     __shared__ double sA[kMaxDot * kMaxDot];    // A (symmetric), from wave 0
     __shared__ double sc[kMaxDot];              // C_dd 1
     __shared__ double red[8];                   // [4] 1^T C_dd 1, [5] sum|A| / 2
-    __shared__ double sS[kMaxDot * kMaxDot];    // the elimination after the high pivots, from wave 0
+    __shared__ double sS[kMaxDot * kMaxDot];    // the elimination after the pivots 8..15, from wave 0
+    __shared__ double sS6[NM == 16 ? kMaxDot * kMaxDot : 1];  // and after 6..15
+    __shared__ double sMult[NM == 16 ? kSetupPixThreads : 1];
+    __shared__ double sLam[NM == 16 && CLOSED ? kSetupPixThreads : 1];
     __shared__ double sG[kMaxGate * NM];        // C_gd transposed: sG[j * NM + i]
     __shared__ int cnt[4];
     // Staging in one round trip: every load below is issued before any of
@@ -324,16 +328,20 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
     const double one_c = red[4];
 
     double xu = 0.0, x = 0.0;
+    // KKT data of the continuous minimum for the bound: multipliers mu >= 0 of
+    // x >= 0 and lam of the closed sum (kkt false: x_u and zeros take their
+    // place, for which the bound below holds too), kept in LDS until the bound
+    bool kkt = true;
     int n0 = 0, k = -1, flags = 0, cflags = 0;
     uint32_t fm = 0;
     uint32_t gm = 0;  // rounding of x* inside the candidate set
     if (!pixel_wave) {
         // the inverse is the block's critical path: its wave issues first
         __builtin_amdgcn_s_setprio(3);
-        prep_inverse_wave(m4, n, sA, red, sS);
+        prep_inverse_wave(m4, n, sA, red, sS, NM == 16 ? sS6 : nullptr);
         // a grid of at least 256 blocks: wave 0 of block b fills energy-table
         // entry b while the pixel waves finish (off the kernel's tail)
-        if (gridDim.x >= 256) {
+        if (split != kBoundLow6 && gridDim.x >= 256) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -361,13 +369,17 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
         if (CLOSED) {
             const double lam = ((double)nhat - group_dsum<NM>(xu)) / one_c;
             x0 = is_dot ? xu + lam * sc[dot] : 0.0;
+            if (NM == 16) sLam[tp] = lam;
         }
         x = x0;
+        if (NM == 16) sMult[tp] = 0.0;
         uint32_t W = group_ballot<NM>(is_dot && x0 < 0.0);
         if (CLOSED && nhat == 0) {
             // x = 0 is the only admissible point of a closed empty array
             flags = W ? 1 : 0;
             x = 0.0;
+            kkt = false;
+            if (NM == 16) sLam[tp] = 0.0;
             W = 0;
         }
         if (W) {
@@ -417,6 +429,16 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
             }
             x = is_dot ? fmax(x, 0.0) : 0.0;
             flags = settled ? 1 : 3;
+            if (NM == 16 && split != kBoundNone) {
+                // on the active set v holds -mu; x = x_u + C mu + lam C 1
+                const double mult = (settled && (W >> dot & 1u)) ? fmax(-v, 0.0) : 0.0;
+                kkt = settled;
+                sMult[tp] = mult;
+                if (CLOSED)
+                    sLam[tp] = settled ? ((double)nhat - group_dsum<NM>(is_dot ? xu + sc[dot] * mult : 0.0)) /
+                                             one_c
+                                       : 0.0;
+            }
         }
 
         // candidate set (Sec. 3.2): base n0, free dots, closed: k raised free dots
@@ -460,6 +482,11 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
     }
     __syncthreads();  // A from wave 0
 
+    // the row kernels' tables, by the waves that have no pixels: one unit per
+    // block while the pixel waves form their records (small grids: below)
+    if (NM == 16 && split == kBoundLow6 && !pixel_wave && gridDim.x >= kRowUnits &&
+        blockIdx.x < kRowUnits)
+        prep_row_unit(rt, sA, sS6, n, (int)blockIdx.x);
     if (pixel_wave) {
         // g0 = A (n0 - x_u) and U(n0) = 1/2 (n0 - x_u)^T g0 (Eq. free_energy)
         const double z = is_dot ? (double)n0 - xu : 0.0;
@@ -481,7 +508,7 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
         // U(n0): b^T g0 + 1/2 b^T A b, with (A b)_dot the sum of the columns
         // of A that b raises
         double eg = 0.0;
-        if (NM == 16 && n >= 13) {
+        if (NM == 16 && split != kBoundNone) {
             double ab = 0.0;
             static_for_dev<0, NM>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
@@ -506,29 +533,51 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
                 }
             }
         }
-        // terms of the lower bound of the bound-ordered scorer (N >= 13):
-        // s = S z_hi and K = 1/2 z_hi^T s - U(n0) with S = (C_dd,HH)^{-1};
-        // closed arrays also mu = -1^T A_LL^{-1} g0_lo
+        // Terms of the lower bound of a high part (dots `split`..15).  With the
+        // multipliers of the continuous minimum x (A (x - x_u) = mu + lam 1)
+        //     U(n) = U(x) + mu^T n + 1/2 (n - x)^T A (n - x)
+        // for every n of the candidate set, and dropping mu_lo^T n_lo >= 0
+        // and minimising over a real-valued low part leaves
+        //     K + b_hi^T s + 1/2 b_hi^T S b_hi,   S = (C_dd,HH)^{-1},
+        // z = n0 - x, s = S z_hi + mu_hi, K = 1/2 z_hi^T S z_hi
+        // - 1/2 z^T (g0 + lam 1) relative to U(n0); closed arrays also
+        // mu' = -1^T A_LL^{-1} (A z)_lo with A z = g0 - mu - lam 1.  Around
+        // x_u instead (no multipliers) a dot held at zero far below its
+        // unconstrained charge loosens the bound by its whole multiplier:
+        // on the 4x4 array's sweeps that left up to 990 of 1024 rows.
         double sv = 0.0, Kb = 0.0, mu = 0.0;
-        if (NM == 16 && n >= 13) {
-            const int hd = dot >= 8 ? dot : 8;
-            double srow[8];
-            static_for_dev<0, 8>([&](auto qc) {
+        float slack = 0.0f;
+        if (NM == 16 && split != kBoundNone) {
+            const double *Sm = split == kBoundLow6 ? sS6 : sS;
+            const int hd = dot >= split ? dot : split;
+            const double zb = is_dot ? (double)n0 - (kkt ? x : xu) : 0.0;
+            const double mult = sMult[tp], lam_b = CLOSED ? sLam[tp] : 0.0;
+            double srow[10];
+            static_for_dev<0, 10>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                srow[q] = sS[hd * kMaxDot + 8 + q];
+                srow[q] = (q >= 2 || split == kBoundLow6) ? Sm[hd * kMaxDot + 6 + q] : 0.0;
             });
-            static_for_dev<0, 8>([&](auto qc) {
+            static_for_dev<0, 10>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                sv += srow[q] * group_bcast<NM, (8 + q) & (NM - 1)>(z, base);
+                sv += srow[q] * group_bcast<NM, (6 + q) & (NM - 1)>(zb, base);
             });
-            sv = dot >= 8 ? sv : 0.0;
-            Kb = 0.5 * group_dsum<NM>(z * sv) - u0;
+            sv = dot >= split ? sv : 0.0;
+            Kb = 0.5 * group_dsum<NM>(zb * (sv - (g0 + lam_b)));
+            sv += mult;
+            // What a row kernel adds to an energy before it compares it with the
+            // FP32 bound: the FP32 error of the bound (a dozen roundings of
+            // partial sums below |K| + sum|s| + the table's 1/2 sum|S|, which
+            // the kernel adds with the closed term), the rounding of eg, the
+            // FP64 rounding of the terms above, and 2e-9, so that every state
+            // within 1e-9 of the minimum lies in a computed row.
+            slack = 0x1p-19f * (fabsf((float)Kb) + (float)group_dsum<NM>(fabs(sv))) +
+                    0x1p-22f * fabsf((float)eg) + 0x1p-36f * fabsf((float)u0) + 2e-9f;
             if (CLOSED) {
                 double qrow = 0.0;
-                const int ld = dot < 8 ? dot : 0;
+                const int ld = dot < 6 ? dot : 0;  // (closed sets go to the row kernels)
 #pragma unroll
-                for (int q = 0; q < 8; ++q) qrow += sS[ld * kMaxDot + q];
-                mu = -group_dsum<NM>(dot < 8 ? qrow * g0 : 0.0);
+                for (int q = 0; q < 6; ++q) qrow += sS6[ld * kMaxDot + q];
+                mu = -group_dsum<NM>(dot < 6 ? qrow * (g0 - mult - lam_b) : 0.0);
             }
         }
 
@@ -538,11 +587,12 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
                 o->g0[q] = (q < NM) ? g0 : 0.0;
                 o->n0[q] = (int16_t)((q < NM) ? n0 : 0);
             }
-            if (dot >= 8) o->s[dot - 8] = (float)sv;
+            if (NM == 16 && split != kBoundNone && dot >= split) o->s[dot - split] = (float)sv;
             if (dot == 0) {
                 o->K = (float)Kb;
                 o->mu = (float)mu;
                 o->eg = (float)eg;
+                o->slack = slack;
                 o->u0 = u0;
                 o->free = fm;
                 o->k = k;
@@ -570,7 +620,14 @@ __global__ __launch_bounds__(kSetupThreads, CLOSED ? 3 : 4) void k_setup(DiagRec
         if (counters)
             for (int i = threadIdx.x; i < kCounterWords; i += blockDim.x) counters[i] = 0;
     }
-    if (gridDim.x < 256) prep_tables_spread(dr, sA, sS);
+    if (split == kBoundLow6) {
+        constexpr int kWaves = kSetupThreads / kWave;
+        if (NM == 16 && gridDim.x < kRowUnits)
+            for (int u = blockIdx.x * kWaves + tid / kWave; u < kRowUnits; u += gridDim.x * kWaves)
+                prep_row_unit(rt, sA, sS6, n, u);
+    } else if (gridDim.x < 256) {
+        prep_tables_spread(dr, sA, sS);
+    }
 }
 
 #define QA_DISPATCH_NM(n, CALL)                        \
@@ -589,18 +646,21 @@ int64_t setup_blocks(int64_t P, int n_dot)
 }
 
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
-                        int32_t *bstats, int n_dot, bool closed, hipStream_t s, double *x_out,
-                        int32_t *flags_out, const VGrid *sweep)
+                        int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
+                        hipStream_t s, double *x_out, int32_t *flags_out, const VGrid *sweep)
 {
+    if (split == kBoundLow6 && (!rt || n_dot < 9)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)setup_blocks(P, n_dot)), block(kSetupThreads);
     VGrid vg{};
     if (sweep) vg = *sweep;
     if (closed)
         QA_DISPATCH_NM(n_dot, hipLaunchKernelGGL((k_setup<NM_, true>), grid, block, 0, s, dr, V,
-                                                 P, pr, counters, bstats, x_out, flags_out, vg));
+                                                 P, pr, counters, bstats, x_out, flags_out,
+                                                 (int)split, rt, vg));
     else
         QA_DISPATCH_NM(n_dot, hipLaunchKernelGGL((k_setup<NM_, false>), grid, block, 0, s, dr, V,
-                                                 P, pr, counters, bstats, x_out, flags_out, vg));
+                                                 P, pr, counters, bstats, x_out, flags_out,
+                                                 (int)split, rt, vg));
     return hipGetLastError();
 }
 

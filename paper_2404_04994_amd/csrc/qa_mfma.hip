@@ -109,23 +109,6 @@ __device__ __forceinline__ void wave_sync()
 
 constexpr int kPrecFP32 = 1, kPrecX3 = 2, kPrecX2 = 3;
 
-#ifndef QA_SCORER_WAVES
-#define QA_SCORER_WAVES 3
-#endif
-// waves per SIMD of the bound-ordered scorer (measured): five for the FP32
-// dense box, four otherwise (the split-BF16 forms read their column
-// operands from LDS once per product, and a fifth wave per SIMD costs more
-// in LDS bandwidth than it hides)
-#ifndef QA_BOUND_WAVES
-#define QA_BOUND_WAVES(PREC, MODE) ((MODE) == kDense && (PREC) == kPrecFP32 ? 5 : 4)
-#endif
-#ifndef QA_BOUND_B_LDS
-#define QA_BOUND_B_LDS 1
-#endif
-#ifndef QA_BOUND_B_REGS
-#define QA_BOUND_B_REGS 0
-#endif
-
 // MODE kDense: the floor/ceil box.  kPruned: the thresholded candidate set
 // (Sec. 3.2.2), n0 + b with b a subset of the pixel's free dots.  kClosed:
 // closed arrays (Sec. 2, constraint iii), b a subset of the free dots with
@@ -143,7 +126,7 @@ constexpr int kPrecFP32 = 1, kPrecX3 = 2, kPrecX2 = 3;
 constexpr int kDense = 0, kPruned = 1, kClosed = 2;
 
 template <int PREC, int MODE>
-__global__ __launch_bounds__(256, QA_SCORER_WAVES) void k_score_mfma(const DiagRec *__restrict__ dr,
+__global__ __launch_bounds__(256, 3) void k_score_mfma(const DiagRec *__restrict__ dr,
                                                     const PixRec *__restrict__ pr, int64_t P,
                                                     int32_t *__restrict__ n_out,
                                                     int64_t *__restrict__ counters)
@@ -261,13 +244,7 @@ __global__ __launch_bounds__(256, QA_SCORER_WAVES) void k_score_mfma(const DiagR
             gabs += fabsf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(gl), i)));
         }
         if (MODE == kPruned) ncand += 1ll << __popc(F & ((1u << n) - 1u));
-        if (CLOSED) {
-            // C(free dots, k)
-            const int nf = __popc(F & ((1u << n) - 1u));
-            int64_t b = 1;
-            for (int j = 0; j < kc && j < nf; ++j) b = b * (nf - j) / (j + 1);
-            ncand += (kc >= 0 && kc <= nf) ? b : 0;
-        }
+        if (CLOSED) ncand += closed_states(__popc(F & ((1u << n) - 1u)), kc);
         // row tiles (high dots 12..15) and column tiles (low dots 4..7) that
         // raise no fixed dot (closed: and that can hold k raised dots)
         auto rt_ok = [&](int rt) {
@@ -581,9 +558,8 @@ __global__ __launch_bounds__(256, QA_SCORER_WAVES) void k_score_mfma(const DiagR
 }
 
 // ---------------------------------------------------------------------------
-// Bound-ordered search of the candidate sets of N >= 13 dots (more than one
-// row tile): the dense box, the thresholded sub-boxes (MODE kPruned) and the
-// closed subsets (kClosed).
+// Bound-ordered search of the dense box of N >= 13 dots (more than one row
+// tile) in the split-BF16 forms.
 //
 // The argmin over the 2^N states of the box is found without scoring all of
 // them.  With y = n0 - x_u (so g = A y and U(n0 + b) - U(n0) = b^T g +
@@ -593,9 +569,8 @@ __global__ __launch_bounds__(256, QA_SCORER_WAVES) void k_score_mfma(const DiagR
 //     E(b_hi, b_lo) >= L(b_hi) = K + b_hi^T s + 1/2 b_hi^T S b_hi,
 //     s = S y_hi,  K = 1/2 y_hi^T s - U(n0)
 // (the setup forms S in its Gauss-Jordan sweep, the table of
-// 1/2 b_hi^T S b_hi, and s and K of every pixel in FP64).
-// Closed arrays fix the low part's sum at m = k - popc(b_hi), which adds
-// (m - mu - w^T b_hi)^2 / (2 gamma) to the bound.
+// 1/2 b_hi^T S b_hi, and s and K of every pixel in FP64, around the continuous
+// minimum rather than x_u where dots are held at zero).
 // L is a lower bound for all 256 states of a high index, so a high index
 // whose bound lies above an upper bound of the best approximate energy (plus
 // a margin that covers the FP32 error of the bound and three times the
@@ -618,14 +593,12 @@ __global__ __launch_bounds__(256, QA_SCORER_WAVES) void k_score_mfma(const DiagR
 // the column operands sit in an LDS table (one read per product) so that
 // the registers allow four or five waves.
 // ---------------------------------------------------------------------------
-template <int PREC, int MODE>
-__global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound(const DiagRec *__restrict__ dr,
+template <int PREC>
+__global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restrict__ dr,
                                                      const PixRec *__restrict__ pr, int64_t P,
                                                      int32_t *__restrict__ n_out,
                                                      int64_t *__restrict__ counters)
 {
-    constexpr bool PRUNED = MODE != kDense;
-    constexpr bool CLOSED = MODE == kClosed;
     __shared__ float sT1[16][8];
     __shared__ float sT2[16][8];
     __shared__ float sH[256];
@@ -639,7 +612,7 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
     __shared__ uint8_t sList[4][256];            // per wave: high index of every scored row
     __shared__ uint32_t sBand[4][128];           // per wave: near-tie states to re-score
     __shared__ uint4 sB[16][64];                 // column operands: [column tile][lane]
-    __shared__ unsigned long long sflag, sgap, srows, scand;
+    __shared__ unsigned long long sflag, sgap, srows;
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int q = lane >> 4;
@@ -653,33 +626,22 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
     const int nrt = 1 << (nh - 4);
     const float sumabs = dr->sumabs;
     const float hsabs = dr->sabsS;
-    // closed arrays: w and 1 / (2 gamma) of the low-sum term of the bound
-    float wb[8];
-    float wabs = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        wb[j] = CLOSED ? dr->wB[j] : 0.0f;
-        wabs += fabsf(wb[j]);
-    }
-    const float inv2g = CLOSED ? dr->inv2g : 0.0f;
     // the first pixel's record, requested before the tables are staged:
-    // lane i < 16 holds g0_i and n0_i, lanes 8..15 also s_{i-8}, lane 0 K,
-    // lane 1 mu (vector loads, one pixel ahead from here on)
+    // lane i < 16 holds g0_i and n0_i, lanes 8..15 also s_{i-8}, lane 0 K
+    // (vector loads, one pixel ahead from here on)
     // (read unconditionally, from the last pixel for waves past the end:
     // P >= 1, and no branch holds the staging below behind these loads)
     const int64_t w0 = wave < P ? wave : P - 1;
-    // byte offset of the lane's float in the record (s_{li-8}, mu or K),
+    // byte offset of the lane's float in the record (s_{li-8} or K),
     // fixed per lane, so the per-pixel read is one load without branches
     const int soff = li >= 8 ? (int)offsetof(PixRec, s) + 4 * (li - 8)
-                             : (li == 1 ? (int)offsetof(PixRec, mu) : (int)offsetof(PixRec, K));
+                             : (int)offsetof(PixRec, K);
     auto rec_f = [&](int64_t i) -> float {
         return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(pr + i) + soff);
     };
     double gnext = pr[w0].g0[li];
     int nnext = pr[w0].n0[li];
     float snext = rec_f(w0);
-    uint32_t fnext = PRUNED ? pr[w0].free : 0u;
-    int knext = CLOSED ? pr[w0].k : 0;
     float egnext = pr[w0].eg;
     {
         // the diagram's tables, one entry per thread (the blocks are 256
@@ -703,7 +665,7 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         sHs[e] = hs;
         sHlo[e] = hl;
     }
-    if (threadIdx.x == 0) { sflag = 0; sgap = 0; srows = 0; scand = 0; }
+    if (threadIdx.x == 0) { sflag = 0; sgap = 0; srows = 0; }
     __syncthreads();
 
     // pixel-independent column operands (as in the dense scorer), from the
@@ -712,12 +674,7 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         const int clo = ct * 16 + mrow;
         const float h = sHlo[clo];
         uint4 w;
-        if (PREC == kPrecFP32) {
-            w.x = fbits((float)((clo >> q) & 1));
-            w.y = fbits((float)((clo >> (4 + q)) & 1));
-            w.z = fbits(h);  // h_lo of the lane's column, added with C before the products
-            w.w = 0u;
-        } else if (q < 3) {
+        if (q < 3) {
             uint32_t d4[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d)
@@ -734,28 +691,10 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         return w;
     };
     // in LDS, one table per block (the operands depend on the lane, not the
-    // wave): wave w builds column tiles 4 w .. 4 w + 3.  The near-tie sweep
-    // reads them there; the main sweep too, or from registers.
+    // wave): wave w builds column tiles 4 w .. 4 w + 3
 #pragma unroll
     for (int k = 0; k < 4; ++k) sB[4 * wv + k][lane] = col_operand(4 * wv + k);
     __syncthreads();
-    auto bop_lds = [&](int ct) -> uint4 { return sB[ct][lane]; };
-#if QA_BOUND_B_LDS
-    // the first QA_BOUND_B_REGS column tiles' operands also in registers
-    // (less LDS traffic per product), the others read from LDS
-    // (split-BF16 forms only: the FP32 form's registers are taken)
-    constexpr int kBRegs = PREC == kPrecFP32 ? 0 : QA_BOUND_B_REGS;
-    uint4 bw[kBRegs > 0 ? kBRegs : 1];
-#pragma unroll
-    for (int ct = 0; ct < kBRegs; ++ct) bw[ct] = col_operand(ct);
-    auto bop = [&](int ct) -> uint4 { return ct < kBRegs ? bw[ct] : bop_lds(ct); };
-#else
-    // in registers for the whole kernel
-    uint4 bw[16];
-#pragma unroll
-    for (int ct = 0; ct < 16; ++ct) bw[ct] = col_operand(ct);
-    auto bop = [&](int ct) -> uint4 { return bw[ct]; };
-#endif
     // constant chunk of an unused row: C = 1e30, so its states never win
     uint2 csent;
     {
@@ -763,11 +702,10 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         const float c1 = trunc16(C);
         const float cr = C - c1;
         const float c2 = trunc16(cr);
-        csent = (PREC == kPrecFP32) ? make_uint2(fbits(C), 0u)
-                                    : make_uint2(pack2(c1, c2), pack2(cr - c2, 1.0f));
+        csent = make_uint2(pack2(c1, c2), pack2(cr - c2, 1.0f));
     }
 
-    int64_t nflag = 0, ngap = 0, nrows = 0, ncand = 0;
+    int64_t nflag = 0, ngap = 0, nrows = 0;
     uint8_t *list = sList[wv];
     double *g64 = sG64[wv];
     float *ptab = sPt[wv];
@@ -776,41 +714,23 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         const double gcur = gnext;
         const int ncur = nnext;
         const float scur = snext;
-        // free dots, raised count and guess of the pixel (wave-uniform)
-        const uint32_t F = PRUNED ? __builtin_amdgcn_readfirstlane(fnext) : 0xFFFFu;
-        const int kc = CLOSED ? __builtin_amdgcn_readfirstlane(knext) : 0;
+        // the guess of the pixel (wave-uniform)
         const float egf = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(egnext)));
         if (p + nwaves < P) {
             gnext = pr[p + nwaves].g0[li];
             nnext = pr[p + nwaves].n0[li];
             snext = rec_f(p + nwaves);
-            if (PRUNED) fnext = pr[p + nwaves].free;
-            if (CLOSED) knext = pr[p + nwaves].k;
             egnext = pr[p + nwaves].eg;
         }
-        // g0 beyond n is zero in the record.  Thresholded and closed sets: a
-        // fixed dot's entry carries the penalty 2^100 (states raising it never
-        // win; the others score as in the dense form), the error bound takes
-        // the unpenalised values.
+        // g0 beyond n is zero in the record
         const float gl = (float)gcur;
-        const float glp = (PRUNED && !(F >> li & 1u)) ? 0x1p100f : gl;
         float g[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            g[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(glp), i));
+            g[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gl), i));
         // sum |g_i| (every 16-lane row holds g0_0..15)
         const float gabs = __int_as_float(__builtin_amdgcn_readfirstlane(
             __float_as_int(row_sumf(fabsf(gl)))));
-        const uint32_t Fhi = (F >> 8) & 0xFFu;
-        const int nflo = __popc(F & 0xFFu);
-        if (MODE == kPruned) ncand += 1ll << __popc(F & ((1u << n) - 1u));
-        if (CLOSED) {
-            // C(free dots, k)
-            const int nf = __popc(F & ((1u << n) - 1u));
-            int64_t bc = 1;
-            for (int j = 0; j < kc && j < nf; ++j) bc = bc * (nf - j) / (j + 1);
-            ncand += (kc >= 0 && kc <= nf) ? bc : 0;
-        }
         // ---- the bound terms of the setup: s = S (n0 - x_u)_hi and K ----
         if (lane < kMaxDot) g64[lane] = gcur;  // FP64 g of the near-tie re-score
         float sb[8];
@@ -820,55 +740,32 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         const float sabs = __int_as_float(__builtin_amdgcn_readfirstlane(
             __float_as_int(row_sumf(li >= 8 ? fabsf(scur) : 0.0f))));
         const float Kf = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scur), 0));
-        const float muf = CLOSED ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scur), 1))
-                                 : 0.0f;
         // Certified bound on |E_approx - E| (as in the dense scorer), and the
         // FP32 error of the bound: at most a dozen roundings of partial sums
         // that are bounded by |K| + sum|s| + 1/2 sum|S|; 2^-19 of that covers
         // them with room to spare.
         const float S = gabs + sumabs;
         const float delta = (PREC == kPrecX2 ? 0x1p-15f : 0x1p-17f) * S;
-        // closed: the low-sum term (m - mu - w^T b_hi)^2 / (2 gamma) adds the
-        // FP32 error of a square of terms bounded by 8 + |mu| + sum|w|
-        const float lsum = 8.0f + fabsf(muf) + wabs;
-        const float margin = 4.0f * delta + 0x1p-19f * (fabsf(Kf) + sabs + hsabs) +
-                             (CLOSED ? 0x1p-19f * lsum * lsum * inv2g : 0.0f);
+        const float margin = 4.0f * delta + 0x1p-19f * (fabsf(Kf) + sabs + hsabs);
 
         // ---- per lane: the bounds of high indices (q + 4 e4) * 16 + row.
         // Bits 0..3 of the index are the lane's row, bits 4 and 5 its quarter
         // q, bits 6 and 7 the compile-time e4: the lane's part of b_hi^T s
-        // (and of w^T b_hi, popc) is summed once, e4's part added per index.
-        float Rb = Kf, Wb = 0.0f;
+        // is summed once, e4's part added per index.
+        float Rb = Kf;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (mrow >> j & 1) {
-                Rb += sb[j];
-                Wb += wb[j];
-            }
-        }
-        if (q & 1) { Rb += sb[4]; Wb += wb[4]; }
-        if (q & 2) { Rb += sb[5]; Wb += wb[5]; }
-        const float s67 = sb[6] + sb[7], w67 = wb[6] + wb[7];
-        const int pcl = __popc((uint32_t)mrow) + __popc((uint32_t)q);
+        for (int j = 0; j < 4; ++j)
+            if (mrow >> j & 1) Rb += sb[j];
+        if (q & 1) Rb += sb[4];
+        if (q & 2) Rb += sb[5];
+        const float s67 = sb[6] + sb[7];
         float lb[4];
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             const int rt = q + 4 * e4;
             const int chi = rt * 16 + mrow;
             const float R = e4 == 0 ? Rb : Rb + (e4 == 1 ? sb[6] : (e4 == 2 ? sb[7] : s67));
-            float L = R + sHs[chi];
-            bool ok = rt < nrt;
-            if (PRUNED) ok = ok && !((uint32_t)chi & ~Fhi);  // raises a fixed high dot
-            if (CLOSED) {
-                // m raised low dots: none of this high part's states is admissible
-                // unless 0 <= m <= free low dots
-                const int m = kc - (pcl + __popc((uint32_t)e4));
-                const float W = e4 == 0 ? Wb : Wb + (e4 == 1 ? wb[6] : (e4 == 2 ? wb[7] : w67));
-                const float dm = ((float)m - muf) - W;
-                L += dm * dm * inv2g;
-                ok = ok && m >= 0 && m <= nflo;
-            }
-            lb[e4] = ok ? L : INFINITY;
+            lb[e4] = rt < nrt ? R + sHs[chi] : INFINITY;
         }
         // b_hi^T g_hi over the low four and the high four bits of the high
         // index (lanes 0..15 and 16..31), for the constant chunks
@@ -881,8 +778,7 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
             ptab[lane] = v;
         }
         // The rows to score.  The setup's guess (the rounding of x* and its
-        // best single flip when that lowers the energy; closed: the k free
-        // dots with the largest fractional parts) is a state of
+        // best single flip when that lowers the energy) is a state of
         // the candidate set; its energy E_g (FP64 in the setup, rounded to
         // FP32) bounds the approximate best from above (by E_g + 1.1 delta),
         // so a high part whose bound exceeds E_g + margin + delta holds
@@ -946,39 +842,17 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         }
         wave_sync();  // the row list and the b_hi^T g_hi tables
 
-        // g_{2q}, g_{2q+1} (split-BF16 forms) or g_q, g_{4+q} (FP32) of this lane
+        // g_{2q}, g_{2q+1} of this lane
         float ga = g[0], gb = g[1];
 #pragma unroll
-        for (int d = 1; d < 4; ++d) {
+        for (int d = 1; d < 4; ++d)
             if (q == d) {
-                ga = (PREC == kPrecFP32) ? g[d] : g[2 * d];
-                gb = (PREC == kPrecFP32) ? g[4 + d] : g[2 * d + 1];
+                ga = g[2 * d];
+                gb = g[2 * d + 1];
             }
-        }
-        if (PREC == kPrecFP32) gb = (q == 0) ? g[4] : gb;
 
-        auto ct_ok = [&](int ct) { return !PRUNED || !(((uint32_t)ct << 4) & ~F & 0xF0u); };
         // C(c_hi) in FP32: the same sums as b_hi^T g_hi + table
         auto cconst = [&](int chi) { return (ptab[chi & 15] + ptab[16 + (chi >> 4)]) + sH[chi]; };
-        // closed: popcounts of this lane's four elements of tile t less that of
-        // the column tile (rows 4q..4q+3, column bits mrow)
-        auto elem_pc = [&](int t, int (&eq)[4]) {
-            if (CLOSED) {
-                const uint32_t r4 = *reinterpret_cast<const uint32_t *>(&list[t * 16 + 4 * q]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    eq[i] = __popc((r4 >> (8 * i)) & 0xFFu) + __popc((uint32_t)mrow);
-            }
-        };
-        // closed: elements whose state does not raise exactly k dots are +inf
-        auto qualify = [&](f32x4_t d, const int (&eq)[4], int ct) -> f32x4_t {
-            if (CLOSED) {
-                const int r = kc - __popc((uint32_t)ct);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) d[i] = (eq[i] == r) ? d[i] : INFINITY;
-            }
-            return d;
-        };
         // The A operand of tile t (row r of the tile is high index
         // list[16 t + r]; unused rows past cnt get the sentinel constant
         // chunk), in two steps so that the next tile's LDS reads are in
@@ -986,7 +860,7 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         // tables, assemble forms the operand.
         struct Rows {
             float t1a, t1b, t2a, t2b;  // T1 and T2 entries of the lane's two dots
-            float c[4];                // X3/X2: c[0] = C of the lane's row; FP32: C of rows 4q + i
+            float c;                   // C of the lane's row
             bool real;
         };
         auto fetch = [&](int t) -> Rows {
@@ -995,99 +869,64 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
             r.real = idx < cnt;
             const int chi = r.real ? (int)list[idx] : 0;
             const int row = chi & 15, rtt = chi >> 4;
-            const int da = (PREC == kPrecFP32) ? q : 2 * q;
-            const int db = (PREC == kPrecFP32) ? 4 + q : 2 * q + 1;
-            r.t1a = sT1[row][da];
-            r.t1b = sT1[row][db];
-            r.t2a = sT2[rtt][da];
-            r.t2b = sT2[rtt][db];
-            if (PREC == kPrecFP32) {
-                // C of the four output rows 4q..4q+3 of this lane: the
-                // accumulator starts at C(row) + h_lo(column), so two
-                // K = 4 products per tile suffice
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int ri = t * 16 + 4 * q + i;
-                    r.c[i] = ri < cnt ? cconst(list[ri]) : 1e30f;
-                }
-            } else {
-                r.c[0] = r.real ? cconst(chi) : 0.0f;
-            }
+            r.t1a = sT1[row][2 * q];
+            r.t1b = sT1[row][2 * q + 1];
+            r.t2a = sT2[rtt][2 * q];
+            r.t2b = sT2[rtt][2 * q + 1];
+            r.c = r.real ? cconst(chi) : 0.0f;
             return r;
         };
-        auto assemble = [&](const Rows &r, Pack8 &a, float (&af)[6]) {
+        auto assemble = [&](const Rows &r, Pack8 &a) {
             const float v0 = (ga + r.t1a) + r.t2a;
             const float v1 = (gb + r.t1b) + r.t2b;
-            if (PREC == kPrecFP32) {
-                af[0] = v0;
-                af[1] = v1;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) af[2 + i] = r.c[i];
-            } else {
-                uint2 cw = csent;
-                if (r.real) {
-                    const float C = r.c[0];
-                    const float c1 = trunc16(C);
-                    const float cr = C - c1;
-                    const float c2 = trunc16(cr);
-                    cw = make_uint2(pack2(c1, c2), pack2(cr - c2, 1.0f));
-                }
-                uint32_t R0, R1, R2;
-                if (PREC == kPrecX3) {
-                    const float a0 = trunc16(v0), b0 = trunc16(v1);
-                    const float r0 = v0 - a0, s0 = v1 - b0;
-                    const float a1 = trunc16(r0), b1 = trunc16(s0);
-                    R0 = pack2(a0, b0);
-                    R1 = pack2(a1, b1);
-                    R2 = pack2(r0 - a1, s0 - b1);
-                } else {
-                    const float a0 = rne16(v0), b0 = rne16(v1);
-                    R0 = pack2(a0, b0);
-                    R1 = pack2(rne16(v0 - a0), rne16(v1 - b0));
-                    R2 = 0u;
-                }
-                uint32_t R3 = (q == 2) ? 0x3F803F80u : 0u;
-                R3 = (q == 1) ? cw.y : R3;
-                R3 = (q == 0) ? cw.x : R3;
-                const auto t02 = __builtin_amdgcn_permlane32_swap(R0, R2, false, false);
-                const auto t13 = __builtin_amdgcn_permlane32_swap(R1, R3, false, false);
-                const auto u01 = __builtin_amdgcn_permlane16_swap(t02[0], t13[0], false, false);
-                const auto u23 = __builtin_amdgcn_permlane16_swap(t02[1], t13[1], false, false);
-                a.u[0] = u01[0];
-                a.u[1] = u01[1];
-                a.u[2] = u23[0];
-                a.u[3] = u23[1];
+            uint2 cw = csent;
+            if (r.real) {
+                const float C = r.c;
+                const float c1 = trunc16(C);
+                const float cr = C - c1;
+                const float c2 = trunc16(cr);
+                cw = make_uint2(pack2(c1, c2), pack2(cr - c2, 1.0f));
             }
-        };
-        auto build_rows = [&](int t, Pack8 &a, float (&af)[6]) { assemble(fetch(t), a, af); };
-        auto tile = [&](const Pack8 &a, const float (&af)[6], int ct,
-                        bool from_lds = false) -> f32x4_t {
-            f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            const uint4 bb = from_lds ? bop_lds(ct) : bop(ct);
-            if (PREC == kPrecFP32) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = af[2 + i] + __uint_as_float(bb.z);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(af[0], __uint_as_float(bb.x), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(af[1], __uint_as_float(bb.y), acc, 0, 0, 0);
+            uint32_t R0, R1, R2;
+            if (PREC == kPrecX3) {
+                const float a0 = trunc16(v0), b0 = trunc16(v1);
+                const float r0 = v0 - a0, s0 = v1 - b0;
+                const float a1 = trunc16(r0), b1 = trunc16(s0);
+                R0 = pack2(a0, b0);
+                R1 = pack2(a1, b1);
+                R2 = pack2(r0 - a1, s0 - b1);
             } else {
-                Pack8 b;
-                b.u[0] = bb.x; b.u[1] = bb.y; b.u[2] = bb.z; b.u[3] = bb.w;
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc, 0, 0, 0);
+                const float a0 = rne16(v0), b0 = rne16(v1);
+                R0 = pack2(a0, b0);
+                R1 = pack2(rne16(v0 - a0), rne16(v1 - b0));
+                R2 = 0u;
             }
-            return acc;
+            uint32_t R3 = (q == 2) ? 0x3F803F80u : 0u;
+            R3 = (q == 1) ? cw.y : R3;
+            R3 = (q == 0) ? cw.x : R3;
+            const auto t02 = __builtin_amdgcn_permlane32_swap(R0, R2, false, false);
+            const auto t13 = __builtin_amdgcn_permlane32_swap(R1, R3, false, false);
+            const auto u01 = __builtin_amdgcn_permlane16_swap(t02[0], t13[0], false, false);
+            const auto u23 = __builtin_amdgcn_permlane16_swap(t02[1], t13[1], false, false);
+            a.u[0] = u01[0];
+            a.u[1] = u01[1];
+            a.u[2] = u23[0];
+            a.u[3] = u23[1];
         };
-        // the four column tiles 4 cg .. 4 cg + 3 of row tile (a, af): the
-        // lane's 16 elements (element 4 k + i: column tile 4 cg + k, output
-        // row 4 q + i); column tiles without a candidate read +inf
-        auto group = [&](const Pack8 &a, const float (&af)[6], const int (&eq)[4], auto cgc,
-                         f32x4_t (&d)[4]) {
+        auto build_rows = [&](int t, Pack8 &a) { assemble(fetch(t), a); };
+        auto tile = [&](const Pack8 &a, int ct) -> f32x4_t {
+            const uint4 bb = sB[ct][lane];
+            Pack8 b;
+            b.u[0] = bb.x; b.u[1] = bb.y; b.u[2] = bb.z; b.u[3] = bb.w;
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f},
+                                                           0, 0, 0);
+        };
+        // the four column tiles 4 cg .. 4 cg + 3 of row tile a: the lane's 16
+        // elements (element 4 k + i: column tile 4 cg + k, output row 4 q + i)
+        auto group = [&](const Pack8 &a, auto cgc, f32x4_t (&d)[4]) {
             constexpr int cg = decltype(cgc)::value;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int ct = 4 * cg + k;
-                if (ct_ok(ct)) d[k] = qualify(tile(a, af, ct), eq, ct);
-                else d[k] = f32x4_t{INFINITY, INFINITY, INFINITY, INFINITY};
-            }
+            for (int k = 0; k < 4; ++k) d[k] = tile(a, 4 * cg + k);
         };
         // Per lane: the three smallest group minima b1 <= b2 <= b3 and the
         // group codes 4 t + cg of the first two (a1, a2), a group being the
@@ -1096,18 +935,13 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
         int a1 = 0, a2 = 0;
         uint32_t ac0 = 0, ac1 = 0, ac2 = 0, ac3 = 0;  // A operand of tile 0
-        float afc0 = 0.0f, afc1 = 0.0f, afc2 = 0.0f, afc3 = 0.0f, afc4 = 0.0f, afc5 = 0.0f;
-        auto score = [&](int t, const Pack8 &a, const float (&af)[6]) {
-            int eq[4];
-            elem_pc(t, eq);
+        auto score = [&](int t, const Pack8 &a) {
             sfor<0, 4>([&](auto cgc) {
                 constexpr int cg = decltype(cgc)::value;
                 float m = INFINITY;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const int ct = 4 * cg + k;
-                    if (!ct_ok(ct)) continue;
-                    const f32x4_t d = qualify(tile(a, af, ct), eq, ct);
+                    const f32x4_t d = tile(a, 4 * cg + k);
                     m = __builtin_fminf(m, __builtin_fminf(d[0], d[1]));
                     m = __builtin_fminf(m, __builtin_fminf(d[2], d[3]));
                 }
@@ -1132,15 +966,12 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
             Rows rn = fetch(t0);
             for (int t = t0; t < t1; ++t) {
                 Pack8 a;
-                float af[6];
-                assemble(rn, a, af);
+                assemble(rn, a);
                 if (t + 1 < t1) rn = fetch(t + 1);
                 if (t == 0) {
                     ac0 = a.u[0]; ac1 = a.u[1]; ac2 = a.u[2]; ac3 = a.u[3];
-                    afc0 = af[0]; afc1 = af[1]; afc2 = af[2];
-                    afc3 = af[3]; afc4 = af[4]; afc5 = af[5];
                 }
-                score(t, a, af);
+                score(t, a);
             }
         };
         if (!by_guess) {
@@ -1178,6 +1009,14 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
             swap_pair([](uint32_t v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
             swap_pair([](uint32_t v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
         }
+        // the A operand of tile t once more
+        auto operand = [&](int t, Pack8 &a) {
+            if (t == 0) {
+                a.u[0] = ac0; a.u[1] = ac1; a.u[2] = ac2; a.u[3] = ac3;
+            } else {
+                build_rows(t, a);
+            }
+        };
         const float wmin = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m1)));
         const float wsec = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m2)));
         const unsigned long long hit = __ballot(b1 == wmin);
@@ -1187,19 +1026,10 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         const int tw = aw >> 2, cgw = aw & 3;
         {
             Pack8 a;
-            float af[6];
-            if (tw == 0) {
-                a.u[0] = ac0; a.u[1] = ac1; a.u[2] = ac2; a.u[3] = ac3;
-                af[0] = afc0; af[1] = afc1; af[2] = afc2;
-                af[3] = afc3; af[4] = afc4; af[5] = afc5;
-            } else {
-                build_rows(tw, a, af);
-            }
-            int eq[4];
-            elem_pc(tw, eq);
+            operand(tw, a);
             f32x4_t d[4] = {};
             sfor<0, 4>([&](auto cgc) {
-                if (decltype(cgc)::value == cgw) group(a, af, eq, cgc, d);
+                if (decltype(cgc)::value == cgw) group(a, cgc, d);
             });
             if (lane == winner) {
 #pragma unroll
@@ -1268,11 +1098,10 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
             wave_sync();
             nb = 0;
         };
-        // the in-band states of column tile ct of row tile (a, af) = tile t
+        // the in-band states of column tile ct of row tile a = tile t
         // into the band list
-        auto gather = [&](int t, const Pack8 &a, const float (&af)[6], const int (&eq)[4], int ct) {
-            if (!ct_ok(ct)) return;
-            const f32x4_t d = qualify(tile(a, af, ct, true), eq, ct);
+        auto gather = [&](int t, const Pack8 &a, int ct) {
+            const f32x4_t d = tile(a, ct);
             const float dm = fminf(fminf(d[0], d[1]), fminf(d[2], d[3]));
             if (!__ballot(dm <= thr)) return;
 #pragma unroll
@@ -1289,15 +1118,6 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
                 if (nb >= 64) flush();
             }
         };
-        auto operand = [&](int t, Pack8 &a, float (&af)[6]) {
-            if (t == 0) {
-                a.u[0] = ac0; a.u[1] = ac1; a.u[2] = ac2; a.u[3] = ac3;
-                af[0] = afc0; af[1] = afc1; af[2] = afc2;
-                af[3] = afc3; af[4] = afc4; af[5] = afc5;
-            } else {
-                build_rows(t, a, af);
-            }
-        };
         if (!__ballot(b3 <= thr)) {
             // no lane has a third group in the band: the in-band states lie
             // in the groups a1 (where b1 <= thr) and a2 (where b2 <= thr) of
@@ -1310,22 +1130,16 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
                 gm &= gm - 1;
                 const int t = gc >> 2, cgs = gc & 3;
                 Pack8 a;
-                float af[6];
-                int eq[4];
-                operand(t, a, af);
-                elem_pc(t, eq);
+                operand(t, a);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) gather(t, a, af, eq, 4 * cgs + k);
+                for (int k = 0; k < 4; ++k) gather(t, a, 4 * cgs + k);
             }
         } else {
             // otherwise every scored row tile
             for (int t = 0; t < ntiles; ++t) {
                 Pack8 a;
-                float af[6];
-                int eq[4];
-                operand(t, a, af);
-                elem_pc(t, eq);
-                for (int ct = 0; ct < 16; ++ct) gather(t, a, af, eq, ct);
+                operand(t, a);
+                for (int ct = 0; ct < 16; ++ct) gather(t, a, ct);
             }
         }
         if (nb) flush();
@@ -1370,15 +1184,13 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
         if (nflag) atomicAdd(&sflag, (unsigned long long)nflag);
         if (ngap) atomicAdd(&sgap, (unsigned long long)ngap);
         if (nrows) atomicAdd(&srows, (unsigned long long)nrows);
-        if (ncand) atomicAdd(&scand, (unsigned long long)ncand);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         block_add_counter(counters, C_NEAR_TIE, (int64_t)sflag);
         block_add_counter(counters, C_GAP_1E9, (int64_t)sgap);
         block_add_counter(counters, C_SCORED, (int64_t)srows << 8);  // 256 states per row
-        if (PRUNED) block_add_counter(counters, C_CANDIDATES, (int64_t)scand);  // summed per pixel
-        else if (blockIdx.x == 0) block_add_counter(counters, C_CANDIDATES, P << n);
+        if (blockIdx.x == 0) block_add_counter(counters, C_CANDIDATES, P << n);
     }
 }
 
@@ -1387,9 +1199,9 @@ __global__ __launch_bounds__(256, QA_BOUND_WAVES(PREC, MODE)) void k_score_bound
 template <typename Kernel>
 static int resident_blocks(Kernel kernel, int slot)
 {
-    static int cache[24][64];
+    static int cache[11][64];
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || slot < 0 || slot >= 24) return 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || slot < 0 || slot >= 11) return 0;
     int &c = cache[slot][dev];
     if (c) return c;
     int cus = 0, per_cu = 0;
@@ -1422,20 +1234,12 @@ hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int
 {
     if (n_dot < 9 || n_dot > 16 || mode < kDense || mode > kClosed) return hipErrorInvalidValue;
     if (P <= 0) return hipSuccess;
-    if (n_dot >= 13 && !exhaustive) {
-#define QA_BOUND_CASE(PR, MD, SLOT)                                                             \
-    if (prec == PR && mode == MD)                                                               \
-        return launch_persistent(k_score_bound<PR, MD>, SLOT, dr, pr, P, n_out, counters, s);
-        QA_BOUND_CASE(kPrecFP32, kDense, 9)
-        QA_BOUND_CASE(kPrecX3, kDense, 10)
-        QA_BOUND_CASE(kPrecX2, kDense, 11)
-        QA_BOUND_CASE(kPrecFP32, kPruned, 12)
-        QA_BOUND_CASE(kPrecX3, kPruned, 13)
-        QA_BOUND_CASE(kPrecX2, kPruned, 14)
-        QA_BOUND_CASE(kPrecFP32, kClosed, 15)
-        QA_BOUND_CASE(kPrecX3, kClosed, 16)
-        QA_BOUND_CASE(kPrecX2, kClosed, 17)
-#undef QA_BOUND_CASE
+    if (!exhaustive) {
+        if (n_dot < 13 || mode != kDense) return hipErrorInvalidValue;
+        if (prec == kPrecX3)
+            return launch_persistent(k_score_bound<kPrecX3>, 9, dr, pr, P, n_out, counters, s);
+        if (prec == kPrecX2)
+            return launch_persistent(k_score_bound<kPrecX2>, 10, dr, pr, P, n_out, counters, s);
         return hipErrorInvalidValue;
     }
 #define QA_SCORER_CASE(PR, MD, SLOT)                                                            \

@@ -169,8 +169,8 @@ def ground_state(cdd, cgd, V, closed=False, nhat=0, t=1.0, precision="fp64", str
                  stats=False, out=None, exhaustive=False):
     """T = 0 ground state of every pixel (Eq. argmin); int32 tensor (P, N) on the GPU.
     With stats=True returns (n, stats_dict) and waits for the stream.
-    exhaustive=True makes the matrix-core scorer compute every energy of the
-    dense box instead of searching it in bound order (same result)."""
+    exhaustive=True makes the scorer compute every energy of the candidate set
+    instead of searching it in bound order (same result)."""
     lib = load()
     pb, keep = make_problem(cdd, cgd, closed, nhat, 0.0, t, precision,
                             FLAG_EXHAUSTIVE if exhaustive else 0)
