@@ -378,6 +378,25 @@ hipError_t launch_scorer(Scorer sc, const DiagRec *dr, const RowTab *rt, const P
     }
 }
 
+// Cholesky factor L of C_dd (C_dd = L L^T) and R = L^{-1}, so that
+// R^T R = C_dd^{-1}; A = C_dd^{-1}.  The problem has been validated.
+void chol_inverse(int n, const double *C, double *R, double *A);
+
+// Whether the softargmin of N >= 9 dots may run as matrix products: the factor
+// that couples dots 0..5 to dots 6..11, exp(-T'/kT) with |T'| <= 1/4 sum|A_ij|,
+// has to stay within exp(+-300) (qa_soft.hip).  That holds down to kT of about
+// 0.002 for arrays of capacitance 1; below, every candidate is walked.
+bool soft_mm_range(const qa_problem *pb)
+{
+    if (pb->n_dot < 9) return false;
+    const int n = pb->n_dot;
+    double R[QA_MAX_DOT * QA_MAX_DOT], A[QA_MAX_DOT * QA_MAX_DOT], t = 0.0;
+    chol_inverse(n, pb->cdd, R, A);
+    for (int i = 0; i < 6; ++i)
+        for (int j = 6; j < n && j < 12; ++j) t += std::fabs(A[i * n + j]);
+    return 0.25 * t <= 300.0 * pb->kT;
+}
+
 // The device work of one single-diagram call on stream s, with the inputs
 // already in dr: prologue, setup and QP in one kernel, then either the T = 0
 // scoring (n_out) or the softargmin (nbar, saved).  pr holds P pixel records,
@@ -390,10 +409,14 @@ qa_status enqueue_path(DiagRec *dr, RowTab *rt, PixRec *pr, int64_t *counters, i
     const bool closed = pb->mode == QA_CLOSED;
     const Scorer sc = scorer_of(pb, P);
     if (ev) QA_HIP(hipEventRecord((*ev)[0], s));
-    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed,
-                        nbar ? kBoundNone : scorer_split(sc), rt, s, nullptr, nullptr, sweep));
+    const bool mm = nbar && soft_mm_range(pb);
+    const BoundSplit split = nbar ? kBoundNone : scorer_split(sc);
+    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed, split,
+                        mm || split == kBoundLow6 ? rt : nullptr, s, nullptr, nullptr, sweep));
     if (ev) QA_HIP(hipEventRecord((*ev)[1], s));
-    if (nbar)
+    if (mm)
+        QA_HIP(launch_soft_mm(dr, rt, pr, P, nbar, saved, pb->n_dot, closed, s));
+    else if (nbar)
         QA_HIP(launch_soft_fwd(dr, pr, P, nbar, saved, counters, pb->n_dot, s));
     else
         QA_HIP(launch_scorer(sc, dr, rt, pr, counters, pb, P, n_out, s));
@@ -426,7 +449,7 @@ qa_status run_single(Workspace *w, const qa_problem *pb, const double *V, int64_
     std::array<hipEvent_t, 4> *ev = timing_slot(w);
     if (ev || !g_graphs || sweep)
         return enqueue_single(w, w->stream, pb, V, P, n_out, nbar, saved, ev, sweep);
-    const int path = nbar ? 2 : 10 + 16 * (int)scorer_of(pb, P) + 3 * pb->precision + scorer_mode(pb);
+    const int path = nbar ? 2 + soft_mm_range(pb) : 10 + 16 * (int)scorer_of(pb, P) + 3 * pb->precision + scorer_mode(pb);
     std::vector<int64_t> key = {pb->n_dot, pb->mode, path, pb->flags, P, (int64_t)(uintptr_t)V,
                                 (int64_t)(uintptr_t)n_out, (int64_t)(uintptr_t)nbar,
                                 (int64_t)(uintptr_t)saved, (int64_t)(uintptr_t)w->dr,
@@ -1123,7 +1146,8 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
     const Scorer sc = scorer_of(prob, P);
     auto setup = [&]() {
         return launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
-                            prob->mode == QA_CLOSED, scorer_split(sc), w->rt, s) == hipSuccess;
+                            prob->mode == QA_CLOSED, scorer_split(sc),
+                            scorer_split(sc) == kBoundLow6 ? w->rt : nullptr, s) == hipSuccess;
     };
     // reps setup launches, then reps (setup, scorer) pairs: the scorer of a
     // pair reads what its setup has just written, as in a call
@@ -1322,8 +1346,6 @@ void pinv(int m, int n, const double *M, double *X)
     }
 }
 
-// Cholesky factor L of C_dd (C_dd = L L^T) and R = L^{-1}, so that
-// R^T R = C_dd^{-1}; A = C_dd^{-1}.  The problem has been validated.
 void chol_inverse(int n, const double *C, double *R, double *A)
 {
     double L[QA_MAX_DOT * QA_MAX_DOT] = {0};

@@ -233,8 +233,8 @@ struct alignas(64) PixRec {  // 256 bytes, two 128-byte lines
 };
 
 struct alignas(8) SavedRec {
-    double emin;          // smallest candidate energy
-    double Z;             // sum exp(-(E - emin)/kT) (>= 1)
+    double emin;          // reference energy (N <= 8: the smallest candidate energy)
+    double Z;             // sum exp(-(E - emin)/kT)
     double nb[kMaxDot];   // <n> - n0 = sum_s pi_s 1_s (zero beyond n)
     int16_t n0[kMaxDot];
     uint32_t free;
@@ -343,7 +343,8 @@ hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s
 // clears the kCounterWords counters) and setup of every pixel; the per-block
 // counts {pixels, QP, doubled, QP failures} go to bstats[4 * block] for
 // setup_blocks(P, n_dot) blocks; split: the bound terms the scorer of this call
-// reads (kBoundNone for N <= 8); rt: the row kernels' tables (kBoundLow6); x_out (P x N) / flags_out (P) are optional
+// reads (kBoundNone for N <= 8); rt: receives the row tables (N >= 9, needed for
+// kBoundLow6) or NULL; x_out (P x N) / flags_out (P) are optional
 // copies of x*; grid, when given and on, replaces the voltages V.  P >= 1.
 int64_t setup_blocks(int64_t P, int n_dot);
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
@@ -368,6 +369,11 @@ hipError_t launch_score_tab(const DiagRec *dr, const PixRec *pr, int64_t P, int3
 hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int prec, int mode,
                              bool exhaustive, int32_t *n_out, int64_t *counters, int n_dot,
                              hipStream_t s);
+// softargmin of N >= 9 dots as FP64 matrix products (qa_soft.hip), for couplings
+// and temperatures that soft_mm_range (qa_api.hip) admits
+hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr, int64_t P,
+                          double *nbar, SavedRec *saved, int n_dot, bool closed, hipStream_t s);
+// softargmin: the table form (N <= 8), or a walk over every candidate
 hipError_t launch_soft_fwd(const DiagRec *dr, const PixRec *pr, int64_t P, double *nbar,
                            SavedRec *saved, int64_t *counters, int n_dot, hipStream_t s);
 // adjoint partial sums: kBwdReplicas copies of (dL/dA, kMaxDot^2; dL/dC_gd,

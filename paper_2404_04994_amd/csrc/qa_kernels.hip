@@ -341,7 +341,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         prep_inverse_wave(m4, n, sA, red, sS, NM == 16 ? sS6 : nullptr);
         // a grid of at least 256 blocks: wave 0 of block b fills energy-table
         // entry b while the pixel waves finish (off the kernel's tail)
-        if (split != kBoundLow6 && gridDim.x >= 256) {
+        if (!(NM == 16 && rt) && gridDim.x >= 256) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -484,8 +484,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
 
     // the row kernels' tables, by the waves that have no pixels: one unit per
     // block while the pixel waves form their records (small grids: below)
-    if (NM == 16 && split == kBoundLow6 && !pixel_wave && gridDim.x >= kRowUnits &&
-        blockIdx.x < kRowUnits)
+    if (NM == 16 && rt && !pixel_wave && gridDim.x >= kRowUnits && blockIdx.x < kRowUnits)
         prep_row_unit(rt, sA, sS6, n, (int)blockIdx.x);
     if (pixel_wave) {
         // g0 = A (n0 - x_u) and U(n0) = 1/2 (n0 - x_u)^T g0 (Eq. free_energy)
@@ -620,9 +619,9 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         if (counters)
             for (int i = threadIdx.x; i < kCounterWords; i += blockDim.x) counters[i] = 0;
     }
-    if (split == kBoundLow6) {
+    if (NM == 16 && rt) {
         constexpr int kWaves = kSetupThreads / kWave;
-        if (NM == 16 && gridDim.x < kRowUnits)
+        if (gridDim.x < kRowUnits)
             for (int u = blockIdx.x * kWaves + tid / kWave; u < kRowUnits; u += gridDim.x * kWaves)
                 prep_row_unit(rt, sA, sS6, n, u);
     } else if (gridDim.x < 256) {

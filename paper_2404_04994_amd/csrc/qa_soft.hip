@@ -1,0 +1,507 @@
+// qa_soft.hip -- softargmin (Sec. 4.2, Eq. softargmin) of 9 <= N <= 16 dots as FP64
+// matrix products.
+//
+// With the dots split into a low part (dots 0..5, 64 states l), a middle part
+// (dots 6..11, 64 states c) and a high part (dots 12..N-1, states k), a
+// candidate's energy relative to U(n0) is
+//     E(l, c, k) = a_k(l) + c_k(c) + T(c, l),   T = b_l^T A b_c,
+// so its weight is a product of three factors, exp(-E/kT) = F1_k(l) F2_k(c) W(c, l),
+// and W depends on the diagram alone.  All sums over the 4096 states of one
+// (pixel, k) are then
+//     sum_l [..] F1(l) Y(l),   Y(l) = sum_c W(c, l) F2(c),
+//     sum_c [..] F2(c) X(c),   X(c) = sum_l W(c, l) F1(l),
+// two products of the same 64 x 64 matrix with a column per (pixel, k): 16
+// columns at a time, v_mfma_f64_16x16x4_f64, W in registers for the whole kernel
+// (each of a block's four waves keeps 16 rows of W and of W^T).  That is 4
+// flops per candidate and 128 exponentials per 4096 candidates; walking the
+// candidates took an exponential and some forty FP64 operations each.
+//
+// Range: T is taken around the middle of the box, T' = (b_l - 1/2)^T A (b_c - 1/2)
+// (the linear rest goes to a and c), and a and c from their smallest values, so
+// that F1, F2 <= 1 and |log W| <= max|T'| / kT.  A candidate within exp(-52) of
+// the largest weight then has every factor above exp(-2 max|T'| / kT - 52): for
+// max|T'| <= 300 kT nothing that counts is lost (the host checks it; smaller kT
+// walks the candidates).
+//
+// Closed arrays: a low state of popcount m pairs with the middle states of
+// popcount K - m only (K = k - popc of the high state).  The middle states are
+// ordered by popcount, a matrix step never crosses a class (19 steps of four
+// instead of 16), each class keeps its own accumulator, and the sums pick the
+// one class of each low state; the other product alike.  F1 and F2 are then
+// taken from the smallest values of their class, and a pair of classes has its
+// own factor, so the same range holds within each.
+//
+// Bound: for 16 dots the vector instructions around the products (some 600 per
+// wave and set of columns beside 32 products of 64 cycles) at two waves per SIMD,
+// which is what the registers allow; launch and prologue latency for few
+// pixels.  Measured against the walk over the candidates (one wave per pixel):
+// 16 dots, 10^4 pixels 10900 -> 105 us; 12 dots, 4096 pixels 400 -> 9.9 us; error
+// against 64 bits 3.3e-15 -> 1.8e-15 (16 dots, kT = 0.01).
+#include "qa_device.h"
+
+namespace qa {
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kSoftThreads = 256;
+constexpr int kSoftRows = 16;  // (pixel, k) columns per batch
+
+// states ordered by popcount, each class padded to a multiple of four slots
+constexpr int kClassStep[8] = {0, 1, 3, 7, 12, 16, 18, 19};  // first step of class m
+struct ClassOrder {
+    uint8_t slot[64];   // slot of a state
+    uint8_t state[76];  // state of a slot (64: padding)
+};
+constexpr ClassOrder class_order()
+{
+    ClassOrder o{};
+    int fill[7] = {};
+    for (int s = 0; s < 76; ++s) o.state[s] = 64;
+    for (int s = 0; s < 64; ++s) {
+        const int m = __builtin_popcount(s);
+        o.slot[s] = (uint8_t)(4 * kClassStep[m] + fill[m]++);
+        o.state[o.slot[s]] = (uint8_t)s;
+    }
+    return o;
+}
+static __constant__ const ClassOrder kOrder = class_order();
+
+// exp(x) for -1100 <= x <= 700 (zero at the lower end): x = n ln 2 + r, |r| <= ln 2 / 2, and a
+// polynomial of degree 11 for exp(r), the interpolant of (exp(r) - 1 - r) / r^2 at
+// Chebyshev nodes (relative error 2e-17 before rounding).
+__device__ __forceinline__ double exp_small(double x)
+{
+    const double n = rint(x * 0x1.71547652b82fep+0);
+    double r = fma(n, -0x1.62e42fefa39efp-1, x);
+    r = fma(n, -0x1.abc9e3b39803fp-56, r);
+    double p = 0x1.af390e40bdeadp-26;
+    p = fma(p, r, 0x1.2891a8fe8d7d2p-22);
+    p = fma(p, r, 0x1.71de0d81d74e1p-19);
+    p = fma(p, r, 0x1.a019b8ef350abp-16);
+    p = fma(p, r, 0x1.a01a01a7d093cp-13);
+    p = fma(p, r, 0x1.6c16c17893938p-10);
+    p = fma(p, r, 0x1.11111111109a0p-7);
+    p = fma(p, r, 0x1.5555555553d4fp-5);
+    p = fma(p, r, 0x1.5555555555556p-3);
+    p = fma(p, r, 0x1.0000000000001p-1);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)n);
+}
+
+// exp(x) for x <= 0, zero below -1100
+__device__ __forceinline__ double exp_neg(double x) { return exp_small(fmax(x, -1100.0)); }
+
+// value of the lane in the neighbouring 16-lane row (rows 0-1, 2-3) or half
+__device__ __forceinline__ double other_row(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const int odd = threadIdx.x >> 4 & 1;
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)(odd ? lo[0] : lo[1]) |
+                                            ((uint64_t)(odd ? hi[0] : hi[1]) << 32)));
+}
+__device__ __forceinline__ double other_half(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const int odd = threadIdx.x >> 5 & 1;
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)(odd ? lo[0] : lo[1]) |
+                                            ((uint64_t)(odd ? hi[0] : hi[1]) << 32)));
+}
+// minimum over a 16-lane row
+__device__ __forceinline__ double row_min_d(double x)
+{
+    x = fmin(x, dppd<kDppXor1>(x));
+    x = fmin(x, dppd<kDppXor2>(x));
+    x = fmin(x, dppd<kDppHalfMirror>(x));
+    return fmin(x, dppd<kDppMirror>(x));
+}
+
+constexpr double kNoState = 0x1p1000;  // energy of a state outside the candidate set
+
+// The matrix operand of one wave: rows 16 w .. 16 w + 15 of W^T (low states, over
+// the middle states) and of W, lane (m, q) holding row m, column of slot 4 t + q.
+template <int STEPS>
+struct SoftW {
+    double y[STEPS], x[STEPS];
+};
+// T: the diagram's table in LDS, columns of kTStride doubles
+constexpr int kTStride = 65;
+template <bool CLOSED, int STEPS>
+__device__ __forceinline__ void soft_w(const double *T, double ikT, int w, SoftW<STEPS> &o)
+{
+    const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+    const int row = 16 * w + m;
+    const double tl = T[63 * kTStride + row], tc = T[row * kTStride + 63];
+    const double tt = 0.25 * T[63 * kTStride + 63];
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        const int s = CLOSED ? (int)kOrder.state[4 * t + q] : 4 * t + q;
+        const int sc = s & 63;
+        // T' of (middle s, low row) and of (middle row, low s), of either sign (below
+        // 300 kT by the host's check); padding slots are zero
+        const double ey = (T[sc * kTStride + row] - 0.5 * (tl + T[sc * kTStride + 63])) + tt;
+        const double ex = (T[row * kTStride + sc] - 0.5 * (tc + T[63 * kTStride + sc])) + tt;
+        const double wy = exp_small(-ey * ikT), wx = exp_small(-ex * ikT);
+        o.y[t] = s < 64 ? wy : 0.0;
+        o.x[t] = s < 64 ? wx : 0.0;
+        // finished here: the compiler sinks the last steps of every exponential
+        // past the barrier otherwise, and keeps twice the registers until then
+        asm volatile("" : "+v"(o.y[t]), "+v"(o.x[t])::"memory");
+    }
+}
+
+// acc[m] += rows of W times the columns F (LDS, stride doubles per column)
+template <bool CLOSED, int STEPS, int CLASSES>
+__device__ __forceinline__ void soft_product(const double (&w)[STEPS], const double *F, int stride,
+                                             f64x4_t (&acc)[CLASSES])
+{
+    const int lane = threadIdx.x & 63;
+    const double *col = F + (lane & 15) * stride + (lane >> 4);
+    static_for_dev<0, STEPS>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        constexpr int m = CLOSED ? (t < 1 ? 0 : t < 3 ? 1 : t < 7 ? 2 : t < 12 ? 3 : t < 16 ? 4 : t < 18 ? 5 : 6) : 0;
+        acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[t], col[4 * t], acc[m], 0, 0, 0);
+    });
+}
+
+// The five sums of a product's tile over its 16 rows s = 16 w + q + 4 i (element i
+// of the lane): all of them and those with bit 0..3 of s set, of F(s) times the
+// product; every lane of a column ends with them.
+// (closed: times the factor of the pair of classes, cls[popcount of the low state])
+template <bool CLOSED, bool LOW, int CLASSES>
+__device__ __forceinline__ void soft_sums5(const f64x4_t (&acc)[CLASSES], const double *F, int stride,
+                                           const double *cls, int w, int K, double (&out)[5])
+{
+    const int lane = threadIdx.x & 63, col = lane & 15, q = lane >> 4;
+    double v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int s = 16 * w + q + 4 * i;
+        double y = acc[0][i];
+        if (CLOSED) {
+            const int own = __popc((uint32_t)s), want = K - own;  // the partner's popcount
+            y = want == 0 ? y : 0.0;
+#pragma unroll
+            for (int m = 1; m < CLASSES; ++m) y = want == m ? acc[m][i] : y;
+            y *= cls[8 * col + ((LOW ? own : want) & 7)];
+        }
+        v[i] = F[col * stride + (CLOSED ? (int)kOrder.slot[s] : s)] * y;
+    }
+    double t = (v[0] + v[1]) + (v[2] + v[3]);
+    double b2 = v[1] + v[3], b3 = v[2] + v[3];
+    const double to = other_row(t);
+    double b0 = (q & 1) ? t : to;
+    t += to;
+    b2 += other_row(b2);
+    b3 += other_row(b3);
+    const double th = other_half(t);
+    const double b1 = (q & 2) ? t : th;
+    out[0] = t + th;
+    out[1] = b0 + other_half(b0);
+    out[2] = b1;
+    out[3] = b2 + other_half(b2);
+    out[4] = b3 + other_half(b3);
+}
+
+template <bool CLOSED>
+struct SoftLds {
+    static constexpr int kSteps = CLOSED ? 19 : 16;
+    static constexpr int kStride = 4 * kSteps + 2;  // columns two doubles apart in the banks
+    double F1[kSoftRows][kStride], F2[kSoftRows][kStride];
+    double part[4][2][5][kSoftRows];  // [wave][product][sum][column]
+    // closed: smallest energies of each class (low, middle) as ordered integers,
+    // and the factors of the pairs of classes
+    unsigned long long cmin[CLOSED ? 2 : 1][kSoftRows][8];
+    double cls[kSoftRows][8];
+    double ref[kSoftRows];            // smallest a + c of the column
+    PixRec rec[2][kSoftRows];
+};
+
+// The factors of a batch's columns: thread (column = tid / 16, s = tid mod 16 + 16 i)
+// forms F1 and F2 of four states each and the column's reference.
+struct SoftConst {
+    double a[4], c[4];  // quadratic terms of the thread's states for the column's k
+    double kbit[4];     // bits of k
+    double bit[4];      // bits 0..3 of the thread's states
+};
+template <int NK>
+__device__ __forceinline__ void soft_const(const RowTab *__restrict__ rt, const double *T,
+                                           SoftConst &o)
+{
+    const int s0 = threadIdx.x & 15, k = (threadIdx.x >> 4) & ((1 << NK) - 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        o.kbit[j] = (k >> j & 1) ? 1.0 : 0.0;
+        o.bit[j] = (s0 >> j & 1) ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int s = s0 + 16 * i;
+        double a = rt->hlo[s] + 0.5 * T[63 * kTStride + s];
+        double c = (rt->hhi[s] + 0.5 * T[s * kTStride + 63]) - 0.25 * T[63 * kTStride + 63] + rt->hk[k];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a = fma(o.kbit[j], rt->lo[j][s], a);
+            c = fma(o.kbit[j], rt->hi[j][s], c);
+        }
+        o.a[i] = a;
+        o.c[i] = c;
+    }
+}
+
+// doubles as integers of the same order (no NaN)
+__device__ __forceinline__ unsigned long long ordered(double x)
+{
+    const long long u = __double_as_longlong(x);
+    return (unsigned long long)u ^ ((unsigned long long)(u >> 63) | (1ull << 63));
+}
+__device__ __forceinline__ double from_ordered(unsigned long long o)
+{
+    return __longlong_as_double((long long)(o ^ (~((long long)o >> 63) | (1ll << 63))));
+}
+
+// (contains block barriers when CLOSED)
+template <bool CLOSED, int NK>
+__device__ __forceinline__ void soft_factors(const PixRec *r, const SoftConst &o, double ikT,
+                                             SoftLds<CLOSED> &L)
+{
+    const int s0 = threadIdx.x & 15, colm = threadIdx.x >> 4;
+    const int kk = colm & ((1 << NK) - 1);
+    double gl = 0.0, gm = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        gl = fma(o.bit[j], r->g0[j], gl);
+        gm = fma(o.bit[j], r->g0[6 + j], gm);
+    }
+#pragma unroll
+    for (int j = 0; j < NK; ++j) gm = fma(o.kbit[j], r->g0[12 + j], gm);
+    const uint32_t fm = r->free;
+    const bool khi = ((uint32_t)kk & ~(fm >> 12)) == 0;  // raises no fixed dot of 12..15
+    double e1[4], e2[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t s = (uint32_t)(s0 + 16 * i);
+        const double g45 = (i & 1 ? r->g0[4] : 0.0) + (i & 2 ? r->g0[5] : 0.0);
+        const double h45 = (i & 1 ? r->g0[10] : 0.0) + (i & 2 ? r->g0[11] : 0.0);
+        e1[i] = (s & ~fm & 63u) ? kNoState : (o.a[i] + gl) + g45;
+        e2[i] = (s & ~(fm >> 6) & 63u) || !khi ? kNoState : (o.c[i] + gm) + h45;
+    }
+    if (!CLOSED) {
+        const double r1 = row_min_d(fmin(fmin(e1[0], e1[1]), fmin(e1[2], e1[3])));
+        const double r2 = row_min_d(fmin(fmin(e2[0], e2[1]), fmin(e2[2], e2[3])));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            L.F1[colm][s0 + 16 * i] = exp_neg((r1 - e1[i]) * ikT);
+            L.F2[colm][s0 + 16 * i] = r2 < kNoState ? exp_neg((r2 - e2[i]) * ikT) : 0.0;
+            if (i & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        if (s0 == 0) L.ref[colm] = r1 + r2;
+        return;
+    }
+    // states s0 + 16 i have popcounts pl, pl + 1, pl + 1, pl + 2
+    const int pl = __popc((uint32_t)s0);
+    atomicMin(&L.cmin[0][colm][pl], ordered(e1[0]));
+    atomicMin(&L.cmin[0][colm][pl + 1], ordered(fmin(e1[1], e1[2])));
+    atomicMin(&L.cmin[0][colm][pl + 2], ordered(e1[3]));
+    atomicMin(&L.cmin[CLOSED][colm][pl], ordered(e2[0]));
+    atomicMin(&L.cmin[CLOSED][colm][pl + 1], ordered(fmin(e2[1], e2[2])));
+    atomicMin(&L.cmin[CLOSED][colm][pl + 2], ordered(e2[3]));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int at = kOrder.slot[s0 + 16 * i], m = pl + (i == 0 ? 0 : (i == 3 ? 2 : 1));
+        const double r1 = from_ordered(L.cmin[0][colm][m]), r2 = from_ordered(L.cmin[CLOSED][colm][m]);
+        L.F1[colm][at] = e1[i] < kNoState ? exp_neg((r1 - e1[i]) * ikT) : 0.0;
+        L.F2[colm][at] = e2[i] < kNoState ? exp_neg((r2 - e2[i]) * ikT) : 0.0;
+        if (i & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    {
+        // low class m = s0 pairs with middle class K - m
+        const int K = r->k - __popc((uint32_t)kk), a = K - s0;
+        double rr = kNoState;
+        if (s0 < 7 && a >= 0 && a < 7) {
+            const double r1 = from_ordered(L.cmin[0][colm][s0]), r2 = from_ordered(L.cmin[CLOSED][colm][a]);
+            rr = r1 < kNoState && r2 < kNoState ? r1 + r2 : kNoState;
+        }
+        const double ref = row_min_d(rr);
+        if (s0 < 8) L.cls[colm][s0] = rr < kNoState ? exp_neg((ref - rr) * ikT) : 0.0;
+        if (s0 == 0) L.ref[colm] = ref;
+    }
+}
+
+// Block b takes batches b, b + gridDim.x, ...: 16 >> NK pixels of 2^NK high
+// states, NK = max(0, N - 12).
+template <bool CLOSED, int NK>
+__global__ __launch_bounds__(kSoftThreads, 2) void k_soft_mm(const DiagRec *__restrict__ dr,
+                                                             const RowTab *__restrict__ rt,
+                                                             const PixRec *__restrict__ pr, int64_t P,
+                                                             double *__restrict__ nbar,
+                                                             SavedRec *__restrict__ saved, int n)
+{
+    constexpr int STEPS = SoftLds<CLOSED>::kSteps, STRIDE = SoftLds<CLOSED>::kStride;
+    constexpr int CLASSES = CLOSED ? 7 : 1;
+    // the table T during the prologue, then the batch's buffers
+    __shared__ union Shared {
+        double T[64 * kTStride];
+        SoftLds<CLOSED> L;
+        __device__ Shared() {}
+    } sh;
+    SoftLds<CLOSED> &L = sh.L;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int per = kSoftRows >> NK;  // pixels per batch
+    const int64_t batches = (P + per - 1) / per;
+    const double ikT = 1.0 / dr->kT;
+    for (int r = 0; r < 16; ++r) {
+        const int e = r * kSoftThreads + tid;
+        sh.T[(e >> 6) * kTStride + (e & 63)] = (&rt->T[0][0])[e];
+    }
+    // record dwords 4 (tid mod 16) .. + 3 of the batch's pixel tid / 16
+    auto fetch = [&](int64_t b) -> uint4 {
+        int64_t p = b * per + (tid >> 4);
+        p = p < P ? p : P - 1;
+        return (tid >> 4) < per ? reinterpret_cast<const uint4 *>(pr + p)[tid & 15] : uint4{};
+    };
+    uint4 next = fetch(blockIdx.x);
+    __syncthreads();
+    SoftW<STEPS> W;
+    soft_w<CLOSED, STEPS>(sh.T, ikT, w, W);
+    SoftConst sc;
+    soft_const<NK>(rt, sh.T, sc);
+    __syncthreads();
+    for (int i = tid; i < kSoftRows * STRIDE; i += kSoftThreads) {
+        (&L.F1[0][0])[i] = 0.0;  // the padding slots stay zero
+        (&L.F2[0][0])[i] = 0.0;
+    }
+    int buf = 0;
+    for (int64_t b = blockIdx.x; b < batches; b += gridDim.x, buf ^= 1) {
+        if ((tid >> 4) < per) reinterpret_cast<uint4 *>(&L.rec[buf][tid >> 4])[tid & 15] = next;
+        if (CLOSED) (&L.cmin[0][0][0])[tid] = ordered(kNoState);
+        if (b + gridDim.x < batches) next = fetch(b + gridDim.x);
+        __syncthreads();
+        soft_factors<CLOSED, NK>(&L.rec[buf][(tid >> 4) >> NK], sc, ikT, L);
+        __syncthreads();
+        {
+            const int col = tid & 15;
+            const int K = CLOSED ? L.rec[buf][col >> NK].k - __popc((uint32_t)(col & ((1 << NK) - 1))) : 0;
+            double sy[5], sx[5];
+            {
+                f64x4_t y[CLASSES] = {};
+                soft_product<CLOSED, STEPS, CLASSES>(W.y, &L.F2[0][0], STRIDE, y);
+                soft_sums5<CLOSED, true, CLASSES>(y, &L.F1[0][0], STRIDE, &L.cls[0][0], w, K, sy);
+            }
+            {
+                f64x4_t x[CLASSES] = {};
+                soft_product<CLOSED, STEPS, CLASSES>(W.x, &L.F1[0][0], STRIDE, x);
+                soft_sums5<CLOSED, false, CLASSES>(x, &L.F2[0][0], STRIDE, &L.cls[0][0], w, K, sx);
+            }
+            if ((tid & 63) < 16) {
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    L.part[w][0][j][col] = sy[j];
+                    L.part[w][1][j][col] = sx[j];
+                }
+            }
+        }
+        __syncthreads();
+        // thread (column, item): item 0 the normaliser, 1..6 dots 0..5, 7..12 dots
+        // 6..11, 13..16 dots 12..15; the columns of a pixel are added up by the
+        // lanes of its 2^nk columns
+        const int col = tid & 15;
+        const double ref = L.ref[col];
+        auto over_k = [&](double v, auto &&op) {
+            if constexpr (NK >= 1) v = op(v, dppd<kDppXor1>(v));
+            if constexpr (NK >= 2) v = op(v, dppd<kDppXor2>(v));
+            if constexpr (NK >= 3) v = op(v, dppd<kDppHalfMirror>(v));
+            if constexpr (NK >= 4) v = op(v, dppd<kDppMirror>(v));
+            return v;
+        };
+        const double low = over_k(ref, [](double u, double v) { return fmin(u, v); });
+        const double scale = exp_neg((low - ref) * ikT);
+        auto tile4 = [&](int prod, int j) {
+            return (L.part[0][prod][j][col] + L.part[1][prod][j][col]) +
+                   (L.part[2][prod][j][col] + L.part[3][prod][j][col]);
+        };
+        const double zc = scale * tile4(0, 0);
+        const double Z = over_k(zc, [](double u, double v) { return u + v; });
+        const int64_t p = b * per + (col >> NK);
+        const bool writer = (col & ((1 << NK) - 1)) == 0 && p < P;
+        const PixRec *r = &L.rec[buf][col >> NK];
+        for (int item = tid >> 4; item < 17; item += 16) {
+            double v = 0.0;
+            if (item >= 13) {
+                v = (col >> (item - 13) & 1) && item - 13 < NK ? zc : 0.0;
+            } else if (item >= 1) {
+                const int prod = item >= 7 ? 1 : 0, j = (item - 1) % 6;
+                v = j < 4 ? tile4(prod, 1 + j)
+                          : (j == 4 ? L.part[1][prod][0][col] + L.part[3][prod][0][col]
+                                    : L.part[2][prod][0][col] + L.part[3][prod][0][col]);
+                v *= scale;
+            }
+            v = over_k(v, [](double u, double t) { return u + t; });
+            if (!writer) continue;
+            if (item == 0) {
+                if (saved) {
+                    SavedRec *o = saved + p;
+                    o->emin = r->u0 + low;
+                    o->Z = Z;
+                    o->free = r->free;
+                    o->k = r->k;
+                }
+                continue;
+            }
+            const int d = item - 1;
+            const double f = d < n ? v / Z : 0.0;
+            if (d < n) nbar[p * n + d] = (double)r->n0[d] + f;
+            if (saved) {
+                saved[p].nb[d] = f;
+                saved[p].n0[d] = r->n0[d];
+            }
+        }
+    }
+}
+
+hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr, int64_t P,
+                          double *nbar, SavedRec *saved, int n_dot, bool closed, hipStream_t s)
+{
+    if (n_dot < 9 || n_dot > kMaxDot || !rt) return hipErrorInvalidValue;
+    if (P <= 0) return hipSuccess;
+    const int nk = n_dot > 12 ? n_dot - 12 : 0;
+    const int64_t batches = (P + (kSoftRows >> nk) - 1) / (kSoftRows >> nk);
+    // as many blocks as the chip keeps resident (cached per kernel and device)
+    static int cache[10][64];
+    auto go = [&](auto kernel, int slot) {
+        int dev = 0;
+        int64_t most = 512;
+        if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
+            int &c = cache[slot][dev];
+            int cus = 0, per_cu = 0;
+            if (!c &&
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kSoftThreads, 0) == hipSuccess)
+                c = cus * per_cu;
+            if (c > 0) most = c;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(batches < most ? batches : most)),
+                           dim3(kSoftThreads), 0, s, dr, rt, pr, P, nbar, saved, n_dot);
+        return hipGetLastError();
+    };
+    switch (2 * nk + (closed ? 1 : 0)) {
+    case 0: return go(k_soft_mm<false, 0>, 0);
+    case 1: return go(k_soft_mm<true, 0>, 1);
+    case 2: return go(k_soft_mm<false, 1>, 2);
+    case 3: return go(k_soft_mm<true, 1>, 3);
+    case 4: return go(k_soft_mm<false, 2>, 4);
+    case 5: return go(k_soft_mm<true, 2>, 5);
+    case 6: return go(k_soft_mm<false, 3>, 6);
+    case 7: return go(k_soft_mm<true, 3>, 7);
+    case 8: return go(k_soft_mm<false, 4>, 8);
+    default: return go(k_soft_mm<true, 4>, 9);
+    }
+}
+
+}  // namespace qa
