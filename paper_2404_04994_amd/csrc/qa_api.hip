@@ -94,6 +94,7 @@ struct Workspace {
     // inputs in dr_inputs: a setup or prologue launch has been enqueued since
     // they were uploaded
     bool dr_derived = false;
+    bool rt_derived = false;  // and w->rt the row tables
     // the adjoint's accumulators are zero (the final adjoint kernel leaves
     // them so; fresh allocations are cleared once)
     bool acc_zero = false;
@@ -303,7 +304,7 @@ qa_status upload_diag(Workspace *w, const qa_problem *pb)
     QA_HIP(hipMemcpyAsync(w->dr, &w->stage[slot], kDiagInputBytes, hipMemcpyHostToDevice,
                           w->stream));
     QA_HIP(hipEventRecord(w->stage_ev[slot], w->stream));
-    w->dr_derived = false;
+    w->dr_derived = w->rt_derived = false;
     const unsigned char *b = reinterpret_cast<const unsigned char *>(&w->stage[slot]);
     w->dr_inputs.assign(b, b + kDiagInputBytes);
     return QA_OK;
@@ -397,6 +398,12 @@ bool soft_mm_range(const qa_problem *pb)
     return 0.25 * t <= 300.0 * pb->kT;
 }
 
+// whether the setup of such a call writes the row tables
+bool writes_row_tables(const qa_problem *pb, bool soft, int64_t P)
+{
+    return soft ? soft_mm_range(pb) : scorer_split(scorer_of(pb, P)) == kBoundLow6;
+}
+
 // The device work of one single-diagram call on stream s, with the inputs
 // already in dr: prologue, setup and QP in one kernel, then either the T = 0
 // scoring (n_out) or the softargmin (nbar, saved).  pr holds P pixel records,
@@ -432,7 +439,10 @@ qa_status enqueue_single(Workspace *w, hipStream_t s, const qa_problem *pb, cons
 {
     qa_status st = enqueue_path(w->dr, w->rt, w->pr, w->counters, w->bstats, s, pb, V, P, n_out, nbar,
                                 saved, ev, sweep);
-    if (!st) w->dr_derived = true;
+    if (!st) {
+        w->dr_derived = true;
+        if (writes_row_tables(pb, nbar != nullptr, P)) w->rt_derived = true;
+    }
     return st;
 }
 
@@ -530,6 +540,9 @@ qa_status backward(const qa_problem *prob, const double *V_dev, const VGrid *vg,
     DiagRec *dr0 = w->dr;
     if ((st = grow(w, w->dr, w->dr_cap, 1))) return st;
     if (w->dr != dr0) w->dr_inputs.clear();
+    RowTab *rt0 = w->rt;
+    if ((st = grow(w, w->rt, w->rt_cap, 1))) return st;
+    if (w->rt != rt0) w->rt_derived = false;
     const int64_t nacc = (int64_t)kBwdReplicas * kBwdAccWords;
     double *acc0 = w->acc;
     if ((st = grow(w, w->acc, w->acc_cap, nacc))) return st;
@@ -546,8 +559,18 @@ qa_status backward(const qa_problem *prob, const double *V_dev, const VGrid *vg,
         QA_HIP(launch_zero_i64(reinterpret_cast<int64_t *>(w->acc), (int)nzero, w->stream));
     }
     w->acc_zero = false;  // until the final kernel below is enqueued
-    QA_HIP(launch_soft_bwd(w->dr, V_dev, P, grad_nbar_dev, (const SavedRec *)saved_dev, w->acc,
-                           grad_V_dev, prob->n_dot, w->stream, vg));
+    if (soft_mm_range(prob)) {
+        if (!w->rt_derived) {
+            QA_HIP(launch_row_tab(w->dr, w->rt, w->stream));
+            w->rt_derived = true;
+        }
+        QA_HIP(launch_soft_mm_bwd(w->dr, w->rt, V_dev, P, grad_nbar_dev,
+                                  (const SavedRec *)saved_dev, w->acc, grad_V_dev, prob->n_dot,
+                                  prob->mode == QA_CLOSED, w->stream, vg));
+    } else {
+        QA_HIP(launch_soft_bwd(w->dr, V_dev, P, grad_nbar_dev, (const SavedRec *)saved_dev, w->acc,
+                               grad_V_dev, prob->n_dot, w->stream, vg));
+    }
     QA_HIP(launch_soft_bwd_final(w->dr, w->acc, grad_cdd_dev, grad_cgd_dev, w->stream));
     w->acc_zero = true;
     return QA_OK;

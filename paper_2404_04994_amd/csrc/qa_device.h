@@ -689,6 +689,7 @@ __device__ __forceinline__ void prep_row_unit(RowTab *rt, const double *A, const
         rt->hlo[lane] = lo;
         rt->hhi[lane] = hi;
         if (lane < 16) rt->hk[lane] = hk;
+        if (!S) return;  // (the bound's terms are not wanted)
         // w = C_HH^{-1} C_HL 1 (lane j < 10), sum|S| / 2, gamma = 1^T A_LL^{-1} 1
         const int nh = n - 6;
         double w = 0.0, sa = 0.0, gam = 0.0;

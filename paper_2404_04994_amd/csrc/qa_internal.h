@@ -373,6 +373,13 @@ hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int
 // and temperatures that soft_mm_range (qa_api.hip) admits
 hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr, int64_t P,
                           double *nbar, SavedRec *saved, int n_dot, bool closed, hipStream_t s);
+// its adjoint (9 <= N <= 12), into the same accumulators as launch_soft_bwd
+hipError_t launch_soft_mm_bwd(const DiagRec *dr, const RowTab *rt, const double *V, int64_t P,
+                              const double *gbar, const SavedRec *saved, double *acc,
+                              double *gradV, int n_dot, bool closed, hipStream_t s,
+                              const VGrid *grid = nullptr);
+// the row tables (without the bound's) of a record whose prologue has run
+hipError_t launch_row_tab(const DiagRec *dr, RowTab *rt, hipStream_t s);
 // softargmin: the table form (N <= 8), or a walk over every candidate
 hipError_t launch_soft_fwd(const DiagRec *dr, const PixRec *pr, int64_t P, double *nbar,
                            SavedRec *saved, int64_t *counters, int n_dot, hipStream_t s);

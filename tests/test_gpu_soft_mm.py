@@ -87,3 +87,68 @@ def test_soft_many_pixels_and_far_voltages(qa, oracle):
     bad = qa.soft_charge(cdd, cgd, Vd, 0.02)[0].cpu().numpy()
     assert np.isnan(bad[5]).all()
     assert np.array_equal(np.delete(bad, 5, 0), np.delete(nb, 5, 0))
+
+
+def check_grads(got, want):
+    for a, b in zip(got, want):
+        a = a.cpu().numpy()
+        assert np.linalg.norm(a - b) <= 1e-9 * max(np.linalg.norm(b), 1e-300)
+
+
+@pytest.mark.parametrize("closed,t", [(False, 1.0), (False, 0.5), (True, 1.0), (True, 0.4)])
+@pytest.mark.parametrize("n_dot", range(9, 13))
+def test_soft_mm_backward(qa, oracle, n_dot, closed, t):
+    """The adjoint of 9 <= N <= 12 dots, 16 pixels a set; kT = 0.002 is below the
+    range of the factored weights.  The relative bound is that of the adjoint's
+    other tests; at kT = 0.08 every gradient is far from zero."""
+    kw = dict(closed=closed, nhat=n_dot if closed else 0, t=t)
+    rng = np.random.default_rng(2100 + n_dot)
+    for pixels, kT in ((1, 0.08), (15, 0.08), (16, 0.08), (17, 0.08), (33, 0.02), (20, 0.002)):
+        cdd, cgd = problem(n_dot, 400 + n_dot, pixels == 33)
+        V = rng.uniform(-2.0, 3.0, (pixels, n_dot))
+        Gb = rng.standard_normal((pixels, n_dot))
+        print("soft bwd", n_dot, pixels, kT, kw, flush=True)
+        st = oracle.method_setup(cdd, cgd, V, **kw)
+        want = oracle.soft_grad(cdd, cgd, V, kT, st["n0"], st["freemask"], st["k"], Gb)
+        Vt, Gt = torch.as_tensor(V).cuda(), torch.as_tensor(Gb).cuda()
+        _, saved = qa.soft_charge(cdd, cgd, Vt, kT, **kw)
+        check_grads(qa.soft_charge_backward(cdd, cgd, Vt, kT, Gt, saved, **kw), want)
+        # on another stream, which has not seen these capacitances
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            got = qa.soft_charge_backward(cdd, cgd, Vt, kT, Gt, saved, **kw)
+        side.synchronize()
+        check_grads(got, want)
+
+
+def test_soft_mm_backward_many_pixels(qa, oracle):
+    """More sets of pixels than the chip holds blocks: the sum over the pixels
+    against calls of a few sets; 32 gates; a voltage that is not a number
+    reaches its own pixel's dL/dV only."""
+    n, g, P, kT = 9, 32, 20011, 0.05
+    rng = np.random.default_rng(7)
+    cdd, _ = problem(n, 410)
+    cgd = rng.uniform(0.0, 0.2, (n, g))
+    V = torch.as_tensor(rng.uniform(-5.0, 5.0, (P, g))).cuda()
+    Gb = torch.as_tensor(rng.standard_normal((P, n))).cuda()
+    _, saved = qa.soft_charge(cdd, cgd, V, kT)
+    dC, dG, dV = qa.soft_charge_backward(cdd, cgd, V, kT, Gb, saved)
+    parts = []
+    for a in range(0, P, 4000):
+        sl = slice(a, min(a + 4000, P))
+        _, sv = qa.soft_charge(cdd, cgd, V[sl], kT)
+        parts.append(qa.soft_charge_backward(cdd, cgd, V[sl], kT, Gb[sl], sv))
+    for whole, part in ((dC, sum(p[0] for p in parts)), (dG, sum(p[1] for p in parts)),
+                        (dV, torch.cat([p[2] for p in parts]))):
+        assert torch.linalg.norm(whole - part) <= 1e-11 * torch.linalg.norm(part)
+    st = oracle.method_setup(cdd, cgd, V[:40].cpu().numpy())
+    want = oracle.soft_grad(cdd, cgd, V[:40].cpu().numpy(), kT, st["n0"], st["freemask"], st["k"],
+                            Gb[:40].cpu().numpy())[2]
+    assert np.linalg.norm(dV[:40].cpu().numpy() - want) <= 1e-9 * np.linalg.norm(want)
+    V[5, 3] = float("nan")
+    _, saved = qa.soft_charge(cdd, cgd, V, kT)
+    bad = qa.soft_charge_backward(cdd, cgd, V, kT, Gb, saved)[2]
+    assert torch.isnan(bad[5]).all()
+    keep = torch.arange(P, device="cuda") != 5
+    assert torch.equal(bad[keep], dV[keep])
