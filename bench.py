@@ -295,7 +295,7 @@ def main():
         return
     if args.mode == "batch":
         b = qa.Batch(W.ragged_batch(args.batch_diagrams, npix=64))
-        b.run()  # first call: autotune
+        b.run()  # first call: allocations, the plan
         log("batch mode: %d calls on %d diagrams" % (args.steps, args.batch_diagrams))
         timed_calls(lambda: b.run(), args.steps, args.warmup, torch)
         log("done")
@@ -593,7 +593,7 @@ def run_extras(qa, W, torch, d, V, out, args, gpu):
         ds = W.ragged_batch(args.batch_diagrams, npix=64)
         b = qa.Batch(ds)
         log("batch of %d diagrams packed in %.1f s" % (args.batch_diagrams, time.perf_counter() - t0))
-        b.run()  # first call: autotune
+        b.run()  # first call: allocations, the plan
         torch.cuda.synchronize()
         nb = max(3, steps // 10)
         wall = timed_calls(lambda: b.run(), nb, 1, torch)

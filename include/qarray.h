@@ -253,7 +253,7 @@ qa_status qa_soft_charge_backward_grid(const qa_problem *prob, const qa_grid *gr
 size_t qa_saved_bytes(int64_t P, int32_t n_dot);
 
 /* A batch of independent diagrams (the dataset-generation use of Sec. 1)
- * in one launch sequence (prologue of every diagram, one persistent
+ * in one launch sequence (prologue of every diagram, one
  * kernel over all pixels).  Diagram d has its own problem
  * probs[d] (N_d, G_d, mode, N_hat, kT, t; precision is ignored, every
  * energy is FP64) and its own P_d pixels.

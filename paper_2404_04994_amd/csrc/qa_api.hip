@@ -72,6 +72,8 @@ struct Workspace {
     int64_t bmats_cap = 0;
     DiagRec *brecs = nullptr;
     int64_t brecs_cap = 0;
+    int32_t *bowner = nullptr;  // the diagram of each work item
+    int64_t bowner_cap = 0;
     // pinned staging of the batch plan (headers, then matrices), two slots
     // used in turn; a slot is rewritten only after its last copy has run
     unsigned char *bstage[2] = {};
@@ -101,19 +103,12 @@ struct Workspace {
     std::map<std::vector<int64_t>, hipGraphExec_t> graphs;
 };
 
-// autotuned launch shape of the batched kernel, per batch signature
-struct BatchTune {
-    int blocks;
-    bool by_size;  // work order: diagrams with more candidates first
-};
-std::map<std::vector<int64_t>, BatchTune> g_tune;
-bool g_autotune_env_read = false, g_autotune = true, g_graphs = false;
+bool g_env_read = false, g_graphs = false;
 
 void read_env()
 {
-    if (g_autotune_env_read) return;
-    g_autotune_env_read = true;
-    if (const char *e = getenv("QA_AUTOTUNE")) g_autotune = atoi(e) != 0;
+    if (g_env_read) return;
+    g_env_read = true;
     if (const char *e = getenv("QA_GRAPHS")) g_graphs = atoi(e) != 0;
 }
 
@@ -833,16 +828,13 @@ struct BatchPlan {
 // pix_counts are unused)
 void plan_batch(const qa_problem *probs, int32_t n_diag, const int64_t *v_offsets,
                 const int64_t *pix_counts, const qa_grid *grids, const int64_t *out_offsets,
-                bool by_size, BatchPlan &plan)
+                BatchPlan &plan)
 {
     std::vector<int> order(n_diag);
     for (int d = 0; d < n_diag; ++d) order[d] = d;
-    if (by_size) {
-        // largest candidate sets first, so the tail of the queue is cheap
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-            return probs[a].n_dot > probs[b].n_dot;
-        });
-    }
+    // largest candidate sets first, so that the last work items are short
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int a, int b) { return probs[a].n_dot > probs[b].n_dot; });
     plan.hdr.resize(n_diag);
     plan.mats.clear();
     plan.tiles = 0;
@@ -895,6 +887,7 @@ qa_status upload_plan(Workspace *w, const BatchPlan &plan, int32_t n_diag)
     if ((st = grow(w, w->bhdr, w->bhdr_cap, n_diag))) return st;
     if ((st = grow(w, w->bmats, w->bmats_cap, (int64_t)plan.mats.size()))) return st;
     if ((st = grow(w, w->brecs, w->brecs_cap, n_diag))) return st;
+    if ((st = grow(w, w->bowner, w->bowner_cap, plan.tiles))) return st;
     if (w->bhdr != h0 || w->bmats != m0) w->bplan_inputs.clear();
     const size_t nh = sizeof(BatchHdr) * n_diag, nm = sizeof(double) * plan.mats.size();
     const unsigned char *hb = reinterpret_cast<const unsigned char *>(plan.hdr.data());
@@ -931,15 +924,14 @@ qa_status upload_plan(Workspace *w, const BatchPlan &plan, int32_t n_diag)
     return QA_OK;
 }
 
-// the device work of one batch: zero the counters and the queue, prologue of
-// every diagram, the persistent kernel
+// the device work of one batch: prologue of every diagram (it clears the
+// counters), the pixel kernel
 qa_status enqueue_batch(Workspace *w, hipStream_t s, int32_t n_diag, const BatchPlan &plan,
-                        const double *V, int32_t *n_out, double *nbar, int blocks)
+                        const double *V, int32_t *n_out, double *nbar)
 {
-    QA_HIP(launch_zero_i64(w->counters, kCounterWords, s));
-    QA_HIP(launch_prep_batch(w->bhdr, w->bmats, w->brecs, n_diag, s));
-    QA_HIP(launch_batch(w->bhdr, w->brecs, w->bmats, n_diag, plan.tiles, V, n_out, nbar,
-                        w->counters, plan.max_dot, blocks, s));
+    QA_HIP(launch_prep_batch(w->bhdr, w->bmats, w->brecs, n_diag, w->bowner, w->counters, s));
+    QA_HIP(launch_batch(w->bhdr, w->brecs, w->bmats, w->bowner, plan.tiles, V, n_out, nbar,
+                        w->counters, plan.max_dot, s));
     return QA_OK;
 }
 
@@ -991,70 +983,22 @@ qa_status batched(const qa_problem *probs, int32_t n_diag, const double *V_dev,
     qa_status st;
     if ((st = get_ws((hipStream_t)hip_stream, &w))) return st;
 
-    // signature of the batch for the tuning cache
-    int max_dot = 0, n_soft = 0;
-    for (int d = 0; d < n_diag; ++d) {
-        max_dot = std::max(max_dot, probs[d].n_dot);
-        n_soft += probs[d].kT > 0.0;
-    }
     w->bstats_used = 0;  // the batched kernels count into the counter slots only
-    std::vector<int64_t> sig = {n_diag, total, max_dot, n_soft > 0 && nbar_out_dev != nullptr,
-                                grids != nullptr};
     BatchPlan plan;
-    auto it = g_tune.find(sig);
-    if (it == g_tune.end() && g_autotune) {
-        // time every candidate launch shape on this very batch (each run
-        // writes the same outputs; the better of two runs, so that a cold
-        // first launch or a stray slow one does not decide) and keep the
-        // fastest
-        int dev = 0, cus = 256;
-        QA_HIP(hipGetDevice(&dev));
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
-        hipEvent_t e0, e1;
-        QA_HIP(hipEventCreate(&e0));
-        QA_HIP(hipEventCreate(&e1));
-        BatchTune best{cus * 4, true};
-        float best_ms = 1e30f;
-        for (int by_size = 0; by_size < 2; ++by_size) {
-            plan_batch(probs, n_diag, v_offsets, pix_counts, grids, out_offsets, by_size != 0,
-                       plan);
-            if ((st = upload_plan(w, plan, n_diag))) return st;
-            for (int mult : {2, 4, 8, 16}) {
-                const int blocks = cus * mult;
-                for (int rep = 0; rep < 2; ++rep) {
-                    QA_HIP(hipEventRecord(e0, w->stream));
-                    if ((st = enqueue_batch(w, w->stream, n_diag, plan, V_dev, n_out_dev,
-                                            nbar_out_dev, blocks)))
-                        return st;
-                    QA_HIP(hipEventRecord(e1, w->stream));
-                    QA_HIP(hipEventSynchronize(e1));
-                    float ms = 0.0f;
-                    QA_HIP(hipEventElapsedTime(&ms, e0, e1));
-                    if (ms < best_ms) { best_ms = ms; best = BatchTune{blocks, by_size != 0}; }
-                }
-            }
-        }
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        it = g_tune.emplace(sig, best).first;
-    }
-    const BatchTune tune = (it != g_tune.end()) ? it->second : BatchTune{1024, true};
-    plan_batch(probs, n_diag, v_offsets, pix_counts, grids, out_offsets, tune.by_size, plan);
+    plan_batch(probs, n_diag, v_offsets, pix_counts, grids, out_offsets, plan);
     if ((st = upload_plan(w, plan, n_diag))) return st;
 
     if (!g_graphs) {
-        if ((st = enqueue_batch(w, w->stream, n_diag, plan, V_dev, n_out_dev, nbar_out_dev,
-                                tune.blocks)))
+        if ((st = enqueue_batch(w, w->stream, n_diag, plan, V_dev, n_out_dev, nbar_out_dev)))
             return st;
         return read_stats(w, stats);
     }
-    // one graph per (batch layout, buffers): zero kernel, prologue, persistent
-    // kernel; captured on a private stream, launched on the caller's
-    std::vector<int64_t> key = {n_diag, plan.tiles, plan.max_dot, tune.blocks,
+    // one graph per (batch layout, buffers): prologue, pixel kernel; captured on a private stream, launched on the caller's
+    std::vector<int64_t> key = {n_diag, plan.tiles, plan.max_dot,
                                 (int64_t)(uintptr_t)V_dev, (int64_t)(uintptr_t)n_out_dev,
                                 (int64_t)(uintptr_t)nbar_out_dev, (int64_t)(uintptr_t)w->bhdr,
-                                (int64_t)(uintptr_t)w->bmats, (int64_t)(uintptr_t)w->brecs};
+                                (int64_t)(uintptr_t)w->bmats, (int64_t)(uintptr_t)w->brecs,
+                                (int64_t)(uintptr_t)w->bowner};
     if (!w->graph || w->graph_key != key) {
         if (w->graph) {
             QA_HIP(hipStreamSynchronize(w->stream));
@@ -1064,8 +1008,7 @@ qa_status batched(const qa_problem *probs, int32_t n_diag, const double *V_dev,
         if (!w->cap_stream) QA_HIP(hipStreamCreateWithFlags(&w->cap_stream, hipStreamNonBlocking));
         hipGraph_t g;
         QA_HIP(hipStreamBeginCapture(w->cap_stream, hipStreamCaptureModeThreadLocal));
-        st = enqueue_batch(w, w->cap_stream, n_diag, plan, V_dev, n_out_dev, nbar_out_dev,
-                           tune.blocks);
+        st = enqueue_batch(w, w->cap_stream, n_diag, plan, V_dev, n_out_dev, nbar_out_dev);
         hipError_t ec = hipStreamEndCapture(w->cap_stream, &g);
         if (st) return st;
         if (ec != hipSuccess)
@@ -1221,6 +1164,7 @@ void qa_release(void *hip_stream)
     (void)hipFree(w->bhdr);
     (void)hipFree(w->bmats);
     (void)hipFree(w->brecs);
+    (void)hipFree(w->bowner);
     for (int i = 0; i < 2; ++i) {
         if (w->bstage[i]) (void)hipHostFree(w->bstage[i]);
         if (w->bstage_ev[i]) (void)hipEventDestroy(w->bstage_ev[i]);

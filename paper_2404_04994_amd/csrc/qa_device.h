@@ -37,12 +37,10 @@ __device__ __forceinline__ bool better(double e, uint32_t s, double e1, uint32_t
 // of those dots raised by one (k = -1 for open arrays).  Returns the flags
 // (bit1: no admissible state even at t = 1, bit2: the threshold doubled).
 template <int NM>
-__device__ __forceinline__ int candidate_set(const DiagRec *__restrict__ dr, bool closed,
+__device__ __forceinline__ int candidate_set(int n, bool closed, int nhat, double t,
                                              const double (&x)[NM], int (&n0)[NM],
                                              uint32_t &fm, int &k)
 {
-    const int n = dr->n;
-    double t = dr->t;
     int flags = 0;
     k = -1;
     for (int iter = 0; iter < 80; ++iter) {
@@ -64,7 +62,7 @@ __device__ __forceinline__ int candidate_set(const DiagRec *__restrict__ dr, boo
             }
         }
         if (!closed) break;
-        const int need = dr->nhat - sum0;
+        const int need = nhat - sum0;
         if (need >= 0 && need <= __popc(fm)) { k = need; break; }
         if (t >= 1.0) {  // |sum x* - N_hat| < 1 makes this unreachable
             k = need < 0 ? 0 : __popc(fm);
@@ -109,121 +107,78 @@ __device__ __forceinline__ double rsqrt_nr(double a)
     return r * fma(-h * r, r, 1.5);
 }
 
-// Cholesky solve of an SPD system held as a packed lower triangle, M fixed.
-// The factor's diagonal is kept as its reciprocal, so the factorisation and
-// both substitutions multiply where they would divide (no square root, no
-// division).  On return a holds L below the diagonal and 1 / L_jj on it.
-template <int M>
-__device__ __forceinline__ void chol_solve(double (&a)[M * (M + 1) / 2], double (&b)[M])
+// The QP of Sec. 3.1.2, min U(x) s.t. x >= 0 [and 1^T x = N_hat], in its KKT
+// form x = x_0 + K mu, mu >= 0, x >= 0, mu_i x_i = 0, with x_0 the analytic
+// minimum and K = C_dd (open arrays) or C_dd - c c^T / 1^T c, c = C_dd 1 (closed:
+// the multiplier of the sum eliminated).  For an active set W (x_W = 0, mu zero
+// off W) K_WW mu_W = -x_0,W, by a Cholesky factorisation of all rows in which the
+// columns outside W have a zero pivot: their rows' entries then meet only zeros,
+// so no entry needs a mask and all indexing is static.  (In a closed array W
+// never holds every dot, as the others' x sum to N_hat > 0, so K_WW is definite.)
+// Primal-dual active-set update (Hintermueller, Ito and Kunisch, SIAM J. Optim.
+// 13, 2003): keep dots with mu > 0, add dots with x < 0; stop when W repeats.
+// For open arrays C_dd is an M-matrix and W only grows (Chandrasekaran's
+// method), at most N rounds.  Returns false when the iteration did not settle
+// (x is then the last iterate, clipped at 0).  Dots n.. have zero rows in K and
+// zero x_0.
+template <int NM>
+__device__ __forceinline__ bool qp_solve(const double *__restrict__ K, double tol,
+                                         const double (&x0)[NM], double (&x)[NM])
 {
 #define LIDX(i, j) ((i) * ((i) + 1) / 2 + (j))
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        double d = a[LIDX(j, j)];
-#pragma unroll
-        for (int k = 0; k < j; ++k) d -= a[LIDX(j, k)] * a[LIDX(j, k)];
-        const double inv = rsqrt_nr(d);
-        a[LIDX(j, j)] = inv;
-#pragma unroll
-        for (int i = j + 1; i < M; ++i) {
-            double s = a[LIDX(i, j)];
-#pragma unroll
-            for (int k = 0; k < j; ++k) s -= a[LIDX(i, k)] * a[LIDX(j, k)];
-            a[LIDX(i, j)] = s * inv;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-        double s = b[i];
-#pragma unroll
-        for (int k = 0; k < i; ++k) s -= a[LIDX(i, k)] * b[k];
-        b[i] = s * a[LIDX(i, i)];
-    }
-#pragma unroll
-    for (int i = M - 1; i >= 0; --i) {
-        double s = b[i];
-#pragma unroll
-        for (int k = i + 1; k < M; ++k) s -= a[LIDX(k, i)] * b[k];
-        b[i] = s * a[LIDX(i, i)];
-    }
-#undef LIDX
-}
-
-// The QP of Sec. 3.1.2, min U(x) s.t. x >= 0 [and 1^T x = N_hat], in its KKT
-// form x = x_u + C_dd mu + lambda C_dd 1, mu >= 0, x >= 0, mu_i x_i = 0.
-// For an active set W (x_W = 0, mu zero off W) the unknowns (mu_W, lambda)
-// solve  [C_WW  c_W; c_W^T  1^T c] [mu_W; lambda] = [-x_u,W; N_hat - 1^T x_u]
-// (open arrays: the C_WW block alone).  The system is embedded in a fixed
-// (NM [+1])-size SPD matrix with identity rows for dots outside W, so all
-// indexing is static.  Primal-dual active-set update (Hintermueller, Ito and
-// Kunisch, SIAM J. Optim. 13, 2003): keep dots with mu > 0, add dots with
-// x < 0; stop when W repeats.  For open arrays C_dd is an M-matrix and W only
-// grows (Chandrasekaran's method), at most N rounds.  Returns false when the
-// iteration did not settle (x is then the last iterate, clipped at 0).
-template <int NM, bool CLOSED>
-__device__ bool qp_solve(const DiagRec *__restrict__ dr, const double (&xu)[NM], double (&x)[NM])
-{
-    constexpr int M = NM + (CLOSED ? 1 : 0);
-    const int n = dr->n;
-    double sx = 0.0, scale = 1.0, mu[NM];
-#pragma unroll
-    for (int i = 0; i < NM; ++i) {
-        sx += xu[i];
-        scale = fmax(scale, fabs(xu[i]));
-    }
-    const double tol = 1e-13 * scale;
-    const double lam0 = CLOSED ? ((double)dr->nhat - sx) / dr->one_c : 0.0;
     uint32_t W = 0;
 #pragma unroll
-    for (int i = 0; i < NM; ++i)
-        if (i < n && xu[i] + lam0 * dr->c[i] < 0.0) W |= 1u << i;
+    for (int i = 0; i < NM; ++i) W |= x0[i] < 0.0 ? 1u << i : 0u;
     bool converged = false;
     for (int round = 0; round < 4 * NM + 4; ++round) {
-        double a[M * (M + 1) / 2], b[M];
+        double a[NM * (NM + 1) / 2], mu[NM];
 #pragma unroll
-        for (int i = 0; i < NM; ++i) {
-            const bool wi = W >> i & 1u;
+        for (int j = 0; j < NM; ++j) {
+            asm volatile("" ::: "memory");  // (K loaded ahead would spill)
+            const bool wj = W >> j & 1u;
+            double d = K[j * kMaxDot + j], y = -x0[j];
 #pragma unroll
-            for (int j = 0; j <= i; ++j) {
-                const bool wj = W >> j & 1u;
-                double v = (wi && wj) ? dr->Cdd[i * kMaxDot + j] : 0.0;
-                if (i == j && !wi) v = 1.0;
-                a[i * (i + 1) / 2 + j] = v;
+            for (int k = 0; k < j; ++k) {
+                d -= a[LIDX(j, k)] * a[LIDX(j, k)];
+                y -= a[LIDX(j, k)] * mu[k];
             }
-            b[i] = wi ? -xu[i] : 0.0;
-        }
-        if (CLOSED) {
+            const double r = rsqrt_nr(d);
+            const double inv = wj ? r : 0.0;
+            a[LIDX(j, j)] = inv;
+            mu[j] = y * inv;
 #pragma unroll
-            for (int j = 0; j < NM; ++j)
-                a[NM * (NM + 1) / 2 + j] = (W >> j & 1u) ? dr->c[j] : 0.0;
-            a[NM * (NM + 1) / 2 + NM] = dr->one_c;
-            b[M - 1] = (double)dr->nhat - sx;
+            for (int i = j + 1; i < NM; ++i) {
+                double s = K[i * kMaxDot + j];
+#pragma unroll
+                for (int k = 0; k < j; ++k) s -= a[LIDX(i, k)] * a[LIDX(j, k)];
+                a[LIDX(i, j)] = s * inv;
+            }
         }
-        chol_solve<M>(a, b);
-        const double lam = CLOSED ? b[M - 1] : 0.0;
+#pragma unroll
+        for (int i = NM - 1; i >= 0; --i) {
+            double s = mu[i];
+#pragma unroll
+            for (int k = i + 1; k < NM; ++k) s -= a[LIDX(k, i)] * mu[k];
+            mu[i] = s * a[LIDX(i, i)];
+        }
         uint32_t Wn = 0;
 #pragma unroll
-        for (int i = 0; i < NM; ++i) mu[i] = (W >> i & 1u) ? b[i] : 0.0;
-#pragma unroll
         for (int i = 0; i < NM; ++i) {
-            double s = xu[i] + lam * dr->c[i];
+            asm volatile("" ::: "memory");
+            const bool wi = W >> i & 1u;
+            double s = x0[i];
 #pragma unroll
-            for (int j = 0; j < NM; ++j) s += dr->Cdd[i * kMaxDot + j] * mu[j];
-            x[i] = (W >> i & 1u) ? 0.0 : s;
-            if (i < n) {
-                if (W >> i & 1u) {
-                    if (mu[i] > -tol) Wn |= 1u << i;
-                } else if (x[i] < -tol) {
-                    Wn |= 1u << i;
-                }
-            }
+            for (int j = 0; j < NM; ++j) s += K[i * kMaxDot + j] * mu[j];
+            x[i] = wi ? 0.0 : s;
+            Wn |= (wi ? mu[i] > -tol : s < -tol) ? 1u << i : 0u;
         }
         if (Wn == W) { converged = true; break; }
         W = Wn;
     }
 #pragma unroll
-    for (int i = 0; i < NM; ++i) x[i] = (i < n) ? fmax(x[i], 0.0) : 0.0;
+    for (int i = 0; i < NM; ++i) x[i] = fmax(x[i], 0.0);
     return converged;
+#undef LIDX
 }
 
 // ---------------------------------------------------------------------------

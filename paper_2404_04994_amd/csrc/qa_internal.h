@@ -25,8 +25,6 @@ constexpr int kWave = 64;
 // on one address from every block serialise at the memory side, so the
 // statistics are spread over kCounterSlots cache lines ([slot][C_NUM], a
 // block adds to slot blockIdx mod kCounterSlots) and summed by the host.
-// C_WORK is the cursor of one shard of the batched kernel's work queue in
-// every slot.
 constexpr int kCounterSlots = 64;
 enum Counter {
     C_PIXELS = 0,
@@ -39,7 +37,6 @@ enum Counter {
     C_SCORED = 7,       // states whose approximate energy a scorer computed
     C_UNUSED8 = 8,
     C_UNUSED9 = 9,
-    C_WORK = 10,        // work-queue shard cursor of the batched kernel
     C_NUM = 16
 };
 constexpr int kCounterWords = kCounterSlots * C_NUM;
@@ -403,12 +400,12 @@ hipError_t launch_sensor(const DiagRec *dr, int n_sensor, int shape, double gamm
                          double pink, int octaves, double *signal, hipStream_t s);
 hipError_t launch_sensor_jumps(int64_t P, int n_sensor, const double *u, double rate, double amp,
                                double *signal, hipStream_t s);
-// ragged batch (qa_batch.hip): prologue of every diagram, then one persistent
+// ragged batch (qa_batch.hip): prologue of every diagram, then one
 // kernel over all 64-pixel work items
 hipError_t launch_prep_batch(const BatchHdr *hdr, const double *mats, DiagRec *recs, int n_diag,
-                             hipStream_t s);
-hipError_t launch_batch(const BatchHdr *hdr, const DiagRec *recs, const double *mats, int n_diag,
-                        int64_t tiles, const double *V, int32_t *n_out, double *nbar,
-                        int64_t *counters, int max_dot, int blocks, hipStream_t s);
+                             int32_t *owner, int64_t *counters, hipStream_t s);
+hipError_t launch_batch(const BatchHdr *hdr, const DiagRec *recs, const double *mats,
+                        const int32_t *owner, int64_t tiles, const double *V, int32_t *n_out,
+                        double *nbar, int64_t *counters, int max_dot, hipStream_t s);
 
 }  // namespace qa

@@ -149,3 +149,29 @@ def test_empty_diagram_in_batch(qa, oracle):
     ds = W.ragged_batch(3, npix=10, start=400)
     ds[1].V = ds[1].V[:0]
     check_batch(qa, oracle, ds)
+
+
+@pytest.mark.parametrize("closed", [False, True])
+@pytest.mark.parametrize("n_dot", range(1, 9))
+def test_dense_box_blocks(qa, oracle, n_dot, closed):
+    """The dense walk of 1..8 dots (from 5 on in blocks that a bound leaves
+    out) at pixel counts around a wave, temperatures that need few blocks or
+    all of them, and a C_dd with couplings of the other sign, for which A has
+    negative elements; the bounds of check_diagram."""
+    rng = np.random.default_rng(4000 + n_dot)
+    ds = []
+    for pixels, kT, sign in ((1, 0.01, -1), (63, 0.0, -1), (64, 0.3, -1), (65, 2e-4, -1),
+                             (200, 5.0, -1), (130, 0.02, 1)):
+        cdd = np.diag(rng.uniform(1.0, 1.4, n_dot))
+        for i in range(n_dot - 1):
+            cdd[i, i + 1] = cdd[i + 1, i] = sign * rng.uniform(0.1, 0.3)
+        cgd = np.diag(rng.uniform(0.5, 1.0, n_dot)) + rng.uniform(0.0, 0.1, (n_dot, n_dot))
+        V = rng.uniform(-1.0, 5.0, (pixels, n_dot))
+        ds.append(W.Diagram(cdd, cgd, V, closed=closed, nhat=int(rng.integers(1, 2 * n_dot + 1)),
+                            kT=kT))
+    b, st = check_batch(qa, oracle, ds)
+    for i, d in enumerate(ds):
+        if closed:
+            assert (b.result(i)[0].sum(1) == d.nhat).all()
+        else:
+            assert st["candidates"] == b.pixels << n_dot
