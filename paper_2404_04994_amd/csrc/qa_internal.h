@@ -285,8 +285,9 @@ __device__ __forceinline__ double sweep_volt(double v0, double e1, double e2, do
     const double s = v0 + a * e1;
     return s + b * e2;
 }
-// the sweep coordinates (a, b) of pixel p
-__device__ __forceinline__ void grid_ab(const VGrid &G, int64_t p, double &a, double &b)
+// the sweep coordinates (a, b) of pixel p (Grid: VGrid, SetupIn)
+template <typename Grid>
+__device__ __forceinline__ void grid_ab(const Grid &G, int64_t p, double &a, double &b)
 {
     a = lin_point(p % G.nx, G.nx, G.a0, G.da, G.a1);
     b = lin_point(p / G.nx, G.ny, G.b0, G.db, G.b1);
@@ -310,6 +311,22 @@ struct InputChunk {
     int32_t part;        // 0: header and C_dd; 1: C_gd rows [row0, row1)
     int32_t row0, row1;  // part 1: rows of the padded C_gd written by this chunk
     double v[kChunkDoubles];  // part 0: C_dd, n x n; part 1: rows row0.. of C_gd, each g long
+};
+
+// A call's inputs as arguments of the setup kernel: v holds the lower triangle of
+// C_dd by rows, C_gd (n x g) and, for a sweep, v0, e1, e2 (g each).  Against a copy
+// into the record ahead of the kernel (with the event that guards its pinned
+// source) a call takes 4.4 us for 9.3 at the host and a launch less on the GPU; 256
+// or 640 blocks that read 3 KB of arguments take no longer than from memory.  440
+// doubles keep the kernel's arguments below 4 KB: 16 dots with 16 gates and a sweep.
+constexpr int kSetupInDoubles = 440;
+struct SetupIn {
+    int32_t n, g, closed, nhat;
+    double kT, t;
+    int32_t prec, on;  // on: a sweep, of
+    double a0, da, a1, b0, db, b1;
+    int64_t nx, ny;
+    double v[kSetupInDoubles];
 };
 
 // which lower bound of a high part the setup forms per pixel (N >= 9): none,
@@ -342,12 +359,15 @@ hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s
 // setup_blocks(P, n_dot) blocks; split: the bound terms the scorer of this call
 // reads (kBoundNone for N <= 8); rt: receives the row tables (N >= 9, needed for
 // kBoundLow6) or NULL; x_out (P x N) / flags_out (P) are optional
-// copies of x*; grid, when given and on, replaces the voltages V.  P >= 1.
+// copies of x*; grid, when given and on, replaces the voltages V; in: the inputs
+// (with the sweep) as arguments, stored into dr by the kernel, or NULL when dr
+// holds them.  P >= 1.
 int64_t setup_blocks(int64_t P, int n_dot);
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
                         int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
                         hipStream_t s, double *x_out = nullptr, int32_t *flags_out = nullptr,
-                        const VGrid *grid = nullptr);
+                        const VGrid *grid = nullptr,
+                        const SetupIn *in = nullptr);
 // T = 0 argmin in FP64 over the candidate set of every pixel
 hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                              int64_t *counters, int n_dot, hipStream_t s);

@@ -237,7 +237,7 @@ __device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, int dot
 constexpr int kSetupThreads = kWave + kSetupPixThreads;
 static_assert(kSetupThreads >= kMaxDot * kMaxDot, "C_dd staging: one entry per thread");
 
-template <int NM, bool CLOSED>
+template <int NM, bool CLOSED, bool ARGS>
 __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict__ dr,
                                                          const double *__restrict__ V, int64_t P,
                                                          PixRec *__restrict__ pr,
@@ -246,7 +246,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
                                                          double *__restrict__ x_out,
                                                          int32_t *__restrict__ flags_out,
                                                          const int split,
-                                                         RowTab *__restrict__ rt, const VGrid vg)
+                                                         RowTab *__restrict__ rt,
+                                                         const std::conditional_t<ARGS, SetupIn, VGrid> vg)
 {
     __shared__ double sCdd[kMaxDot * kMaxDot];  // C_dd (input)
     __shared__ double sA[kMaxDot * kMaxDot];    // A (symmetric), from wave 0
@@ -257,6 +258,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     __shared__ double sMult[NM == 16 ? kSetupPixThreads : 1];
     __shared__ double sLam[NM == 16 && CLOSED ? kSetupPixThreads : 1];
     __shared__ double sG[kMaxGate * NM];        // C_gd transposed: sG[j * NM + i]
+    __shared__ double sV[ARGS ? 3 * kMaxGate : 1];  // a sweep's v0, e1, e2 (g each)
     __shared__ int cnt[4];
     // Staging in one round trip: every load below is issued before any of
     // them is used.  C_gd (transposed, only the gates the diagram has) by
@@ -265,8 +267,14 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     // pixel waves of 16-dot groups also fetch their voltages (lane j: V_j
     // and V_16+j).
     const int tid = threadIdx.x;
-    const int n = dr->n, g = dr->g, nhat = dr->nhat;
-    const double t_in = dr->t;
+    int n, g, nhat;
+    double t_in;
+    if constexpr (ARGS) {
+        n = vg.n, g = vg.g, nhat = vg.nhat, t_in = vg.t;
+    } else {
+        n = dr->n, g = dr->g, nhat = dr->nhat, t_in = dr->t;
+    }
+    const int tri = n * (n + 1) / 2;  // (arguments: entries of C_dd)
     const bool pixel_wave = tid >= kWave;
     const int tp = tid - kWave;  // thread index among the pixel waves
     const int dot = tp & (NM - 1);
@@ -285,13 +293,24 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
 #pragma unroll
     for (int r = 0; r < kGv; ++r) {
         const int e = tid + r * kSetupThreads;
-        gv[r] = (e < g * NM) ? dr->Cgd[(e % NM) * kMaxGate + e / NM] : 0.0;
+        if constexpr (ARGS)
+            gv[r] = (e < g * NM && e % NM < n) ? vg.v[tri + (e % NM) * g + e / NM] : 0.0;
+        else
+            gv[r] = (e < g * NM) ? dr->Cgd[(e % NM) * kMaxGate + e / NM] : 0.0;
     }
     double m4[4];
     if (!pixel_wave) {
         const int j = tid & 15, b = tid >> 4;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) m4[q] = dr->Cdd[(4 * b + q) * kMaxDot + j];
+        for (int q = 0; q < 4; ++q) {
+            const int i = 4 * b + q;
+            if constexpr (ARGS) {
+                const int hi = i > j ? i : j, lo = i > j ? j : i;
+                m4[q] = hi < n ? vg.v[hi * (hi + 1) / 2 + lo] : 0.0;
+            } else {
+                m4[q] = dr->Cdd[i * kMaxDot + j];
+            }
+        }
     }
     double v0 = 0.0, v1 = 0.0;
     if (NM == 16 && pixel_wave && !vg.on) {
@@ -303,6 +322,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         const int e = tid + r * kSetupThreads;
         if (e < g * NM) sG[e] = gv[r];
     }
+    if constexpr (ARGS)
+        if (vg.on && tid < 3 * g) sV[tid] = vg.v[tri + n * g + tid];
     if (tid < 4) cnt[tid] = 0;
     if (!pixel_wave) {
         // wave 0 holds all of C_dd (lane 16 b + j: column j of rows
@@ -353,7 +374,12 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         if (vg.on) {
             double a, b;
             grid_ab(vg, pc, a, b);
-            for (int j = 0; j < g; ++j) xu += sG[j * NM + dot] * grid_v(vg, j, a, b);
+            for (int j = 0; j < g; ++j) {
+                double vj;
+                if constexpr (ARGS) vj = sweep_volt(sV[j], sV[g + j], sV[2 * g + j], a, b);
+                else vj = grid_v(vg, j, a, b);
+                xu += sG[j * NM + dot] * vj;
+            }
         } else if constexpr (NM == 16) {
             // V_j from lane j of the group (prefetched before the barrier)
             static_for_dev<0, kMaxGate>([&](auto jc) {
@@ -616,6 +642,23 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     // of the first 256 blocks
     if (blockIdx.x == 0) {
         prep_store_core(dr, sA, sc, red);
+        if constexpr (ARGS) {
+            if (tid == 0) {
+                dr->n = n;
+                dr->g = g;
+                dr->closed = vg.closed;
+                dr->nhat = nhat;
+                dr->kT = vg.kT;
+                dr->t = t_in;
+                dr->prec = vg.prec;
+                dr->pad0 = 0;
+            }
+            for (int e = tid; e < kMaxDot * kMaxDot; e += kSetupThreads) dr->Cdd[e] = sCdd[e];
+            for (int e = tid; e < kMaxDot * kMaxGate; e += kSetupThreads) {
+                const int i = e / kMaxGate, j = e % kMaxGate;
+                dr->Cgd[e] = (i < n && j < g) ? sG[j * NM + i] : 0.0;
+            }
+        }
         if (counters)
             for (int i = threadIdx.x; i < kCounterWords; i += blockDim.x) counters[i] = 0;
     }
@@ -625,7 +668,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             for (int u = blockIdx.x * kWaves + tid / kWave; u < kRowUnits; u += gridDim.x * kWaves)
                 prep_row_unit(rt, sA, sS6, n, u);
     } else if (gridDim.x < 256) {
-        prep_tables_spread(dr, sA, sS);
+        prep_tables_spread(dr, sA, sS, -1, 0, n);
     }
 }
 
@@ -646,20 +689,24 @@ int64_t setup_blocks(int64_t P, int n_dot)
 
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
                         int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
-                        hipStream_t s, double *x_out, int32_t *flags_out, const VGrid *sweep)
+                        hipStream_t s, double *x_out, int32_t *flags_out, const VGrid *sweep,
+                        const SetupIn *in)
 {
     if (split == kBoundLow6 && (!rt || n_dot < 9)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)setup_blocks(P, n_dot)), block(kSetupThreads);
+    const auto go = [&](auto kernel, const auto &src) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, dr, V, P, pr, counters, bstats, x_out,
+                           flags_out, (int)split, rt, src);
+    };
+    if (in) {
+        if (closed) QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, true, true>, *in)));
+        else QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, false, true>, *in)));
+        return hipGetLastError();
+    }
     VGrid vg{};
     if (sweep) vg = *sweep;
-    if (closed)
-        QA_DISPATCH_NM(n_dot, hipLaunchKernelGGL((k_setup<NM_, true>), grid, block, 0, s, dr, V,
-                                                 P, pr, counters, bstats, x_out, flags_out,
-                                                 (int)split, rt, vg));
-    else
-        QA_DISPATCH_NM(n_dot, hipLaunchKernelGGL((k_setup<NM_, false>), grid, block, 0, s, dr, V,
-                                                 P, pr, counters, bstats, x_out, flags_out,
-                                                 (int)split, rt, vg));
+    if (closed) QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, true, false>, vg)));
+    else QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, false, false>, vg)));
     return hipGetLastError();
 }
 
