@@ -70,6 +70,8 @@ struct Workspace {
     int64_t bhdr_cap = 0;
     double *bmats = nullptr;
     int64_t bmats_cap = 0;
+    int32_t *parity = nullptr;  // of the telegraph flips (sensor response)
+    int64_t parity_cap = 0;
     DiagRec *brecs = nullptr;
     int64_t brecs_cap = 0;
     int32_t *bowner = nullptr;  // the diagram of each work item
@@ -1226,6 +1228,7 @@ void qa_release(void *hip_stream)
     (void)hipFree(w->bhdr);
     (void)hipFree(w->bmats);
     (void)hipFree(w->brecs);
+    (void)hipFree(w->parity);
     (void)hipFree(w->bowner);
     for (int i = 0; i < 2; ++i) {
         if (w->bstage[i]) (void)hipHostFree(w->bstage[i]);
@@ -1280,10 +1283,15 @@ qa_status qa_sensor_response(const qa_problem *prob, const qa_sensor *sp, const 
     if (noisy && !noise_dev) return fail(QA_E_NULL, "noise_dev is NULL with noise switched on");
     Workspace *w;
     if ((st = get_ws((hipStream_t)hip_stream, &w))) return st;
-    DiagRec *dr0 = w->dr;
-    if ((st = grow(w, w->dr, w->dr_cap, 1))) return st;
-    if (w->dr != dr0) w->dr_inputs.clear();
-    if ((st = upload_diag(w, prob))) return st;
+    if ((st = grow(w, w->parity, w->parity_cap, kSensorParities))) return st;
+    SetupIn in;
+    const bool args = setup_in(prob, nullptr, &in);
+    if (!args) {
+        DiagRec *dr0 = w->dr;
+        if ((st = grow(w, w->dr, w->dr_cap, 1))) return st;
+        if (w->dr != dr0) w->dr_inputs.clear();
+        if ((st = upload_diag(w, prob))) return st;
+    }
     const int S = sp->n_sensor;
     const double *white = (noisy && sp->white > 0.0) ? noise_dev : nullptr;
     const double *pink = (noisy && sp->pink > 0.0) ? noise_dev + (size_t)P * S : nullptr;
@@ -1291,12 +1299,12 @@ qa_status qa_sensor_response(const qa_problem *prob, const qa_sensor *sp, const 
     size_t pink_len = 0;
     for (int k = 0; k < sp->pink_octaves; ++k)
         pink_len += (size_t)S * (size_t)((P + ((int64_t)1 << k) - 1) >> k);
-    QA_HIP(launch_sensor(w->dr, S, sp->shape, sp->gamma, V_dev, P, n_array_dev,
-                         n_array_dev ? nullptr : nbar_array_dev, white, sp->white, pink, sp->pink,
-                         sp->pink > 0.0 ? sp->pink_octaves : 0, signal_dev, w->stream));
-    if (sp->jump > 0.0 && sp->jump_rate > 0.0)
-        QA_HIP(launch_sensor_jumps(P, S, noise_dev + (size_t)P * S + pink_len, sp->jump_rate,
-                                   sp->jump, signal_dev, w->stream));
+    const bool jumps = sp->jump > 0.0 && sp->jump_rate > 0.0;
+    QA_HIP(launch_sensor(w->dr, args ? &in : nullptr, prob->n_dot, S, sp->shape, sp->gamma, V_dev, P,
+                         n_array_dev, n_array_dev ? nullptr : nbar_array_dev, white, sp->white,
+                         pink, sp->pink, sp->pink > 0.0 ? sp->pink_octaves : 0,
+                         jumps ? noise_dev + (size_t)P * S + pink_len : nullptr, sp->jump,
+                         sp->jump_rate, w->parity, signal_dev, w->stream));
     return QA_OK;
 }
 

@@ -411,15 +411,17 @@ hipError_t launch_soft_bwd(const DiagRec *dr, const double *V, int64_t P,
                            double *gradV, int n_dot, hipStream_t s, const VGrid *grid = nullptr);
 hipError_t launch_soft_bwd_final(const DiagRec *dr, double *acc, double *grad_cdd,
                                  double *grad_cgd, hipStream_t s);
-// charge-sensor response (qa_sensor.hip): the last n_sensor dots of dr are
-// sensors; array charges from n_int or n_dbl (P x (n - n_sensor)); noise
-// draws optional (NULL: none); signal P x n_sensor
-hipError_t launch_sensor(const DiagRec *dr, int n_sensor, int shape, double gamma, const double *V,
-                         int64_t P, const int32_t *n_int, const double *n_dbl,
-                         const double *white_draws, double white, const double *pink_draws,
-                         double pink, int octaves, double *signal, hipStream_t s);
-hipError_t launch_sensor_jumps(int64_t P, int n_sensor, const double *u, double rate, double amp,
-                               double *signal, hipStream_t s);
+// charge-sensor response (qa_sensor.hip): the last n_sensor dots of the problem in
+// `in` (or in dr when NULL) are sensors; array charges from n_int or n_dbl
+// (P x (n - n_sensor)); noise draws optional (NULL: none); parity: scratch of
+// kSensorParities words; signal P x n_sensor
+constexpr int kSensorParities = 1024;
+hipError_t launch_sensor(const DiagRec *dr, const SetupIn *in, int n_dot, int n_sensor, int shape,
+                         double gamma, const double *V, int64_t P, const int32_t *n_int,
+                         const double *n_dbl, const double *white_draws, double white,
+                         const double *pink_draws, double pink, int octaves,
+                         const double *jump_draws, double jump, double rate, int32_t *parity,
+                         double *signal, hipStream_t s);
 // ragged batch (qa_batch.hip): prologue of every diagram, then one
 // kernel over all 64-pixel work items
 hipError_t launch_prep_batch(const BatchHdr *hdr, const double *mats, DiagRec *recs, int n_diag,

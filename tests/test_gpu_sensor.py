@@ -140,3 +140,36 @@ def test_sensor_errors(qa):
         qa.sensor_response(cdd, cgd, V, 1, np.zeros((16, 8), np.int32), -1.0)  # gamma <= 0
     with pytest.raises(qa.QArrayError):
         qa.sensor_response(cdd, cgd, V, 1, np.zeros((16, 8), np.int32), 0.05, white=0.1)  # no draws
+
+
+@pytest.mark.parametrize("S,P,g", [(1, 191, 9), (3, 192, 8), (4, 193, 32), (1, 577, 1), (2, 196609, 3),
+                                   (4, 2, 17), (2, 50, 32)])
+def test_tiles_shares_and_gates(qa, oracle, S, P, g):
+    """Samples around a tile of 192 pixels and past 1024 tiles (two tiles a
+    block), 1..32 gates (one group of eight or more, inputs as arguments or
+    copied), every noise source; any array charges will do."""
+    rng = np.random.default_rng(100 * S + P + g)
+    Na = 12 if (S, g) == (2, 32) else 2
+    n = Na + S
+    cdd = np.diag(rng.uniform(1.0, 1.4, n))
+    for i in range(n - 1):
+        cdd[i, i + 1] = cdd[i + 1, i] = -rng.uniform(0.02, 0.2)
+    cgd = rng.uniform(0.0, 0.6, (n, g))
+    V = rng.uniform(-1.0, 3.0, (P, g))
+    n_arr = rng.integers(0, 3, (P, Na)).astype(np.int32)
+    K = 9
+    draws = rng.standard_normal(qa.sensor_noise_len(P, S, K))
+    draws[-P * S:] = rng.uniform(0, 1, P * S)
+    at = np.arange(P) if P < 1000 else np.r_[0:200, 98200:98500, P - 200:P]
+    ref, _ = oracle.sensor_signal(cdd, cgd, V[at], n_arr[at], S, 0.2)
+    off = P * S
+    for s in range(S):
+        for k in range(K):
+            ref[:, s] += 0.02 / np.sqrt(K) * draws[off + (at >> k)]
+            off += (P + (1 << k) - 1) >> k
+    ref += 0.03 * draws[:P * S].reshape(P, S)[at]
+    ref += 0.1 * (np.cumsum(draws[off:].reshape(P, S) < 0.3, 0) % 2)[at]
+    got = qa.sensor_response(cdd, cgd, torch.as_tensor(V).cuda(), S, torch.as_tensor(n_arr).cuda(),
+                             0.2, noise=torch.as_tensor(draws).cuda(), white=0.03, pink=0.02,
+                             pink_octaves=K, jump=0.1, jump_rate=0.3).cpu().numpy()
+    assert np.abs(got[at] - ref).max() <= 1e-10
