@@ -34,9 +34,18 @@ class QArrayError(RuntimeError):
         self.status = status
 
 
+def _address(a):
+    """Address of a contiguous FP64 array (the buffer's, 0.3 us; .ctypes takes 1 us
+    and makes a pointer object in another)."""
+    try:
+        return C.addressof(C.c_double.from_buffer(a))
+    except (TypeError, ValueError):  # read-only or empty
+        return a.ctypes.data
+
+
 class Problem(C.Structure):
     _fields_ = [("n_dot", C.c_int32), ("n_gate", C.c_int32),
-                ("cdd", C.POINTER(C.c_double)), ("cgd", C.POINTER(C.c_double)),
+                ("cdd", C.c_void_p), ("cgd", C.c_void_p),
                 ("mode", C.c_int32), ("n_charge", C.c_int32),
                 ("kT", C.c_double), ("threshold", C.c_double),
                 ("precision", C.c_int32), ("flags", C.c_int32)]
@@ -48,8 +57,8 @@ FLAG_EXHAUSTIVE = 1
 class Grid(C.Structure):
     """qa_grid: V(i, j) = (v0 + a_i e1) + b_j e2, a = linspace(a0, a1, nx),
     b = linspace(b0, b1, ny), pixel p = j * nx + i."""
-    _fields_ = [("v0", C.POINTER(C.c_double)), ("e1", C.POINTER(C.c_double)),
-                ("e2", C.POINTER(C.c_double)), ("a0", C.c_double), ("a1", C.c_double),
+    _fields_ = [("v0", C.c_void_p), ("e1", C.c_void_p),
+                ("e2", C.c_void_p), ("a0", C.c_double), ("a1", C.c_double),
                 ("b0", C.c_double), ("b1", C.c_double), ("nx", C.c_int32), ("ny", C.c_int32)]
 
 
@@ -58,8 +67,7 @@ def make_grid(sweep):
     b0, b1, ny) plus the host arrays it points into (keep both alive)."""
     arrs = tuple(np.ascontiguousarray(_host(sweep[k]), np.float64).ravel()
                  for k in ("v0", "e1", "e2"))
-    dp = C.POINTER(C.c_double)
-    g = Grid(arrs[0].ctypes.data_as(dp), arrs[1].ctypes.data_as(dp), arrs[2].ctypes.data_as(dp),
+    g = Grid(_address(arrs[0]), _address(arrs[1]), _address(arrs[2]),
              float(sweep["a0"]), float(sweep["a1"]), float(sweep["b0"]), float(sweep["b1"]),
              int(sweep["nx"]), int(sweep["ny"]))
     return g, arrs
@@ -133,9 +141,9 @@ def _check(status: int):
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is None:  # the current stream's handle, without a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _host(m):
@@ -150,13 +158,15 @@ def make_problem(cdd, cgd, closed=False, nhat=0, kT=0.0, t=1.0, precision="fp64"
     if cdd.ndim != 2 or cgd.ndim != 2 or cdd.shape[0] != cdd.shape[1] or cgd.shape[0] != cdd.shape[0]:
         raise QArrayError(2, "cdd must be N x N and cgd N x G")
     prec = PRECISION[precision] if isinstance(precision, str) else int(precision)
-    pb = Problem(cdd.shape[0], cgd.shape[1], cdd.ctypes.data_as(C.POINTER(C.c_double)),
-                 cgd.ctypes.data_as(C.POINTER(C.c_double)), QA_CLOSED if closed else QA_OPEN,
-                 int(nhat), float(kT), float(t), prec, int(flags))
+    pb = Problem(cdd.shape[0], cgd.shape[1], _address(cdd), _address(cgd),
+                 QA_CLOSED if closed else QA_OPEN, int(nhat), float(kT), float(t), prec, int(flags))
     return pb, (cdd, cgd)
 
 
 def _device_V(V, n_gate):
+    if (isinstance(V, torch.Tensor) and V.dtype is torch.float64 and V.is_cuda and V.dim() == 2
+            and V.shape[1] == n_gate and V.is_contiguous()):
+        return V
     if not isinstance(V, torch.Tensor):
         V = torch.as_tensor(np.asarray(V, np.float64))
     if not V.is_cuda:
@@ -179,8 +189,8 @@ def ground_state(cdd, cgd, V, closed=False, nhat=0, t=1.0, precision="fp64", str
     if out is None:
         out = torch.empty((P, pb.n_dot), dtype=torch.int32, device=V.device)
     st = Stats() if stats else None
-    _check(lib.qa_ground_state(C.byref(pb), C.c_void_p(V.data_ptr()), P,
-                               C.c_void_p(out.data_ptr()), C.byref(st) if st else None,
+    _check(lib.qa_ground_state(C.byref(pb), V.data_ptr(), P,
+                               out.data_ptr(), C.byref(st) if st else None,
                                _stream(stream)))
     del keep
     return (out, st.as_dict()) if stats else out
@@ -196,7 +206,7 @@ def ground_state_grid(cdd, cgd, sweep, closed=False, nhat=0, t=1.0, precision="f
     g, gkeep = make_grid(sweep)
     out = torch.empty((g.nx * g.ny, pb.n_dot), dtype=torch.int32, device=device)
     st = Stats() if stats else None
-    _check(lib.qa_ground_state_grid(C.byref(pb), C.byref(g), C.c_void_p(out.data_ptr()),
+    _check(lib.qa_ground_state_grid(C.byref(pb), C.byref(g), out.data_ptr(),
                                     C.byref(st) if st else None, _stream(stream)))
     del keep, gkeep
     return (out, st.as_dict()) if stats else out
@@ -211,8 +221,8 @@ def soft_charge_grid(cdd, cgd, sweep, kT, closed=False, nhat=0, t=1.0, stream=No
     P = g.nx * g.ny
     nbar = torch.empty((P, pb.n_dot), dtype=torch.float64, device=device)
     saved = torch.empty(max(saved_bytes(P, pb.n_dot), 1), dtype=torch.uint8, device=device)
-    _check(lib.qa_soft_charge_grid(C.byref(pb), C.byref(g), C.c_void_p(nbar.data_ptr()),
-                                   C.c_void_p(saved.data_ptr()), None, _stream(stream)))
+    _check(lib.qa_soft_charge_grid(C.byref(pb), C.byref(g), nbar.data_ptr(),
+                                   saved.data_ptr(), None, _stream(stream)))
     del keep, gkeep
     return nbar, saved
 
@@ -230,9 +240,9 @@ def soft_charge_backward_grid(cdd, cgd, sweep, kT, grad_nbar, saved, closed=Fals
     dG = torch.empty((pb.n_dot, pb.n_gate), dtype=torch.float64, device=dev)
     dV = torch.empty((P, pb.n_gate), dtype=torch.float64, device=dev) if want_V else None
     _check(lib.qa_soft_charge_backward_grid(
-        C.byref(pb), C.byref(g), C.c_void_p(gb.data_ptr()), C.c_void_p(saved.data_ptr()),
-        C.c_void_p(dC.data_ptr()), C.c_void_p(dG.data_ptr()),
-        C.c_void_p(dV.data_ptr()) if dV is not None else None, _stream(stream)))
+        C.byref(pb), C.byref(g), gb.data_ptr(), saved.data_ptr(),
+        dC.data_ptr(), dG.data_ptr(),
+        dV.data_ptr() if dV is not None else None, _stream(stream)))
     del keep, gkeep
     return dC, dG, dV
 
@@ -253,8 +263,8 @@ def ground_state_noalloc(cdd, cgd, V, out, closed=False, nhat=0, t=1.0, precisio
     if (out.dtype != torch.int32 or not out.is_contiguous() or out.device != V.device
             or tuple(out.shape) != (P, pb.n_dot)):
         raise QArrayError(2, "out must be a contiguous int32 (P, N) tensor on V's device")
-    _check(lib.qa_ground_state_noalloc(C.byref(pb), C.c_void_p(V.data_ptr()), P,
-                                       C.c_void_p(out.data_ptr()), _stream(stream)))
+    _check(lib.qa_ground_state_noalloc(C.byref(pb), V.data_ptr(), P,
+                                       out.data_ptr(), _stream(stream)))
     del keep
     return out
 
@@ -268,8 +278,8 @@ def continuous_min(cdd, cgd, V, closed=False, nhat=0, stream=None, stats=False):
     x = torch.empty((P, pb.n_dot), dtype=torch.float64, device=V.device)
     fl = torch.empty(max(P, 1), dtype=torch.int32, device=V.device)
     st = Stats() if stats else None
-    _check(lib.qa_continuous_min(C.byref(pb), C.c_void_p(V.data_ptr()), P, C.c_void_p(x.data_ptr()),
-                                 C.c_void_p(fl.data_ptr()), C.byref(st) if st else None,
+    _check(lib.qa_continuous_min(C.byref(pb), V.data_ptr(), P, x.data_ptr(),
+                                 fl.data_ptr(), C.byref(st) if st else None,
                                  _stream(stream)))
     del keep
     return (x, fl[:P], st.as_dict()) if stats else (x, fl[:P])
@@ -288,8 +298,8 @@ def soft_charge(cdd, cgd, V, kT, closed=False, nhat=0, t=1.0, stream=None, stats
     nbar = torch.empty((P, pb.n_dot), dtype=torch.float64, device=V.device)
     saved = torch.empty(max(saved_bytes(P, pb.n_dot), 1), dtype=torch.uint8, device=V.device)
     st = Stats() if stats else None
-    _check(lib.qa_soft_charge(C.byref(pb), C.c_void_p(V.data_ptr()), P,
-                              C.c_void_p(nbar.data_ptr()), C.c_void_p(saved.data_ptr()),
+    _check(lib.qa_soft_charge(C.byref(pb), V.data_ptr(), P,
+                              nbar.data_ptr(), saved.data_ptr(),
                               C.byref(st) if st else None, _stream(stream)))
     del keep
     return (nbar, saved, st.as_dict()) if stats else (nbar, saved)
@@ -306,10 +316,10 @@ def soft_charge_backward(cdd, cgd, V, kT, grad_nbar, saved, closed=False, nhat=0
     dC = torch.empty((pb.n_dot, pb.n_dot), dtype=torch.float64, device=V.device)
     dG = torch.empty((pb.n_dot, pb.n_gate), dtype=torch.float64, device=V.device)
     dV = torch.empty_like(V) if want_V else None
-    _check(lib.qa_soft_charge_backward(C.byref(pb), C.c_void_p(V.data_ptr()), P,
-                                       C.c_void_p(g.data_ptr()), C.c_void_p(saved.data_ptr()),
-                                       C.c_void_p(dC.data_ptr()), C.c_void_p(dG.data_ptr()),
-                                       C.c_void_p(dV.data_ptr()) if dV is not None else None,
+    _check(lib.qa_soft_charge_backward(C.byref(pb), V.data_ptr(), P,
+                                       g.data_ptr(), saved.data_ptr(),
+                                       dC.data_ptr(), dG.data_ptr(),
+                                       dV.data_ptr() if dV is not None else None,
                                        _stream(stream)))
     del keep
     return dC, dG, dV
@@ -400,17 +410,17 @@ class Batch:
         lib = load()
         i64 = lambda a: a.ctypes.data_as(C.POINTER(C.c_int64))
         st = Stats() if stats else None
-        nbar = C.c_void_p(self.nbar.data_ptr()) if with_nbar else None
+        nbar = self.nbar.data_ptr() if with_nbar else None
         if self.grids is not None:
             _check(lib.qa_ground_state_batched_grid(
                 self.problems, len(self.diagrams), self.grids, i64(self.out_offsets),
-                C.c_void_p(self.n.data_ptr()), nbar, C.byref(st) if st else None,
+                self.n.data_ptr(), nbar, C.byref(st) if st else None,
                 _stream(stream)))
         else:
             _check(lib.qa_ground_state_batched(
-                self.problems, len(self.diagrams), C.c_void_p(self.V.data_ptr()),
+                self.problems, len(self.diagrams), self.V.data_ptr(),
                 i64(self.v_offsets), i64(self.pix_counts), i64(self.out_offsets),
-                C.c_void_p(self.n.data_ptr()), nbar, C.byref(st) if st else None,
+                self.n.data_ptr(), nbar, C.byref(st) if st else None,
                 _stream(stream)))
         return st.as_dict() if stats else None
 
@@ -469,11 +479,11 @@ def sensor_response(cdd, cgd, V, n_sensor, n_array=None, gamma=0.05, shape="lore
     if noise is not None:
         noise = torch.as_tensor(noise, dtype=torch.float64).to(V.device).contiguous()
     _check(lib.qa_sensor_response(
-        C.byref(pb), C.byref(sp), C.c_void_p(V.data_ptr()), P,
-        C.c_void_p(n_int.data_ptr()) if n_int is not None else None,
-        C.c_void_p(n_dbl.data_ptr()) if n_dbl is not None else None,
-        C.c_void_p(noise.data_ptr()) if noise is not None else None,
-        C.c_void_p(out.data_ptr()), _stream(stream)))
+        C.byref(pb), C.byref(sp), V.data_ptr(), P,
+        n_int.data_ptr() if n_int is not None else None,
+        n_dbl.data_ptr() if n_dbl is not None else None,
+        noise.data_ptr() if noise is not None else None,
+        out.data_ptr(), _stream(stream)))
     del keep
     return out
 
@@ -526,8 +536,8 @@ def time_kernels(cdd, cgd, V, out, reps, t=1.0, precision="fp64", exhaustive=Fal
                             FLAG_EXHAUSTIVE if exhaustive else 0)
     V = _device_V(V, pb.n_gate)
     ms = (C.c_double * 2)()
-    _check(load().qa_time_kernels(C.byref(pb), C.c_void_p(V.data_ptr()), V.shape[0],
-                                  C.c_void_p(out.data_ptr()), int(reps), ms, _stream(stream)))
+    _check(load().qa_time_kernels(C.byref(pb), V.data_ptr(), V.shape[0],
+                                  out.data_ptr(), int(reps), ms, _stream(stream)))
     del keep
     return ms[0], ms[1]
 
