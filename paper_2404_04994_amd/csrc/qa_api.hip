@@ -354,16 +354,16 @@ qa_status upload_diag(Workspace *w, const qa_problem *pb)
     return QA_OK;
 }
 
-qa_status grow_single(Workspace *w, int64_t P)
+qa_status grow_single(Workspace *w, int64_t P, int64_t records)
 {
     qa_status st;
     DiagRec *dr0 = w->dr;
     if ((st = grow(w, w->dr, w->dr_cap, 1))) return st;
     if (w->dr != dr0) w->dr_inputs.clear();
     if ((st = grow(w, w->rt, w->rt_cap, 1))) return st;
-    if ((st = grow(w, w->pr, w->pr_cap, P))) return st;
+    if ((st = grow(w, w->pr, w->pr_cap, records))) return st;
     // four counts per setup block; N = 16 has the most blocks
-    if ((st = grow(w, w->bstats, w->bstats_cap, 4 * setup_blocks(P, kMaxDot)))) return st;
+    if ((st = grow(w, w->bstats, w->bstats_cap, kBstatWords * setup_blocks(P, kMaxDot)))) return st;
     return QA_OK;
 }
 
@@ -375,7 +375,7 @@ int scorer_mode(const qa_problem *pb)
 }
 
 // Which T = 0 scorer a problem of P pixels takes.
-//   kTable       N <= 8: the whole-box table (FP64).
+//   kTable       N <= 8: the whole-box table (FP64), inside the setup kernel.
 //   kRows        N >= 9: FP64 rows in bound order, whatever precision is asked
 //                for (all four return the same states).
 //   kMatrixBound the split-BF16 matrix-core search in bound order, where it is
@@ -414,7 +414,7 @@ hipError_t launch_scorer(Scorer sc, const DiagRec *dr, const RowTab *rt, const P
                          hipStream_t s)
 {
     switch (sc) {
-    case Scorer::kTable: return launch_score_tab(dr, pr, P, n_out, counters, pb->n_dot, s);
+    case Scorer::kTable: return hipErrorInvalidValue;  // (in the setup kernel)
     case Scorer::kRows: return launch_rows_gs(rt, pr, P, scorer_mode(pb), n_out, counters, pb->n_dot, s);
     case Scorer::kFp64All: return launch_score_fp64(dr, pr, P, n_out, counters, pb->n_dot, s);
     default:
@@ -451,7 +451,7 @@ bool writes_row_tables(const qa_problem *pb, bool soft, int64_t P)
 // The device work of one single-diagram call on stream s, with the inputs
 // already in dr or in `in`: prologue, setup and QP in one kernel, then either the T = 0
 // scoring (n_out) or the softargmin (nbar, saved).  pr holds P pixel records,
-// bstats 4 * setup_blocks(P, n_dot) counts.  ev: optional stage events.
+// bstats kBstatWords * setup_blocks(P, n_dot) counts.  ev: optional stage events.
 qa_status enqueue_path(DiagRec *dr, RowTab *rt, PixRec *pr, int64_t *counters, int32_t *bstats,
                        hipStream_t s, const qa_problem *pb, const double *V, int64_t P, int32_t *n_out,
                        double *nbar, SavedRec *saved, std::array<hipEvent_t, 4> *ev,
@@ -463,13 +463,14 @@ qa_status enqueue_path(DiagRec *dr, RowTab *rt, PixRec *pr, int64_t *counters, i
     const bool mm = nbar && soft_mm_range(pb);
     const BoundSplit split = nbar ? kBoundNone : scorer_split(sc);
     QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed, split,
-                        mm || split == kBoundLow6 ? rt : nullptr, s, nullptr, nullptr, sweep, in));
+                        mm || split == kBoundLow6 ? rt : nullptr, s, nullptr, nullptr, sweep, in,
+                        !nbar && sc == Scorer::kTable ? n_out : nullptr));
     if (ev) QA_HIP(hipEventRecord((*ev)[1], s));
     if (mm)
         QA_HIP(launch_soft_mm(dr, rt, pr, P, nbar, saved, pb->n_dot, closed, s));
     else if (nbar)
         QA_HIP(launch_soft_fwd(dr, pr, P, nbar, saved, counters, pb->n_dot, s));
-    else
+    else if (sc != Scorer::kTable)
         QA_HIP(launch_scorer(sc, dr, rt, pr, counters, pb, P, n_out, s));
     if (ev) QA_HIP(hipEventRecord((*ev)[2], s));
     if (ev) QA_HIP(hipEventRecord((*ev)[3], s));
@@ -485,7 +486,8 @@ qa_status enqueue_single(Workspace *w, hipStream_t s, const qa_problem *pb, cons
     qa_status st = enqueue_path(w->dr, w->rt, w->pr, w->counters, w->bstats, s, pb, V, P, n_out, nbar,
                                 saved, ev, sweep, in);
     if (!st) {
-        w->dr_derived = true;
+        // (the kernel that scores as well leaves no tables)
+        w->dr_derived = nbar || pb->n_dot > 8;
         if (writes_row_tables(pb, nbar != nullptr, P)) w->rt_derived = true;
     }
     return st;
@@ -498,7 +500,8 @@ qa_status run_single(Workspace *w, const qa_problem *pb, const double *V, int64_
                      int32_t *n_out, double *nbar, SavedRec *saved, const VGrid *sweep = nullptr)
 {
     qa_status st;
-    if ((st = grow_single(w, P))) return st;
+    // (a scoring setup kernel, N <= 8 at T = 0, writes no pixel records)
+    if ((st = grow_single(w, P, nbar || pb->n_dot > 8 ? P : 1))) return st;
     w->bstats_used = setup_blocks(P, pb->n_dot);
     std::array<hipEvent_t, 4> *ev = timing_slot(w);
     if (ev || !g_graphs || sweep) {
@@ -556,7 +559,7 @@ qa_status read_stats(Workspace *w, qa_stats *stats)
     QA_HIP(hipMemcpyAsync(all.data(), w->counters, sizeof(int64_t) * kCounterWords,
                           hipMemcpyDeviceToHost, w->stream));
     QA_HIP(hipStreamSynchronize(w->stream));
-    std::vector<int32_t> blk(4 * w->bstats_used);
+    std::vector<int32_t> blk(kBstatWords * w->bstats_used);
     if (w->bstats_used)
         QA_HIP(hipMemcpyAsync(blk.data(), w->bstats, sizeof(int32_t) * blk.size(),
                               hipMemcpyDeviceToHost, w->stream));
@@ -565,9 +568,9 @@ qa_status read_stats(Workspace *w, qa_stats *stats)
     for (int slot = 0; slot < kCounterSlots; ++slot)
         for (int i = 0; i < C_NUM; ++i) c[i] += all[slot * C_NUM + i];
     // counts of the single-diagram setup kernel, per block
-    const int which[4] = {C_PIXELS, C_QP, C_DOUBLED, C_QP_FAIL};
+    const int which[kBstatWords] = {C_PIXELS, C_QP, C_DOUBLED, C_QP_FAIL, C_GAP_1E9, C_CANDIDATES};
     for (int64_t b = 0; b < w->bstats_used; ++b)
-        for (int k = 0; k < 4; ++k) c[which[k]] += blk[4 * b + k];
+        for (int k = 0; k < kBstatWords; ++k) c[which[k]] += blk[kBstatWords * b + k];
     stats->pixels = c[C_PIXELS];
     stats->qp_pixels = c[C_QP];
     stats->qp_failures = c[C_QP_FAIL];
@@ -649,7 +652,7 @@ constexpr size_t kScrDiag = 0;
 constexpr size_t kScrRows = kScrDiag + align256(sizeof(DiagRec));
 constexpr size_t kScrCounters = kScrRows + align256(sizeof(RowTab));
 constexpr size_t kScrBstats = kScrCounters + align256(sizeof(int64_t) * kCounterWords);
-constexpr int64_t kScrBstatsWords = 4 * setup_blocks_max(QA_NOALLOC_MAX_PIXELS);
+constexpr int64_t kScrBstatsWords = kBstatWords * setup_blocks_max(QA_NOALLOC_MAX_PIXELS);
 constexpr size_t kScrPix = kScrBstats + align256(sizeof(int32_t) * kScrBstatsWords);
 constexpr size_t kScratchBytes = kScrPix + sizeof(PixRec) * (size_t)QA_NOALLOC_MAX_PIXELS;
 }  // namespace
@@ -747,7 +750,7 @@ qa_status qa_ground_state_noalloc(const qa_problem *prob, const double *V_dev, i
                     (long long)P, QA_NOALLOC_MAX_PIXELS);
     if (P == 0) return QA_OK;
     if (!V_dev || !n_out_dev) return fail(QA_E_NULL, "V_dev or n_out_dev is NULL");
-    if (4 * setup_blocks(P, prob->n_dot) > kScrBstatsWords)
+    if (kBstatWords * setup_blocks(P, prob->n_dot) > kScrBstatsWords)
         return fail(QA_E_SHAPE, "P=%lld needs more setup blocks than the scratch counts",
                     (long long)P);
     unsigned char *base;
@@ -796,7 +799,7 @@ qa_status qa_continuous_min(const qa_problem *prob, const double *V_dev, int64_t
     if (!V_dev || !x_out_dev) return fail(QA_E_NULL, "V_dev or x_out_dev is NULL");
     Workspace *w;
     if ((st = get_ws((hipStream_t)hip_stream, &w))) return st;
-    if ((st = grow_single(w, P))) return st;
+    if ((st = grow_single(w, P, P))) return st;
     if ((st = upload_diag(w, prob))) return st;
     QA_HIP(launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
                         prob->mode == QA_CLOSED, kBoundNone, nullptr, w->stream, x_out_dev,
@@ -1160,7 +1163,7 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
     if (!V_dev || !n_out_dev || !ms_out) return fail(QA_E_NULL, "V_dev, n_out_dev or ms_out is NULL");
     Workspace *w;
     if ((st = get_ws((hipStream_t)hip_stream, &w))) return st;
-    if ((st = grow_single(w, P))) return st;
+    if ((st = grow_single(w, P, P))) return st;
     if ((st = upload_diag(w, prob))) return st;
     w->bstats_used = setup_blocks(P, prob->n_dot);
     const hipStream_t s = w->stream;
@@ -1174,20 +1177,22 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
         return r;
     };
     const Scorer sc = scorer_of(prob, P);
-    auto setup = [&]() {
+    int32_t *const scored = sc == Scorer::kTable ? n_out_dev : nullptr;
+    auto setup = [&](int32_t *n_out) {
         return launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
                             prob->mode == QA_CLOSED, scorer_split(sc),
-                            scorer_split(sc) == kBoundLow6 ? w->rt : nullptr, s) == hipSuccess;
+                            scorer_split(sc) == kBoundLow6 ? w->rt : nullptr, s, nullptr, nullptr,
+                            nullptr, nullptr, n_out) == hipSuccess;
     };
     // reps setup launches, then reps (setup, scorer) pairs: the scorer of a
     // pair reads what its setup has just written, as in a call
     if (hipEventRecord(ev[0], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
     for (int r = 0; r < reps; ++r)
-        if (!setup()) return done(fail(QA_E_DEVICE, "setup launch failed"));
+        if (!setup(nullptr)) return done(fail(QA_E_DEVICE, "setup launch failed"));
     if (hipEventRecord(ev[1], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
     for (int r = 0; r < reps; ++r) {
-        if (!setup()) return done(fail(QA_E_DEVICE, "setup launch failed"));
-        if (launch_scorer(sc, w->dr, w->rt, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
+        if (!setup(scored)) return done(fail(QA_E_DEVICE, "setup launch failed"));
+        if (!scored && launch_scorer(sc, w->dr, w->rt, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
             return done(fail(QA_E_DEVICE, "scorer launch failed"));
     }
     if (hipEventRecord(ev[2], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));

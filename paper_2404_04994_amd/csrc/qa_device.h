@@ -520,7 +520,8 @@ __device__ __forceinline__ void prep_tables_spread(DiagRec *dr, const double *M,
     const int nw = first >= 0 ? stride : gridDim.x * (blockDim.x / kWave);
     const int x = lane >> 3, y = lane & 7;
     const int nh = n - 8;
-    for (int e = gw; e < 256; e += nw) {
+    const int entries = n >= 8 ? 256 : 1 << n;
+    for (int e = gw; e < entries; e += nw) {
         const bool both = (e >> x & 1) && (e >> y & 1);
         double hl = 0.0, hh = 0.0, hs = 0.0, sa = 0.0;
         if (n >= 9) {

@@ -355,19 +355,22 @@ hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s
                        double *zero = nullptr, int64_t nzero = 0);
 // prologue (every block; block 0 also stores A and the tables into dr and
 // clears the kCounterWords counters) and setup of every pixel; the per-block
-// counts {pixels, QP, doubled, QP failures} go to bstats[4 * block] for
+// counts {pixels, QP, doubled, QP failures, gaps below 1e-9, candidates} go to
+// bstats[kBstatWords * block] for
 // setup_blocks(P, n_dot) blocks; split: the bound terms the scorer of this call
 // reads (kBoundNone for N <= 8); rt: receives the row tables (N >= 9, needed for
 // kBoundLow6) or NULL; x_out (P x N) / flags_out (P) are optional
 // copies of x*; grid, when given and on, replaces the voltages V; in: the inputs
 // (with the sweep) as arguments, stored into dr by the kernel, or NULL when dr
-// holds them.  P >= 1.
+// holds them; n_out (N <= 8): the kernel scores too and writes the ground states
+// there instead of the pixel records and dr's tables.  P >= 1.
+constexpr int kBstatWords = 6;
 int64_t setup_blocks(int64_t P, int n_dot);
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
                         int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
                         hipStream_t s, double *x_out = nullptr, int32_t *flags_out = nullptr,
                         const VGrid *grid = nullptr,
-                        const SetupIn *in = nullptr);
+                        const SetupIn *in = nullptr, int32_t *n_out = nullptr);
 // T = 0 argmin in FP64 over the candidate set of every pixel
 hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                              int64_t *counters, int n_dot, hipStream_t s);
@@ -376,8 +379,6 @@ hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int
 hipError_t launch_rows_gs(const RowTab *rt, const PixRec *pr, int64_t P, int mode, int32_t *n_out,
                           int64_t *counters, int n_dot, hipStream_t s);
 // the same in the table form (n_dot <= 8; the whole-box table from the setup)
-hipError_t launch_score_tab(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
-                            int64_t *counters, int n_dot, hipStream_t s);
 // matrix-core scorer at T = 0; mode 0: the dense box, 1: the sub-box of each
 // pixel's free dots (thresholded), 2: closed arrays (subsets of the free
 // dots with k raised); near ties re-scored in FP64 inside the kernel.  Every

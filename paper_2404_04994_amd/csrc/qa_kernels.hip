@@ -120,60 +120,121 @@ __device__ __forceinline__ uint32_t group_ballot(bool pred)
     return (uint32_t)((b >> sh) & ((1ull << NM) - 1ull));
 }
 
-// Group reductions: a group of 16 is a DPP row (row-local exchanges, no
-// LDS); smaller groups use shuffles.
+// Group reductions, inside a DPP row for every group size (exchanges with lane ^ 1,
+// lane ^ 2, then the mirror images within 8 and 16 lanes; no LDS).
+template <int NM, typename Op>
+__device__ __forceinline__ double group_fold(double v, Op &&op)
+{
+    if constexpr (NM >= 2) v = op(v, dppd<kDppXor1>(v));
+    if constexpr (NM >= 4) v = op(v, dppd<kDppXor2>(v));
+    if constexpr (NM >= 8) v = op(v, dppd<kDppHalfMirror>(v));
+    if constexpr (NM >= 16) v = op(v, dppd<kDppMirror>(v));
+    return v;
+}
+
 template <int NM>
 __device__ __forceinline__ int group_isum(int v)
 {
-    if constexpr (NM == 16) {
-        v += (int)dpp32<kDppXor1>((uint32_t)v);
-        v += (int)dpp32<kDppXor2>((uint32_t)v);
-        v += (int)dpp32<kDppHalfMirror>((uint32_t)v);
-        return v + (int)dpp32<kDppMirror>((uint32_t)v);
-    } else {
-#pragma unroll
-        for (int off = NM / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, NM);
-        return v;
-    }
+    if constexpr (NM >= 2) v += (int)dpp32<kDppXor1>((uint32_t)v);
+    if constexpr (NM >= 4) v += (int)dpp32<kDppXor2>((uint32_t)v);
+    if constexpr (NM >= 8) v += (int)dpp32<kDppHalfMirror>((uint32_t)v);
+    if constexpr (NM >= 16) v += (int)dpp32<kDppMirror>((uint32_t)v);
+    return v;
 }
 
 template <int NM>
 __device__ __forceinline__ double group_dsum(double v)
 {
-    if constexpr (NM == 16) {
-        return row_sum(v);
-    } else {
-#pragma unroll
-        for (int off = NM / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, NM);
-        return v;
-    }
+    return group_fold<NM>(v, [](double a, double b) { return a + b; });
 }
 
 template <int NM>
 __device__ __forceinline__ double group_dmax(double v)
 {
+    return group_fold<NM>(v, [](double a, double b) { return fmax(a, b); });
+}
+
+// z of lane Q of the caller's group, by DPP: a row broadcast (groups of 16), one per
+// half of the row (8), or a quad permutation
+template <int NM, int Q>
+__device__ __forceinline__ uint32_t group_bcast32(uint32_t z)
+{
     if constexpr (NM == 16) {
-        v = fmax(v, dppd<kDppXor1>(v));
-        v = fmax(v, dppd<kDppXor2>(v));
-        v = fmax(v, dppd<kDppHalfMirror>(v));
-        return fmax(v, dppd<kDppMirror>(v));
+        return dpp32<kDppRowBcast0 + Q>(z);
+    } else if constexpr (NM == 8) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)z, kDppRowBcast0 + Q, 0xf, 0x3, false);
+        return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)z, kDppRowBcast0 + 8 + Q, 0xf, 0xc,
+                                                     false);
+    } else if constexpr (NM == 4) {
+        return dpp32<Q * 0x55>(z);
     } else {
-#pragma unroll
-        for (int off = NM / 2; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, NM));
-        return v;
+        return dpp32<Q * 0x55 + 0xA0>(z);  // quad lanes Q, Q, 2 + Q, 2 + Q
     }
 }
-
-// z of lane Q of the caller's group (NM = 16: a DPP row broadcast)
 template <int NM, int Q>
-__device__ __forceinline__ double group_bcast(double z, int base)
+__device__ __forceinline__ double group_bcast(double z)
 {
-    if constexpr (NM == 16)
-        return dppd<kDppRowBcast0 + Q>(z);
-    else
-        return __shfl(z, base + Q, kWave);
+    const uint64_t u = (uint64_t)__double_as_longlong(z);
+    return __longlong_as_double(
+        (long long)((uint64_t)group_bcast32<NM, Q>((uint32_t)u) |
+                    ((uint64_t)group_bcast32<NM, Q>((uint32_t)(u >> 32)) << 32)));
 }
 
+// The smallest and second smallest energy of a pixel's candidates and the state of
+// the smallest one, for NM <= 8 dots by the pixel's NM lanes: lane `dot` takes the
+// states whose low dots (log2 NM of them) are its bits, the rest as a tree of partial
+// sums, U(n0 + 1_s) = ((u0 + sum of g0 in s) + h(s)).  A dot outside fm adds infinity
+// when raised; closed sets keep the states with k raised dots.
+// Within the setup kernel this takes the place of a scoring launch that read the
+// record of every pixel and the table back: 8 dots, 10^4 pixels, 7.7 + 10.4 us ->
+// 8.4 us; 2 dots, 899 pixels, 9.6 + 3.9 us -> 5.8 us (where the tables for later
+// kernels had been the longer part).  Instruction issue of the few waves bounds it.
+template <int NM, bool CLOSED>
+__device__ __forceinline__ void group_argmin(const double *__restrict__ sH, double g0, double u0,
+                                             uint32_t fm, int k, int dot, double &e1, double &e2,
+                                             uint32_t &s1)
+{
+    constexpr int LB = NM == 8 ? 3 : (NM == 4 ? 2 : 1), UB = NM - LB, NU = 1 << UB;
+    const double gm = (fm >> dot & 1u) ? g0 : INFINITY;
+    double lo = u0, val[NU];
+    static_for_dev<0, LB>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const double g = group_bcast<NM, i>(gm);
+        if (dot >> i & 1) lo += g;
+    });
+    val[0] = lo;
+    static_for_dev<0, UB>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        const double g = group_bcast<NM, LB + b>(gm);
+#pragma unroll
+        for (int q = 0; q < (1 << b); ++q) val[q | 1 << b] = val[q] + g;
+    });
+    const int kq = k - __popc((uint32_t)dot);
+    e1 = e2 = INFINITY;
+    s1 = 0;
+    // in the order of ties: dot 0 is the most significant
+    static_for_dev<0, NU>([&](auto rc) {
+        constexpr uint32_t r = (uint32_t)decltype(rc)::value;
+        constexpr uint32_t q = __builtin_bitreverse32(r) >> (32 - UB);
+        double e = val[q] + sH[dot + (int)(q << LB)];
+        if (CLOSED) e = kq == __builtin_popcount(q) ? e : INFINITY;
+        e2 = fmin(e2, fmax(e1, e));
+        s1 = e < e1 ? (uint32_t)dot + (q << LB) : s1;
+        e1 = fmin(e1, e);
+    });
+    const auto fold = [&](auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const double o1 = dppd<C>(e1), o2 = dppd<C>(e2);
+        const uint32_t os = dpp32<C>(s1);
+        const bool take = better(o1, os, e1, s1);
+        e2 = fmin(fmin(e2, o2), fmax(e1, o1));
+        e1 = fmin(e1, o1);
+        s1 = take ? os : s1;
+    };
+    fold(std::integral_constant<int, kDppXor1>{});
+    if constexpr (NM >= 4) fold(std::integral_constant<int, kDppXor2>{});
+    if constexpr (NM >= 8) fold(std::integral_constant<int, kDppHalfMirror>{});
+}
 
 // One Gauss-Jordan pivot on dot k of [K | x]: lane `dot` holds row `dot` in
 // r[] and its right-hand side in v; `base` is the group's first lane.
@@ -247,6 +308,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
                                                          int32_t *__restrict__ flags_out,
                                                          const int split,
                                                          RowTab *__restrict__ rt,
+                                                         int32_t *__restrict__ n_out,
                                                          const std::conditional_t<ARGS, SetupIn, VGrid> vg)
 {
     __shared__ double sCdd[kMaxDot * kMaxDot];  // C_dd (input)
@@ -259,7 +321,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     __shared__ double sLam[NM == 16 && CLOSED ? kSetupPixThreads : 1];
     __shared__ double sG[kMaxGate * NM];        // C_gd transposed: sG[j * NM + i]
     __shared__ double sV[ARGS ? 3 * kMaxGate : 1];  // a sweep's v0, e1, e2 (g each)
-    __shared__ int cnt[4];
+    __shared__ double sH[NM <= 8 ? 1 << NM : 1];  // 1/2 s^T A s (scoring)
+    __shared__ int cnt[kBstatWords];
     // Staging in one round trip: every load below is issued before any of
     // them is used.  C_gd (transposed, only the gates the diagram has) by
     // the first threads, C_dd by wave 0 (four entries per lane, the layout of
@@ -324,7 +387,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     }
     if constexpr (ARGS)
         if (vg.on && tid < 3 * g) sV[tid] = vg.v[tri + n * g + tid];
-    if (tid < 4) cnt[tid] = 0;
+    if (tid < kBstatWords) cnt[tid] = 0;
     if (!pixel_wave) {
         // wave 0 holds all of C_dd (lane 16 b + j: column j of rows
         // 4 b .. 4 b + 3): the input into LDS for the pixel waves' QP, C_dd 1
@@ -362,7 +425,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         prep_inverse_wave(m4, n, sA, red, sS, NM == 16 ? sS6 : nullptr);
         // a grid of at least 256 blocks: wave 0 of block b fills energy-table
         // entry b while the pixel waves finish (off the kernel's tail)
-        if (!(NM == 16 && rt) && gridDim.x >= 256) {
+        if (!(NM == 16 && rt) && !n_out && gridDim.x >= 256) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -500,13 +563,27 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             int rank = 0;
             static_for_dev<0, NM>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                const double fq = group_bcast<NM, q>(fr, base);
+                const double fq = group_bcast<NM, q>(fr);
                 rank += ((fm >> q & 1u) && (fq > fr || (fq == fr && q < dot))) ? 1 : 0;
             });
             gm = group_ballot<NM>(freed && rank < k);
         }
     }
     __syncthreads();  // A from wave 0
+    if (NM <= 8 && n_out) {
+        if (tid < 1 << NM) {
+            double h = 0.0;
+#pragma unroll
+            for (int x = 0; x < NM; ++x) {
+                double t = 0.5 * sA[x * kMaxDot + x];
+#pragma unroll
+                for (int y = 0; y < x; ++y) t += (tid >> y & 1) ? sA[x * kMaxDot + y] : 0.0;
+                h += (tid >> x & 1) ? t : 0.0;
+            }
+            sH[tid] = h;
+        }
+        __syncthreads();
+    }
 
     // the row kernels' tables, by the waves that have no pixels: one unit per
     // block while the pixel waves form their records (small grids: below)
@@ -526,7 +603,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         double g0 = 0.0;
         static_for_dev<0, NM>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
-            g0 += acol[q] * group_bcast<NM, q>(z, base);
+            g0 += acol[q] * group_bcast<NM, q>(z);
         });
         const double u0 = 0.5 * group_dsum<NM>(z * g0);
         // energy of the guess state n0 + b (b = the bits gm) relative to
@@ -584,7 +661,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             });
             static_for_dev<0, 10>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                sv += srow[q] * group_bcast<NM, (6 + q) & (NM - 1)>(zb, base);
+                sv += srow[q] * group_bcast<NM, (6 + q) & (NM - 1)>(zb);
             });
             sv = dot >= split ? sv : 0.0;
             Kb = 0.5 * group_dsum<NM>(zb * (sv - (g0 + lam_b)));
@@ -606,23 +683,40 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             }
         }
 
+        if (NM <= 8 && n_out) {
+            if constexpr (NM <= 8) {
+                double e1, e2;
+                uint32_t s1;
+                group_argmin<NM, CLOSED>(sH, g0, u0, fm, k, dot, e1, e2, s1);
+                if (p < P && is_dot) n_out[p * n + dot] = n0 + (int)(s1 >> dot & 1u);
+                if (p < P && dot == 0) {
+                    if (e2 - e1 < 1e-9) atomicAdd(&cnt[4], 1);
+                    const int m = __popc(fm);
+                    if (e1 < INFINITY) atomicAdd(&cnt[5], CLOSED ? (int)closed_states(m, k) : 1 << m);
+                }
+            }
+        }
         if (p < P) {
             PixRec *o = pr + p;
-            for (int q = dot; q < kMaxDot; q += NM) {
-                o->g0[q] = (q < NM) ? g0 : 0.0;
-                o->n0[q] = (int16_t)((q < NM) ? n0 : 0);
+            if (!(NM <= 8 && n_out)) {
+                for (int q = dot; q < kMaxDot; q += NM) {
+                    o->g0[q] = (q < NM) ? g0 : 0.0;
+                    o->n0[q] = (int16_t)((q < NM) ? n0 : 0);
+                }
+                if (NM == 16 && split != kBoundNone && dot >= split) o->s[dot - split] = (float)sv;
+                if (dot == 0) {
+                    o->K = (float)Kb;
+                    o->mu = (float)mu;
+                    o->eg = (float)eg;
+                    o->slack = slack;
+                    o->u0 = u0;
+                    o->free = fm;
+                    o->k = k;
+                    o->flags = flags | cflags;
+                    o->guess = gm;
+                }
             }
-            if (NM == 16 && split != kBoundNone && dot >= split) o->s[dot - split] = (float)sv;
             if (dot == 0) {
-                o->K = (float)Kb;
-                o->mu = (float)mu;
-                o->eg = (float)eg;
-                o->slack = slack;
-                o->u0 = u0;
-                o->free = fm;
-                o->k = k;
-                o->flags = flags | cflags;
-                o->guess = gm;
                 if (flags_out) flags_out[p] = flags | (cflags & 4);
                 if (cflags & 4) atomicAdd(&cnt[2], 1);
                 if (flags & 1) atomicAdd(&cnt[1], 1);
@@ -635,7 +729,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     // per-block counts with plain stores (the host sums them): the counters
     // of this call are cleared by block 0 concurrently, so no atomics here
     __syncthreads();
-    if (threadIdx.x < 4) bstats[blockIdx.x * 4 + threadIdx.x] = cnt[threadIdx.x];
+    if (tid < kBstatWords) bstats[blockIdx.x * kBstatWords + tid] = cnt[tid];
     // the diagram's record for the next kernels: block 0 stores A and the
     // sums and clears the call's counters; the table entries are spread
     // over the waves of the grid (small grids) or were filled by wave 0
@@ -667,7 +761,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         if (gridDim.x < kRowUnits)
             for (int u = blockIdx.x * kWaves + tid / kWave; u < kRowUnits; u += gridDim.x * kWaves)
                 prep_row_unit(rt, sA, sS6, n, u);
-    } else if (gridDim.x < 256) {
+    } else if (!n_out && gridDim.x < 256) {
         prep_tables_spread(dr, sA, sS, -1, 0, n);
     }
 }
@@ -690,13 +784,14 @@ int64_t setup_blocks(int64_t P, int n_dot)
 hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int64_t *counters,
                         int32_t *bstats, int n_dot, bool closed, BoundSplit split, RowTab *rt,
                         hipStream_t s, double *x_out, int32_t *flags_out, const VGrid *sweep,
-                        const SetupIn *in)
+                        const SetupIn *in, int32_t *n_out)
 {
     if (split == kBoundLow6 && (!rt || n_dot < 9)) return hipErrorInvalidValue;
+    if (n_out && n_dot > 8) return hipErrorInvalidValue;
     const dim3 grid((unsigned)setup_blocks(P, n_dot)), block(kSetupThreads);
     const auto go = [&](auto kernel, const auto &src) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, dr, V, P, pr, counters, bstats, x_out,
-                           flags_out, (int)split, rt, src);
+                           flags_out, (int)split, rt, n_out, src);
     };
     if (in) {
         if (closed) QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, true, true>, *in)));
@@ -1074,77 +1169,6 @@ __global__ __launch_bounds__(256) void k_soft_fwd_tab(const DiagRec *__restrict_
             }
         }
     }
-}
-
-// T = 0 argmin over the candidate set in the table form (n <= 8): the
-// candidate energies U(n0 + s) = U(n0) + g0 . s + h(s), h(s) = 1/2 s^T A s from
-// the whole-box table, CPL candidates per lane, groups of 2^LG lanes per
-// pixel; the same minimum, tie-break and runner-up as k_score_fp64.
-template <int LG, int NM, int CPL>
-__global__ __launch_bounds__(256) void k_score_tab(const DiagRec *__restrict__ dr,
-                                                   const PixRec *__restrict__ pr, int64_t P,
-                                                   int32_t *__restrict__ n_out,
-                                                   int64_t *__restrict__ counters)
-{
-    constexpr int G = 1 << LG;
-    __shared__ double sH[256];
-    __shared__ unsigned long long sc[2];
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) sH[i] = dr->hs[i];
-    if (threadIdx.x < 2) sc[threadIdx.x] = 0;
-    __syncthreads();
-    const int n = dr->n;
-    const int lane = threadIdx.x & (G - 1);
-    const int64_t gid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> LG;
-    const int64_t ngroups = ((int64_t)gridDim.x * blockDim.x) >> LG;
-    for (int64_t p = gid; p < P; p += ngroups) {
-        const PixRec *r = pr + p;
-        // g0: lane l of the group reads entry l mod NM, then broadcasts
-        // within the group (one read per lane instead of NM)
-        const double gl = r->g0[lane & (NM - 1)];
-        double g0[NM];
-        static_for_dev<0, NM>([&](auto ic) { g0[decltype(ic)::value] = lane_bcast<LG, decltype(ic)::value>(gl); });
-        double e[CPL];
-        uint32_t st[CPL];
-        tab_energies<LG, NM, CPL>(sH, g0, r->u0, r->free, r->k, lane, e, st);
-        double e1 = INFINITY, e2 = INFINITY;
-        uint32_t s1 = 0;
-        int scored = 0;
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            if (e[q] < INFINITY) ++scored;
-            if (better(e[q], st[q], e1, s1)) { e2 = e1; e1 = e[q]; s1 = st[q]; }
-            else if (e[q] < e2) e2 = e[q];
-        }
-#pragma unroll
-        for (int off = G / 2; off >= 1; off >>= 1) {
-            const double oe1 = __shfl_xor(e1, off, G);
-            const double oe2 = __shfl_xor(e2, off, G);
-            const uint32_t os1 = __shfl_xor(s1, off, G);
-            if (better(oe1, os1, e1, s1)) { e2 = fmin(e1, oe2); e1 = oe1; s1 = os1; }
-            else e2 = fmin(e2, oe1);
-        }
-        const int total = (int)group_sum<LG>((double)scored);
-        if (lane < n) n_out[p * n + lane] = (int32_t)r->n0[lane] + (int32_t)(s1 >> lane & 1u);
-        if (lane == 0) {
-            if (e2 - e1 < 1e-9) atomicAdd(&sc[0], 1ull);
-            atomicAdd(&sc[1], (unsigned long long)total);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        block_add_counter(counters, C_GAP_1E9, (int64_t)sc[0]);
-        block_add_counter(counters, C_CANDIDATES, (int64_t)sc[1]);
-    }
-}
-
-hipError_t launch_score_tab(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
-                            int64_t *counters, int n_dot, hipStream_t s)
-{
-    if (n_dot < 1 || n_dot > 8) return hipErrorInvalidValue;
-    QA_DISPATCH_TAB(n_dot, hipLaunchKernelGGL((k_score_tab<LG_, NM_, CPL_>),
-                                              dim3(group_blocks(P, LG_, 8192)), dim3(256), 0, s,
-                                              dr, pr, P, n_out, counters));
-    return hipGetLastError();
 }
 
 hipError_t launch_soft_fwd(const DiagRec *dr, const PixRec *pr, int64_t P, double *nbar,
