@@ -487,8 +487,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NM <= 8 ? 3 
     if (h.nx > 0) {
         const double *gv = mats + h.grid_off;
         const double *sc = gv + 3 * h.g;  // a0, da, a1, b0, db, b1
-        const double va = lin_point(p % h.nx, h.nx, sc[0], sc[1], sc[2]);
-        const double vb = lin_point(p / h.nx, h.ny, sc[3], sc[4], sc[5]);
+        const uint32_t nx = (uint32_t)h.nx, row = (uint32_t)p / nx;
+        const double va = lin_point((int32_t)((uint32_t)p - row * nx), (int32_t)nx, sc[0], sc[1], sc[2]);
+        const double vb = lin_point((int32_t)row, (int32_t)h.ny, sc[3], sc[4], sc[5]);
         for (int j = 0; j < h.g; ++j)
             add_gate(j, sweep_volt(gv[j], gv[h.g + j], gv[2 * h.g + j], va, vb));
     } else {

@@ -57,6 +57,10 @@ __device__ __forceinline__ void block_add_counter(int64_t *counters, int which, 
 // a valid source lane for every lane, so the move needs no "old" value: the
 // plain DPP move, not the update form, whose old operand costs a v_mov per
 // use.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+// lane i of every 16-lane row to the whole row
+constexpr int kDppRowBcast0 = 0x150;
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp32(uint32_t x)
 {
@@ -71,10 +75,64 @@ template <int CTRL>
 __device__ __forceinline__ double dppd(double x)
 {
     const uint64_t u = (uint64_t)__double_as_longlong(x);
-    const uint64_t r = (uint64_t)dpp32<CTRL>((uint32_t)u) |
-                       ((uint64_t)dpp32<CTRL>((uint32_t)(u >> 32)) << 32);
-    return __longlong_as_double((long long)r);
+    if constexpr (CTRL >= kDppRowBcast0 && CTRL < kDppRowBcast0 + 16) {
+        // (a row broadcast moves both halves at once)
+        return __longlong_as_double(
+            __builtin_amdgcn_mov_dpp((long long)u, CTRL, 0xF, 0xF, true));
+    } else {
+        const uint64_t r = (uint64_t)dpp32<CTRL>((uint32_t)u) |
+                           ((uint64_t)dpp32<CTRL>((uint32_t)(u >> 32)) << 32);
+        return __longlong_as_double((long long)r);
+    }
 }
+
+// acc + sum_q t_q x(lane q of the row), fused multiply-adds in increasing q, each with
+// the broadcast as its operand (5.7 cycles; a move and an fma take 10).  The leading
+// wait is what a lane exchange needs after x is written, which the compiler does not
+// see inside the block.
+__device__ __forceinline__ double row_dot16(double acc, double x, const double (&t)[16])
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
+        : "+v"(acc)
+        : "v"(x), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
+          "v"(t[7]), "v"(t[8]), "v"(t[9]), "v"(t[10]), "v"(t[11]), "v"(t[12]), "v"(t[13]),
+          "v"(t[14]), "v"(t[15]));
+    return acc;
+}
+// r_q += f r_q(lane K of the row), q < 8
+template <int K>
+__device__ __forceinline__ void row_axpy8(double *r, double f)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %4, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %5, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %6, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %7, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]),
+          "+v"(r[7])
+        : "v"(f), "n"(K));
+}
+
 // 1/a for the pivots of the eliminations: the hardware estimate refined by
 // two Newton steps r <- r + r (1 - a r) (each squares the relative error),
 // within an ulp of the rounded quotient for the normal, finite pivots of a
@@ -88,9 +146,6 @@ __device__ __forceinline__ double recip_nr(double a)
     e = fma(-a, r, 1.0);
     return fma(r, e, r);
 }
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-// lane i of every 16-lane row to the whole row
-constexpr int kDppRowBcast0 = 0x150;
 __device__ __forceinline__ float row_min(float x)
 {
     x = fminf(x, dppf<kDppXor1>(x));
@@ -271,7 +326,7 @@ struct VGrid {
 // start) / (num - 1), 0 for one point), as numpy's linspace forms it
 // (contraction into fused multiply-adds is off in both: each product and
 // sum is rounded on its own)
-__device__ __forceinline__ double lin_point(int64_t i, int64_t num, double start, double step,
+__device__ __forceinline__ double lin_point(int32_t i, int32_t num, double start, double step,
                                             double stop)
 {
 #pragma clang fp contract(off)
@@ -289,8 +344,10 @@ __device__ __forceinline__ double sweep_volt(double v0, double e1, double e2, do
 template <typename Grid>
 __device__ __forceinline__ void grid_ab(const Grid &G, int64_t p, double &a, double &b)
 {
-    a = lin_point(p % G.nx, G.nx, G.a0, G.da, G.a1);
-    b = lin_point(p / G.nx, G.ny, G.b0, G.db, G.b1);
+    // (a sweep has fewer than 2^31 pixels)
+    const uint32_t nx = (uint32_t)G.nx, row = (uint32_t)p / nx;
+    a = lin_point((int32_t)((uint32_t)p - row * nx), (int32_t)nx, G.a0, G.da, G.a1);
+    b = lin_point((int32_t)row, (int32_t)G.ny, G.b0, G.db, G.b1);
 }
 // gate k's voltage at sweep coordinates (a, b)
 __device__ __forceinline__ double grid_v(const VGrid &G, int k, double a, double b)

@@ -149,6 +149,16 @@ __device__ __forceinline__ double group_dsum(double v)
 }
 
 template <int NM>
+__device__ __forceinline__ float group_fsum(float v)
+{
+    if constexpr (NM >= 2) v += dppf<kDppXor1>(v);
+    if constexpr (NM >= 4) v += dppf<kDppXor2>(v);
+    if constexpr (NM >= 8) v += dppf<kDppHalfMirror>(v);
+    if constexpr (NM >= 16) v += dppf<kDppMirror>(v);
+    return v;
+}
+
+template <int NM>
 __device__ __forceinline__ double group_dmax(double v)
 {
     return group_fold<NM>(v, [](double a, double b) { return fmax(a, b); });
@@ -263,29 +273,21 @@ __device__ __forceinline__ void gj_pivot(double (&r)[NM], double &v, int k, int 
     }
 }
 
-// The same pivot with k fixed at compile time, for 16-lane groups (a DPP
-// row): the pivot row, right-hand side and pivot come by row broadcasts.
+// The same pivot with k fixed at compile time, for 16-lane groups (a DPP row): the
+// pivot row, right-hand side and pivot come by row broadcasts.  Groups without `take`
+// keep their rows (a zero factor).
 template <int NM, int K>
-__device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, int dot)
+__device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, int dot, bool take)
 {
     static_assert(NM == 16, "row broadcasts need 16-lane groups");
-    const double rik = r[K];
-    const double piv = dppd<kDppRowBcast0 + K>(rik);
-    double pr[NM];
+    const double rp = recip_nr(dppd<kDppRowBcast0 + K>(r[K]));
+    const bool own = dot == K;
+    const double f = take && !own ? -(r[K] * rp) : 0.0, scale = take && own ? rp : 1.0;
+    row_axpy8<K>(r, f);
+    row_axpy8<K>(r + 8, f);
+    v = fma(dppd<kDppRowBcast0 + K>(v), f, v) * scale;
 #pragma unroll
-    for (int q = 0; q < NM; ++q) pr[q] = dppd<kDppRowBcast0 + K>(r[q]);
-    const double pv = dppd<kDppRowBcast0 + K>(v);
-    const double rp = recip_nr(piv);
-    if (dot == K) {
-#pragma unroll
-        for (int q = 0; q < NM; ++q) r[q] = pr[q] * rp;
-        v = pv * rp;
-    } else {
-        const double f = rik * rp;
-#pragma unroll
-        for (int q = 0; q < NM; ++q) r[q] -= f * pr[q];
-        v -= f * pv;
-    }
+    for (int q = 0; q < NM; ++q) r[q] *= scale;
 }
 
 // The block is eight waves: wave 0 inverts C_dd (the diagram prologue, in
@@ -295,6 +297,13 @@ __device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, int dot
 // for the base-state gradient.  (Eight waves: two blocks fill a CU at four
 // waves per SIMD; four-wave blocks measured the same, five-wave blocks left
 // a fifth of the grid waiting for a second round.)
+//
+// From some 10^4 pixels on the issue of vector instructions bounds it (4 pixels a
+// wave of 16-lane groups, 5 cycles an instruction).  Row broadcasts as operands of
+// the multiply-adds (row_dot16, row_axpy8), the voltage of a gate formed by one lane
+// and a 32-bit division of the sweep's index: 16 dots, setup of 6*10^5 pixels
+// 289 -> 244 us open and 562 -> 446 us closed, of 10^4 pixels 9.5 -> 8.1 us open and
+// 19.1 -> 14.9 us closed.
 constexpr int kSetupThreads = kWave + kSetupPixThreads;
 static_assert(kSetupThreads >= kMaxDot * kMaxDot, "C_dd staging: one entry per thread");
 
@@ -383,7 +392,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
 #pragma unroll
     for (int r = 0; r < kGv; ++r) {
         const int e = tid + r * kSetupThreads;
-        if (e < g * NM) sG[e] = gv[r];
+        if (kGv * kSetupThreads == kMaxGate * NM || e < kMaxGate * NM) sG[e] = gv[r];
     }
     if constexpr (ARGS)
         if (vg.on && tid < 3 * g) sV[tid] = vg.v[tri + n * g + tid];
@@ -434,21 +443,30 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         __builtin_amdgcn_s_setprio(0);
     } else {
         // x_u = C_gd V (V read, or formed from the sweep)
-        if (vg.on) {
-            double a, b;
-            grid_ab(vg, pc, a, b);
-            for (int j = 0; j < g; ++j) {
-                double vj;
-                if constexpr (ARGS) vj = sweep_volt(sV[j], sV[g + j], sV[2 * g + j], a, b);
-                else vj = grid_v(vg, j, a, b);
-                xu += sG[j * NM + dot] * vj;
+        double a = 0.0, b = 0.0;
+        if (vg.on) grid_ab(vg, pc, a, b);
+        const auto volt = [&](int j) {
+            if constexpr (ARGS) return sweep_volt(sV[j], sV[g + j], sV[2 * g + j], a, b);
+            else return grid_v(vg, j, a, b);
+        };
+        if constexpr (NM == 16) {
+            // V_j from lane j of the group (prefetched before the barrier, or
+            // formed by it); C_gd is zero past the last gate
+            if (vg.on) {
+                if (dot < g) v0 = volt(dot);
+                if (16 + dot < g) v1 = volt(16 + dot);
             }
-        } else if constexpr (NM == 16) {
-            // V_j from lane j of the group (prefetched before the barrier)
-            static_for_dev<0, kMaxGate>([&](auto jc) {
-                constexpr int j = decltype(jc)::value;
-                if (j < g) xu += sG[j * NM + dot] * dppd<kDppRowBcast0 + (j & 15)>(j < 16 ? v0 : v1);
-            });
+            double col[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) col[j] = sG[j * NM + dot];
+            xu = row_dot16(0.0, v0, col);
+            if (g > 16) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) col[j] = sG[(16 + j) * NM + dot];
+                xu = row_dot16(xu, v1, col);
+            }
+        } else if (vg.on) {
+            for (int j = 0; j < g; ++j) xu += sG[j * NM + dot] * volt(j);
         } else {
             for (int j = 0; j < g; ++j) xu += sG[j * NM + dot] * V[pc * g + j];
         }
@@ -500,8 +518,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
                     const uint32_t todo = W & ~done;
                     static_for_dev<0, NM>([&](auto kc) {
                         constexpr int kp = decltype(kc)::value;
-                        if (__ballot(todo >> kp & 1u) && (todo >> kp & 1u))
-                            gj_pivot_row<NM, kp>(r, v, dot);
+                        if (__ballot(todo >> kp & 1u))
+                            gj_pivot_row<NM, kp>(r, v, dot, todo >> kp & 1u);
                     });
                 } else {
                     for (uint32_t todo = W & ~done; todo; todo &= todo - 1)
@@ -601,10 +619,14 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         });
         const double aii = sA[dot * kMaxDot + dot];
         double g0 = 0.0;
-        static_for_dev<0, NM>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            g0 += acol[q] * group_bcast<NM, q>(z);
-        });
+        if constexpr (NM == 16) {
+            g0 = row_dot16(0.0, z, acol);
+        } else {
+            static_for_dev<0, NM>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                g0 += acol[q] * group_bcast<NM, q>(z);
+            });
+        }
         const double u0 = 0.5 * group_dsum<NM>(z * g0);
         // energy of the guess state n0 + b (b = the bits gm) relative to
         // U(n0): b^T g0 + 1/2 b^T A b, with (A b)_dot the sum of the columns
@@ -612,10 +634,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         double eg = 0.0;
         if (NM == 16 && split != kBoundNone) {
             double ab = 0.0;
-            static_for_dev<0, NM>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                ab += (gm >> q & 1u) ? acol[q] : 0.0;
-            });
+            if constexpr (NM == 16) ab = row_dot16(0.0, (gm >> dot & 1u) ? 1.0 : 0.0, acol);
             eg = group_dsum<NM>((gm >> dot & 1u) ? g0 + 0.5 * ab : 0.0);
             if (!CLOSED) {
                 // Open arrays: the rounding of x* takes the best single flip
@@ -654,15 +673,12 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             const int hd = dot >= split ? dot : split;
             const double zb = is_dot ? (double)n0 - (kkt ? x : xu) : 0.0;
             const double mult = sMult[tp], lam_b = CLOSED ? sLam[tp] : 0.0;
-            double srow[10];
-            static_for_dev<0, 10>([&](auto qc) {
+            double srow[16];
+            static_for_dev<0, 16>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                srow[q] = (q >= 2 || split == kBoundLow6) ? Sm[hd * kMaxDot + 6 + q] : 0.0;
+                srow[q] = q >= (split == kBoundLow6 ? 6 : 8) ? Sm[hd * kMaxDot + q] : 0.0;
             });
-            static_for_dev<0, 10>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                sv += srow[q] * group_bcast<NM, (6 + q) & (NM - 1)>(zb);
-            });
+            if constexpr (NM == 16) sv = row_dot16(0.0, zb, srow);
             sv = dot >= split ? sv : 0.0;
             Kb = 0.5 * group_dsum<NM>(zb * (sv - (g0 + lam_b)));
             sv += mult;
@@ -672,7 +688,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             // the kernel adds with the closed term), the rounding of eg, the
             // FP64 rounding of the terms above, and 2e-9, so that every state
             // within 1e-9 of the minimum lies in a computed row.
-            slack = 0x1p-19f * (fabsf((float)Kb) + (float)group_dsum<NM>(fabs(sv))) +
+            slack = 0x1p-19f * (fabsf((float)Kb) + group_fsum<NM>(fabsf((float)sv))) +
                     0x1p-22f * fabsf((float)eg) + 0x1p-36f * fabsf((float)u0) + 2e-9f;
             if (CLOSED) {
                 double qrow = 0.0;
