@@ -275,19 +275,21 @@ __device__ __forceinline__ void gj_pivot(double (&r)[NM], double &v, int k, int 
 
 // The same pivot with k fixed at compile time, for 16-lane groups (a DPP row): the
 // pivot row, right-hand side and pivot come by row broadcasts.  Groups without `take`
-// keep their rows (a zero factor).
+// keep their rows (a zero factor).  The pivot row itself stays as it is: the later
+// pivots act on it by multiples, and its own column is zero in all other rows, so
+// its solution is v times the pivot's reciprocal, which `rpiv` keeps.
 template <int NM, int K>
-__device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, int dot, bool take)
+__device__ __forceinline__ void gj_pivot_row(double (&r)[NM], double &v, double &rpiv, int dot,
+                                             bool take)
 {
     static_assert(NM == 16, "row broadcasts need 16-lane groups");
     const double rp = recip_nr(dppd<kDppRowBcast0 + K>(r[K]));
     const bool own = dot == K;
-    const double f = take && !own ? -(r[K] * rp) : 0.0, scale = take && own ? rp : 1.0;
+    const double f = take && !own ? -(r[K] * rp) : 0.0;
+    rpiv = take && own ? rp : rpiv;
     row_axpy8<K>(r, f);
     row_axpy8<K>(r + 8, f);
-    v = fma(dppd<kDppRowBcast0 + K>(v), f, v) * scale;
-#pragma unroll
-    for (int q = 0; q < NM; ++q) r[q] *= scale;
+    v = fma(dppd<kDppRowBcast0 + K>(v), f, v);
 }
 
 // The block is eight waves: wave 0 inverts C_dd (the diagram prologue, in
@@ -492,9 +494,10 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
         if (W) {
             const double tol = 1e-13 * group_dmax<NM>(fmax(1.0, fabs(xu)));
             const double rone_c = CLOSED ? 1.0 / one_c : 0.0;
-            double r[NM], v = x0;
+            double r[NM], v = x0, rpiv = 1.0;
             uint32_t done = 0;
             bool settled = false;
+            double mu = 0.0;  // on the active set: the multiplier
             for (int round = 0; round < 4 * NM + 4; ++round) {
                 if (done == 0) {
                     // row `dot` of K (symmetric), identity beyond n, read
@@ -519,7 +522,7 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
                     static_for_dev<0, NM>([&](auto kc) {
                         constexpr int kp = decltype(kc)::value;
                         if (__ballot(todo >> kp & 1u))
-                            gj_pivot_row<NM, kp>(r, v, dot, todo >> kp & 1u);
+                            gj_pivot_row<NM, kp>(r, v, rpiv, dot, todo >> kp & 1u);
                     });
                 } else {
                     for (uint32_t todo = W & ~done; todo; todo &= todo - 1)
@@ -528,7 +531,9 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
                 done = W;
                 const bool in_w = W >> dot & 1u;
                 x = in_w ? 0.0 : v;
-                const bool keep = is_dot && (in_w ? (-v > -tol) : (v < -tol));
+                if (NM == 16) mu = in_w ? -v * rpiv : 0.0;
+                else mu = -v;
+                const bool keep = is_dot && (in_w ? (mu > -tol) : (v < -tol));
                 const uint32_t Wn = group_ballot<NM>(keep);
                 if (Wn == W) { settled = true; break; }
                 if (W & ~Wn) done = 0;  // a dot leaves the active set: eliminate afresh
@@ -537,8 +542,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             x = is_dot ? fmax(x, 0.0) : 0.0;
             flags = settled ? 1 : 3;
             if (NM == 16 && split != kBoundNone) {
-                // on the active set v holds -mu; x = x_u + C mu + lam C 1
-                const double mult = (settled && (W >> dot & 1u)) ? fmax(-v, 0.0) : 0.0;
+                // x = x_u + C mu + lam C 1
+                const double mult = (settled && (W >> dot & 1u)) ? fmax(mu, 0.0) : 0.0;
                 kkt = settled;
                 sMult[tp] = mult;
                 if (CLOSED)
