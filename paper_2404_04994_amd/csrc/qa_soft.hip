@@ -548,9 +548,10 @@ hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr,
 // one more matrix product with the pixels as inner dimension, kept in registers
 // (wave w: 16 low states by 64 middle states).  The outer products of dL/dA and
 // dL/dC_gd run over the pixels the same way.  Against the walk over the
-// candidates, 12 dots and 4096 pixels: 337 -> 36 us.  That is one set of pixels a
-// block: a serial chain through eight barriers at one or two waves a SIMD, where the
-// products alone would take 5 us.
+// candidates, 12 dots and 4096 pixels: 337 -> 28 us.  That is one set of pixels a
+// block: a serial chain through eight barriers at one wave a SIMD, where the products
+// alone would take 5 us.  (The pair sums at the end had taken 8 us of 36 as a loop
+// that waited for each read.)
 // ---------------------------------------------------------------------------
 template <bool CLOSED>
 struct BwdLds {
@@ -901,14 +902,22 @@ __global__ __launch_bounds__(kSoftThreads, 2) void k_soft_mm_bwd(
     for (int e = tid; e < n * n; e += kSoftThreads) {
         const int i = e / n, j = e % n;
         const int lo = i < j ? i : j, hi = i < j ? j : i;
+        // the states with both dots raised: of the low states' sums (all, or those with
+        // the middle dot hi), or of the middle states' sums
+        const int need = hi < 6 ? 1 << lo | 1 << hi : (lo < 6 ? 1 << lo : 1 << (lo - 6) | 1 << (hi - 6));
+        const double *low = &sh.S.low[hi < 6 ? 0 : (lo < 6 ? hi - 5 : 0)][0];
         double v = 0.0;
-        for (int s = 0; s < 64; ++s) {
-            if (hi < 6) {
-                if ((s >> lo & 1) && (s >> hi & 1)) v += sh.S.low[0][s];
-            } else if (lo < 6) {
-                if (s >> lo & 1) v += sh.S.low[hi - 5][s];
-            } else if ((s >> (lo - 6) & 1) && (s >> (hi - 6) & 1)) {
-                v += (sh.S.mid[0][s] + sh.S.mid[1][s]) + (sh.S.mid[2][s] + sh.S.mid[3][s]);
+        if (lo < 6) {
+#pragma unroll 16
+            for (int s = 0; s < 64; ++s) {
+                const double x = low[s];
+                v += (s & need) == need ? x : 0.0;
+            }
+        } else {
+#pragma unroll 16
+            for (int s = 0; s < 64; ++s) {
+                const double x = (sh.S.mid[0][s] + sh.S.mid[1][s]) + (sh.S.mid[2][s] + sh.S.mid[3][s]);
+                v += (s & need) == need ? x : 0.0;
             }
         }
         v = 0.5 * (sA[i * kMaxDot + j] + sA[j * kMaxDot + i]) + 0.5 * v;
