@@ -548,7 +548,7 @@ hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr,
 // one more matrix product with the pixels as inner dimension, kept in registers
 // (wave w: 16 low states by 64 middle states).  The outer products of dL/dA and
 // dL/dC_gd run over the pixels the same way.  Against the walk over the
-// candidates, 12 dots and 4096 pixels: 337 -> 28 us.  That is one set of pixels a
+// candidates, 12 dots and 4096 pixels: 337 -> 25 us.  That is one set of pixels a
 // block: a serial chain through eight barriers at one wave a SIMD, where the products
 // alone would take 5 us.  (The pair sums at the end had taken 8 us of 36 as a loop
 // that waited for each read.)
@@ -655,15 +655,21 @@ __global__ __launch_bounds__(kSoftThreads, 2) void k_soft_mm_bwd(
         asm volatile("" ::: "memory");
         // x_u = C_gd V by lane = dot
         double xu = 0.0;
-        static_for_dev<0, kMaxGate>([&](auto jc) {
+        // (C_gd and the voltages are zero past the last gate, z and m past the last dot)
+        static_for_dev<0, 16>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            if (j < g) xu += sCt[j * kMaxDot + d] * dppd<kDppRowBcast0 + (j & 15)>(j < 16 ? in.v0 : in.v1);
+            xu += sCt[j * kMaxDot + d] * dppd<kDppRowBcast0 + j>(in.v0);
         });
+        if (g > 16)
+            static_for_dev<0, 16>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                xu += sCt[(16 + j) * kMaxDot + d] * dppd<kDppRowBcast0 + j>(in.v1);
+            });
         const double z = d < n ? (double)in.n0 - xu : 0.0;
         double g0 = 0.0;
         static_for_dev<0, kMaxDot>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
-            if (j < n) g0 += sA[j * kMaxDot + d] * dppd<kDppRowBcast0 + j>(z);
+            g0 += sA[j * kMaxDot + d] * dppd<kDppRowBcast0 + j>(z);
         });
         const double gnb = row_sum(in.gb * in.nb);
         __syncthreads();  // the last batch's products have read the buffers
@@ -761,11 +767,11 @@ __global__ __launch_bounds__(kSoftThreads, 2) void k_soft_mm_bwd(
             const double Z = (L.pz[0][pix] + L.pz[1][pix]) + (L.pz[2][pix] + L.pz[3][pix]);
             const double iz = real ? 1.0 / Z : 0.0;
             const double md =
-                d < 12 ? -(ikT * iz) * soft_dot_sum(L.part, d >= 6 ? 1 : 0, d >= 6 ? d - 6 : d, pix) : 0.0;
+                d < n ? -(ikT * iz) * soft_dot_sum(L.part, d >= 6 ? 1 : 0, d >= 6 ? d - 6 : d, pix) : 0.0;
             double dx = 0.0;
             static_for_dev<0, 12>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
-                if (j < n) dx -= sA[j * kMaxDot + d] * dppd<kDppRowBcast0 + j>(md);
+                dx -= sA[j * kMaxDot + d] * dppd<kDppRowBcast0 + j>(md);
             });
             double gv0 = 0.0, gv1 = 0.0;
             static_for_dev<0, 12>([&](auto jc) {
@@ -778,7 +784,7 @@ __global__ __launch_bounds__(kSoftThreads, 2) void k_soft_mm_bwd(
                 if (d < g) gradV[p * g + d] = gv0;
                 if (16 + d < g) gradV[p * g + 16 + d] = gv1;
             }
-            L.m[pix][d] = d < n ? md : 0.0;
+            L.m[pix][d] = md;
             L.dx[pix][d] = d < n ? dx : 0.0;
             if (d == 0) L.iz[pix] = iz;
         }
