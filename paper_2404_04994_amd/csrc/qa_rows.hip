@@ -233,6 +233,37 @@ struct RowPixel {
         return kset;
     }
 
+    // The smallest energy of the row with the lowest bound (kBarred when there is none)
+    // of a dense box.  A bound that is not a number is never the lowest.
+    __device__ __forceinline__ double lowest(const PixRec *r, const RowConst &c, const RowLds &t,
+                                             int n) const
+    {
+        const int lane = threadIdx.x & 63;
+        float best = 0x1p120f;
+        int at = 0;
+#pragma unroll 1
+        for (int kk = 0; kk < 1 << (n > 12 ? n - 12 : 0); ++kk) {
+            float L = sl + t.hs[kk][lane];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (kk >> j & 1) L += r->s[6 + j];
+            if ((ok >> lane & 1u) && L < best) { best = L; at = kk; }
+        }
+        float low = best;
+        for (int off = 32; off >= 1; off >>= 1) low = fminf(low, __shfl_xor(low, off));
+        const unsigned long long hit = __ballot(best == low && best < 0x1p120f);
+        if (!hit) return kBarred;
+        const int c6 = __builtin_ctzll(hit), kk = __builtin_amdgcn_readlane(at, c6);
+        double base = lg, rc = ch + readlane_d(c.hk, kk);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (kk >> j & 1) {
+                base += t.lo[j][lane];
+                rc += t.hi[j][lane] + r->g0[12 + j];
+            }
+        return wave_min_d((base + readlane_d(rc, c6)) + t.T[c6][lane]);
+    }
+
     // the energies of those rows (relative to U(n0); kBarred outside a closed set,
     // above 2^99 where a fixed dot is raised): f(row, energy of the lane's state)
     template <typename F>
@@ -290,6 +321,30 @@ __device__ __forceinline__ void row_priority(uint32_t mlo, uint32_t mhi, bool mo
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// rows in the masks of rows(), held by lanes 0..15
+__device__ __forceinline__ int row_count(uint32_t mlo, uint32_t mhi)
+{
+    int v = __popc(mlo) + __popc(mhi);
+    v += (int)dpp32<kDppXor1>((uint32_t)v);
+    v += (int)dpp32<kDppXor2>((uint32_t)v);
+    v += (int)dpp32<kDppHalfMirror>((uint32_t)v);
+    v += (int)dpp32<kDppMirror>((uint32_t)v);
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// From this many rows on, the row with the lowest bound is computed first, and the
+// rows are chosen again by its minimum if that is below the guess: some 250
+// instructions, a row is 12.  On arrays the kernel's tail are pixels with a poor guess:
+// over 1500 pixels of a 16-dot array up to 686 rows by the guess, 84 by this row and
+// 68 by the minimum itself (random capacitances: 231, 231 and 218, the bound is loose).
+// The form with this step (TAIL) is for dense boxes of up to kTailPixels, where the
+// kernel ends with such pixels: calls of 10^4 pixels on three arrays 24.3, 36.3 and
+// 37.5 us without it, 24.4, 28.9 and 30.1 us with it; of 6*10^5 pixels, where all
+// pixels' instructions count, 634, 742 and 785 us without, 671, 769 and 812 us with it.
+// Thresholded sets: 17.5, 16.8, 22.0 us without, 18.0, 17.2, 21.4 us with it.
+constexpr int kManyRows = 64;
+constexpr int64_t kTailPixels = 50000;
+
 // T = 0 argmin (Eq. argmin) over each pixel's candidate set: a wave per pixel,
 // one lane per low state, over the rows the bound leaves.  Each lane keeps its
 // two smallest energies with the row in the low ten bits of the mantissa (an
@@ -297,7 +352,7 @@ __device__ __forceinline__ void row_priority(uint32_t mlo, uint32_t mhi, bool mo
 // within 1e-9 is counted, and then the rows are taken once more with the
 // energies as they are: the smallest, ties to the lexicographically smallest
 // state.
-template <int MODE>
+template <int MODE, bool TAIL>
 __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_rows_gs(const RowTab *__restrict__ rt,
                                                             const PixRec *__restrict__ pr, int64_t P,
                                                             int32_t *__restrict__ n_out, int n,
@@ -335,7 +390,21 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         if (MODE == kModePruned) ncand += 1ll << __popc(px.free & ((1u << n) - 1u));
         if (CLOSED) ncand += closed_states(__popc(px.free & ((1u << n) - 1u)), px.k);
         uint32_t mlo, mhi;
-        const uint32_t kset = px.rows(r, T, n, r->eg + px.slack, inv2g, wb, mlo, mhi);
+        uint32_t kset;
+        if constexpr (!TAIL) {
+            kset = px.rows(r, T, n, r->eg + px.slack, inv2g, wb, mlo, mhi);
+        } else {
+            float thr = r->eg + px.slack;
+#pragma unroll 1
+            for (bool again = true;; again = false) {
+                kset = px.rows(r, T, n, thr, inv2g, wb, mlo, mhi);
+                if (!again || row_count(mlo, mhi) < kManyRows) break;
+                const float e = (float)px.lowest(r, c, T, n);
+                nrows += lane == 0;
+                if (!(e < r->eg)) break;
+                thr = e + px.slack + 0x1p-22f * fabsf(e);
+            }
+        }
         nrows += __popc(mlo) + __popc(mhi);  // (a lane's share: summed at the end)
         row_priority(mlo, mhi, p + nwaves < P);
         double m1 = kBarred, m2 = kBarred;
@@ -410,16 +479,18 @@ hipError_t launch_rows_gs(const RowTab *rt, const PixRec *pr, int64_t P, int mod
     if (n_dot < 9 || n_dot > kMaxDot || mode < kModeDense || mode > kModeClosed)
         return hipErrorInvalidValue;
     if (P <= 0) return hipSuccess;
-    static int cache[3][64];
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)row_blocks(kernel, cache[mode], P)),
+    static int cache[4][64];
+    auto go = [&](auto kernel, int slot) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)row_blocks(kernel, cache[slot], P)),
                            dim3(kRowThreads), 0, s, rt, pr, P, n_out, n_dot,
                            counters);
         return hipGetLastError();
     };
-    if (mode == kModeDense) return go(k_rows_gs<kModeDense>);
-    if (mode == kModePruned) return go(k_rows_gs<kModePruned>);
-    return go(k_rows_gs<kModeClosed>);
+    if (mode == kModeDense)
+        return P <= kTailPixels ? go(k_rows_gs<kModeDense, true>, 3)
+                                : go(k_rows_gs<kModeDense, false>, mode);
+    if (mode == kModePruned) return go(k_rows_gs<kModePruned, false>, mode);
+    return go(k_rows_gs<kModeClosed, false>, mode);
 }
 
 }  // namespace qa

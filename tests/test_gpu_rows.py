@@ -90,3 +90,21 @@ def test_rows_extreme_voltages(qa):
     ne = qa.ground_state(cdd, cgd, Vd, exhaustive=True).cpu().numpy()
     keep = [0, 3, 7, 8, 9, 10, 11]
     assert (n[keep] == ne[keep]).all()
+
+
+@pytest.mark.parametrize("n_dot,seed", [(9, 12), (13, 12), (16, 12), (16, 11), (16, 200)])
+def test_pixels_of_many_rows(qa, n_dot, seed):
+    """Arrays whose rounded minimum is a poor guess at some pixels (hundreds of rows):
+    the same states as computing every energy, for a call that looks for a better
+    guess there and for one past its pixel count."""
+    d = W.grid4x4(seed, npix=2)
+    cdd, cgd = d.cdd[:n_dot, :n_dot].copy(), d.cgd[:n_dot, :n_dot].copy()
+    V = np.random.default_rng(seed).uniform(-2.0, 8.0, (3000, n_dot))
+    Vt = torch.as_tensor(V).cuda()
+    few, st = qa.ground_state(cdd, cgd, Vt, stats=True)
+    every, se = qa.ground_state(cdd, cgd, Vt, stats=True, exhaustive=True)
+    many = qa.ground_state(cdd, cgd, Vt.repeat(17, 1))
+    assert st["fp64_gap_below_1e9"] == se["fp64_gap_below_1e9"] == 0
+    assert torch.equal(few, every)
+    assert torch.equal(many, few.repeat(17, 1))
+    assert st["scored"] <= se["scored"] == 3000 << n_dot
