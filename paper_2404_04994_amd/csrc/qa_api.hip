@@ -380,12 +380,13 @@ int scorer_mode(const qa_problem *pb)
 //                for (all four return the same states).
 //   kMatrixBound the split-BF16 matrix-core search in bound order, where it is
 //                the faster one: dense boxes of 16 dots and few pixels, when the
-//                caller asks for it.  Scorer and setup, BF16x3 / rows, 16 dots:
-//                4x4 array 23.3 / 24.1 us at 10^4 pixels, 32.9 / 32.5 at
-//                1.6*10^4, 264 / 216 at 2*10^5; random capacitances 32.7 / 38.1,
-//                40.7 / 46.2, 319 / 296 (13 dots: 29.0 / 25.7 at 10^4).  Closed
-//                and thresholded sets and the FP32 form measured slower than
-//                rows everywhere (16 dots, 10^4: closed 52.6 / 48.7, t = 1/2
+//                caller asks for it.  Scorer and setup, BF16x3 / rows, us, 16
+//                dots: 4x4 array 21.5 / 23.4 at 10^4 pixels, 30.2 / 30.6 at
+//                1.6*10^4; random capacitances 28.3 / 39.9, 35.9 / 47.1.  At
+//                2*10^5 (both with a setup some 40 us slower than now) 264 / 216
+//                and 319 / 296; 13 dots 29.0 / 25.7 at 10^4.  Closed and
+//                thresholded sets and the FP32 form measured slower than rows
+//                everywhere (16 dots, 10^4: closed 52.6 / 48.7, t = 1/2
 //                23.2 / 19.8, FP32 dense 32.1 / 24.1; 12 dots 26.7 / 18.7).
 //   kMatrixAll, kFp64All  every energy of the set (QA_FLAG_EXHAUSTIVE).
 enum class Scorer { kTable, kRows, kMatrixBound, kMatrixAll, kFp64All };
