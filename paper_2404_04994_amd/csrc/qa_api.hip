@@ -66,10 +66,10 @@ struct Workspace {
     std::vector<std::array<hipEvent_t, 4>> ev;
     int64_t ev_used = 0;
     // ragged batch
-    BatchHdr *bhdr = nullptr;
-    int64_t bhdr_cap = 0;
-    double *bmats = nullptr;
-    int64_t bmats_cap = 0;
+    double *bplan = nullptr;  // the batch plan on the device: headers, then matrices
+    int64_t bplan_cap = 0;
+    BatchHdr *bhdr = nullptr;  // in bplan
+    double *bmats = nullptr;   // in bplan
     int32_t *parity = nullptr;  // of the telegraph flips (sensor response)
     int64_t parity_cap = 0;
     DiagRec *brecs = nullptr;
@@ -82,7 +82,7 @@ struct Workspace {
     size_t bstage_cap[2] = {};
     hipEvent_t bstage_ev[2] = {};
     int bstage_next = 0;
-    std::vector<unsigned char> bplan_inputs;  // the plan last copied to bhdr / bmats
+    std::vector<unsigned char> bplan_inputs;  // the plan last copied to bplan
     hipStream_t cap_stream = nullptr;   // private stream used for graph capture
     hipGraphExec_t graph = nullptr;
     std::vector<int64_t> graph_key;
@@ -950,14 +950,14 @@ void plan_batch(const qa_problem *probs, int32_t n_diag, const int64_t *v_offset
 qa_status upload_plan(Workspace *w, const BatchPlan &plan, int32_t n_diag)
 {
     qa_status st;
-    const BatchHdr *h0 = w->bhdr;
-    const double *m0 = w->bmats;
-    if ((st = grow(w, w->bhdr, w->bhdr_cap, n_diag))) return st;
-    if ((st = grow(w, w->bmats, w->bmats_cap, (int64_t)plan.mats.size()))) return st;
+    const size_t nh = sizeof(BatchHdr) * n_diag, nm = sizeof(double) * plan.mats.size();
+    const double *p0 = w->bplan;
+    if ((st = grow(w, w->bplan, w->bplan_cap, (int64_t)((nh + nm) / sizeof(double))))) return st;
+    if (w->bplan != p0) w->bplan_inputs.clear();
+    w->bhdr = reinterpret_cast<BatchHdr *>(w->bplan);
+    w->bmats = w->bplan + nh / sizeof(double);
     if ((st = grow(w, w->brecs, w->brecs_cap, n_diag))) return st;
     if ((st = grow(w, w->bowner, w->bowner_cap, plan.tiles))) return st;
-    if (w->bhdr != h0 || w->bmats != m0) w->bplan_inputs.clear();
-    const size_t nh = sizeof(BatchHdr) * n_diag, nm = sizeof(double) * plan.mats.size();
     const unsigned char *hb = reinterpret_cast<const unsigned char *>(plan.hdr.data());
     const unsigned char *mb = reinterpret_cast<const unsigned char *>(plan.mats.data());
     // the same plan as the last upload on this stream: the device copies hold it
@@ -986,8 +986,7 @@ qa_status upload_plan(Workspace *w, const BatchPlan &plan, int32_t n_diag)
     std::memcpy(stg, hb, nh);
     std::memcpy(stg + nh, mb, nm);
     w->bplan_inputs.assign(stg, stg + nh + nm);
-    QA_HIP(hipMemcpyAsync(w->bhdr, stg, nh, hipMemcpyHostToDevice, w->stream));
-    if (nm) QA_HIP(hipMemcpyAsync(w->bmats, stg + nh, nm, hipMemcpyHostToDevice, w->stream));
+    QA_HIP(hipMemcpyAsync(w->bplan, stg, nh + nm, hipMemcpyHostToDevice, w->stream));
     QA_HIP(hipEventRecord(w->bstage_ev[slot], w->stream));
     return QA_OK;
 }
@@ -1231,8 +1230,7 @@ void qa_release(void *hip_stream)
     (void)hipFree(w->acc);
     for (auto &e : w->ev)
         for (auto &x : e) (void)hipEventDestroy(x);
-    (void)hipFree(w->bhdr);
-    (void)hipFree(w->bmats);
+    (void)hipFree(w->bplan);
     (void)hipFree(w->brecs);
     (void)hipFree(w->parity);
     (void)hipFree(w->bowner);

@@ -39,14 +39,18 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_batch(const BatchHdr *__r
     const int n = h.n, g = h.g;
     const double *cdd = mats + h.mat_off;
     const double *cgd = cdd + n * n;
-    for (int e = threadIdx.x; e < kMaxDot * kMaxDot; e += blockDim.x) {
-        const int i = e / kMaxDot, j = e % kMaxDot;
-        dr->Cdd[e] = (i < n && j < n) ? cdd[i * n + j] : 0.0;
-    }
-    for (int e = threadIdx.x; e < kMaxDot * kMaxGate; e += blockDim.x) {
-        const int i = e / kMaxGate, j = e % kMaxGate;
-        dr->Cgd[e] = (i < n && j < g) ? cgd[i * g + j] : 0.0;
-    }
+    // (all reads, one round trip, then the stores; C_dd stays in LDS for the inverse)
+    static_assert(kPrepThreads == kMaxDot * kMaxDot && 2 * kPrepThreads == kMaxDot * kMaxGate,
+                  "an entry of C_dd and two of C_gd a thread");
+    const int e = threadIdx.x;
+    const int ci = e / kMaxDot, cj = e % kMaxDot, gi = e / kMaxGate, gj = e % kMaxGate;
+    const double c = ci < n && cj < n ? cdd[ci * n + cj] : 0.0;
+    const double g0 = gi < n && gj < g ? cgd[gi * g + gj] : 0.0;
+    const double g1 = 8 + gi < n && gj < g ? cgd[(8 + gi) * g + gj] : 0.0;
+    sCdd[e] = c;
+    dr->Cdd[e] = c;
+    dr->Cgd[e] = g0;
+    dr->Cgd[kPrepThreads + e] = g1;
     if (threadIdx.x == 0) {
         dr->n = n;
         dr->g = g;
@@ -57,7 +61,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_batch(const BatchHdr *__r
         dr->prec = 0;
     }
     __syncthreads();
-    prep_body(dr, sCdd, M, cvec, red);
+    prep_inverse(sCdd, n, M, cvec, red);
+    prep_store(dr, M, cvec, red, n);
 }
 
 hipError_t launch_prep_batch(const BatchHdr *hdr, const double *mats, DiagRec *recs, int n_diag,
@@ -423,8 +428,10 @@ __device__ __forceinline__ int64_t batch_pixel(const DiagLds<NM> &L, const Batch
 //     sharded cursors (a wave that had claimed its next item
 //     could still be at a long one when the others had ended)     -> 250 us,
 //     a QP of one form and no masks, nothing spilled (qp_solve)   -> 202 us.
-// Three waves per SIMD (163 registers); two take as long, four 216 us.  Reading
-// voltages and writing results through LDS, row by row, was slower (287 for 250).
+// With a new plan at every call (one upload, C_dd of the prologue kept in LDS) a call
+// takes 223 us.  Three waves per SIMD (163 registers); two take as long, four 216 us.
+// Reading voltages and writing results through LDS, row by row, was slower (287 for
+// 250).
 template <int NM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NM <= 8 ? 3 : 1))) void k_batch(
     const BatchHdr *__restrict__ hdr, const DiagRec *__restrict__ recs,
@@ -488,7 +495,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NM <= 8 ? 3 
         const double *gv = mats + h.grid_off;
         const double *sc = gv + 3 * h.g;  // a0, da, a1, b0, db, b1
         const uint32_t nx = (uint32_t)h.nx, row = (uint32_t)p / nx;
-        const double va = lin_point((int32_t)((uint32_t)p - row * nx), (int32_t)nx, sc[0], sc[1], sc[2]);
+        const double va =
+            lin_point((int32_t)((uint32_t)p - row * nx), (int32_t)nx, sc[0], sc[1], sc[2]);
         const double vb = lin_point((int32_t)row, (int32_t)h.ny, sc[3], sc[4], sc[5]);
         for (int j = 0; j < h.g; ++j)
             add_gate(j, sweep_volt(gv[j], gv[h.g + j], gv[2 * h.g + j], va, vb));

@@ -667,9 +667,8 @@ __device__ __forceinline__ void prep_row_unit(RowTab *rt, const double *A, const
 
 // everything the prologue stores, by one block
 __device__ __forceinline__ void prep_store(DiagRec *dr, const double *M, const double *cvec,
-                                  const double *red)
+                                  const double *red, int n)
 {
-    const int n = dr->n;
     const int tid = threadIdx.x;
     prep_store_core(dr, M, cvec, red);
     // tables of the matrix-core scorer: low part = dots 0..7, high = 8..n-1
@@ -723,7 +722,7 @@ __device__ __forceinline__ void prep_body(DiagRec *dr, double *sCdd, double *M, 
     sCdd[threadIdx.x] = dr->Cdd[threadIdx.x];
     __syncthreads();
     prep_inverse(sCdd, dr->n, M, cvec, red);
-    prep_store(dr, M, cvec, red);
+    prep_store(dr, M, cvec, red, dr->n);
 }
 
 }  // namespace qa
