@@ -1,6 +1,6 @@
 // qa_kernels.hip -- gfx950 kernels of the constant-capacitance ground-state
-// path (van Straaten et al., arXiv 2404.04994), except the matrix-core
-// scorer (qa_mfma.hip).
+// path (van Straaten et al., arXiv 2404.04994), except the scorers of 9 dots and
+// more (qa_rows.hip, qa_mfma.hip) and their softargmin and adjoint (qa_soft.hip).
 //
 //   k_prep      per diagram: A = C_dd^{-1} (FP64 Gauss-Jordan), C_dd 1, the
 //               pixel-independent energy tables (Sec. 2, Eq. free_energy).
@@ -8,10 +8,12 @@
 //               analytic continuous minimum (Sec. 3.1.1, App. C/D) and, where
 //               it is negative, the constrained minimum of Sec. 3.1.2 in FP64
 //               by an active-set elimination across the group; then the
-//               candidate set (Sec. 3.2) and the base-state gradient.
-//   k_score_fp64  T = 0 argmin (Eq. argmin) over each pixel's candidate set,
-//               FP64, a group of lanes per pixel walking a Gray code.
-//   k_soft_fwd  kT > 0 softargmin (Sec. 4.2, Eq. softargmin), FP64.
+//               candidate set (Sec. 3.2) and the base-state gradient; up to
+//               8 dots at T = 0 also the argmin (Eq. argmin).
+//   k_score_fp64  T = 0 argmin over each pixel's whole candidate set, FP64, a
+//               group of lanes per pixel walking a Gray code (on request).
+//   k_soft_fwd  kT > 0 softargmin (Sec. 4.2, Eq. softargmin), FP64: from a table
+//               up to 8 dots, a walk where qa_soft.hip's weights are out of range.
 //   k_soft_bwd  its adjoint with respect to C_dd, C_gd and V.
 #include "qa_device.h"
 
