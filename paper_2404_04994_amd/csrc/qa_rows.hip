@@ -348,10 +348,10 @@ constexpr int64_t kTailPixels = 50000;
 // T = 0 argmin (Eq. argmin) over each pixel's candidate set: a wave per pixel,
 // one lane per low state, over the rows the bound leaves.  Each lane keeps its
 // two smallest energies with the row in the low ten bits of the mantissa (an
-// error below 2^-42 of the energy, so one minimum carries both); a runner-up
-// within 1e-9 is counted, and then the rows are taken once more with the
-// energies as they are: the smallest, ties to the lexicographically smallest
-// state.
+// error below 2^-42 of the energy, so one minimum carries both).  Where a runner-up
+// lies within 1e-9, or within what the row numbers may have changed, the rows are
+// taken once more with the energies as they are: the smallest, ties to the
+// lexicographically smallest state; a gap below 1e-9 is counted.
 template <int MODE, bool TAIL>
 __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_rows_gs(const RowTab *__restrict__ rt,
                                                             const PixRec *__restrict__ pr, int64_t P,
@@ -420,8 +420,10 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         const int win = hit ? __builtin_ctzll(hit) : 0;
         const uint32_t code = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)__double_as_longlong(e1));
         uint32_t s = (e1 < 0x1p99) ? (uint32_t)win | ((code & 1023u) << 6) : 0u;
-        // a runner-up within 1e-9: another lane's best or some lane's second
-        if (__popcll(__ballot(m1 - e1 < 2e-9)) > 1 || __ballot(m2 - e1 < 2e-9)) {
+        // a runner-up that may be nearer than 1e-9 or the smaller one (both energies are
+        // off by 2^-42 of themselves): another lane's best or some lane's second
+        const double near = fma(0x1p-40, fabs(e1), 2e-9);
+        if (__popcll(__ballot(m1 - e1 < near)) > 1 || __ballot(m2 - e1 < near)) {
             double b1 = kBarred, b2 = kBarred;
             uint32_t best = 0xFFFFFFFFu;  // brev(state), the smallest at b1
             px.scan(r, c, T, kset, mlo, mhi, [&](int row, double e) {

@@ -1,0 +1,54 @@
+"""Ground states of 9 dots and more where the energies are large: capacitances in small
+units (energies of 1e5 and 1e7) and closed arrays far from their carrier number.  The
+states compete by gaps far below 2^-42 of the energies but well above their FP64
+rounding, or tie exactly; both are known without the library."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def qa():
+    from paper_2404_04994_amd import qarray
+    qarray.load()
+    return qarray
+
+
+@pytest.mark.parametrize("precision", ["fp64", "bf16x3"])
+@pytest.mark.parametrize("scale", [1.0, 1e-5, 1e-7])
+@pytest.mark.parametrize("n_dot", [9, 12, 13, 16])
+@pytest.mark.parametrize("closed", [False, True])
+def test_gaps_below_the_row_code(qa, closed, n_dot, scale, precision):
+    """Identical dots, x_u = c + (a permutation of 0..n-1) step: whatever number of dots is
+    raised, it is those with the largest x_u.  Swapping neighbours of the permutation
+    changes the energy by (A_ii - A_ij) step; closed arrays add some 100 A_ii a dot to
+    every energy.  Either gap is above 2^-44 of the energies, which FP64 rounds to a few
+    2^-50 of them."""
+    rng = np.random.default_rng(n_dot)
+    cdd = (np.full((n_dot, n_dot), -0.05) + np.diag(np.full(n_dot, 1.25))) * scale
+    order = np.stack([rng.permutation(n_dot) for _ in range(200)])
+    c = (100.0 if closed else 0.0) + 0.4375
+    V = c + order * 2.0 ** (-34 if closed else -42)
+    k = n_dot // 3
+    n = qa.ground_state(cdd, np.eye(n_dot), torch.as_tensor(V).cuda(), closed=closed,
+                        nhat=k if closed else 0, precision=precision).cpu().numpy()
+    raised = n.sum(1)
+    assert (raised == raised[0]).all() and 0 < raised[0] < n_dot
+    if closed:
+        assert raised[0] == k
+    assert (n == (order >= n_dot - raised[0])).all()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "bf16x3"])
+@pytest.mark.parametrize("n_dot,k", [(9, 4), (12, 6), (16, 5)])
+def test_exact_ties_of_large_energies(qa, n_dot, k, precision):
+    """Uncoupled dots of capacitance 2^-17, a closed array with x* = k / n for every dot:
+    all C(n, k) states have the same, exactly representable energy, and the
+    lexicographically smallest one raises the last k dots."""
+    cdd = np.eye(n_dot) * 2.0 ** -17
+    V = np.full((3, n_dot), 100.5)
+    n = qa.ground_state(cdd, np.eye(n_dot), torch.as_tensor(V).cuda(), closed=True, nhat=k,
+                        precision=precision).cpu().numpy()
+    assert (n == (np.arange(n_dot) >= n_dot - k)).all()
