@@ -43,6 +43,10 @@ __device__ __forceinline__ int candidate_set(int n, bool closed, int nhat, doubl
 {
     int flags = 0;
     k = -1;
+    // Every lane goes round until the last one has its set (one that has it forms the
+    // same again).  With an exit per lane the compiler kept the outcomes of i < n from
+    // inside the loop as lane masks, of the last round's lanes only, and read them for
+    // the other lanes' stores, which then ran past the last dot.
     for (int iter = 0; iter < 80; ++iter) {
         fm = 0;
         int sum0 = 0;
@@ -62,15 +66,18 @@ __device__ __forceinline__ int candidate_set(int n, bool closed, int nhat, doubl
             }
         }
         if (!closed) break;
-        const int need = nhat - sum0;
-        if (need >= 0 && need <= __popc(fm)) { k = need; break; }
-        if (t >= 1.0) {  // |sum x* - N_hat| < 1 makes this unreachable
-            k = need < 0 ? 0 : __popc(fm);
+        k = nhat - sum0;
+        const bool missed = k < 0 || k > __popc(fm);
+        const bool again = missed && t < 1.0;
+        if (missed && !again) {  // |sum x* - N_hat| < 1 makes this unreachable
+            k = k < 0 ? 0 : __popc(fm);
             flags |= 2;
-            break;
         }
-        t = (t > 0.0) ? fmin(1.0, 2.0 * t) : 1.0;
-        flags |= 4;
+        if (again) {
+            t = (t > 0.0) ? fmin(1.0, 2.0 * t) : 1.0;
+            flags |= 4;
+        }
+        if (!__any(again)) break;
     }
     return flags;
 }
