@@ -30,9 +30,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep_batch(const BatchHdr *__r
     __shared__ double red[8];
     const BatchHdr h = hdr[blockIdx.x];
     DiagRec *dr = recs + blockIdx.x;
-    for (int e = blockIdx.x * kPrepThreads + threadIdx.x; e < kCounterWords;
-         e += gridDim.x * kPrepThreads)
-        counters[e] = 0;
+    // (by the first block alone: an index over the grid passes 2^31 from 2^23 diagrams on)
+    if (blockIdx.x == 0)
+        for (int e = threadIdx.x; e < kCounterWords; e += kPrepThreads) counters[e] = 0;
     const int64_t items = (h.P + 63) / 64;
     for (int64_t e = threadIdx.x; e < items; e += kPrepThreads)
         owner[h.tile0 + e] = blockIdx.x;

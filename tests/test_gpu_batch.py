@@ -175,3 +175,15 @@ def test_dense_box_blocks(qa, oracle, n_dot, closed):
             assert (b.result(i)[0].sum(1) == d.nhat).all()
         else:
             assert st["candidates"] == b.pixels << n_dot
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 4, 5, 9])
+def test_counters_start_at_zero(qa, count):
+    """The statistics of a batch are its own whatever ran before and however few
+    diagrams (blocks of the prologue) it has."""
+    big = qa.Batch(W.ragged_batch(40, npix=16))
+    b = qa.Batch(W.ragged_batch(count, npix=9, start=50))
+    first = b.run(stats=True)
+    big.run(stats=True)
+    assert b.run(stats=True) == first
+    assert first["pixels"] == 81 * count and first["candidates"] >= first["pixels"]
