@@ -436,12 +436,12 @@ template <int NM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NM <= 8 ? 3 : 1))) void k_batch(
     const BatchHdr *__restrict__ hdr, const DiagRec *__restrict__ recs,
     const double *__restrict__ mats, const int32_t *__restrict__ owner,
-    const double *__restrict__ V, int32_t *__restrict__ n_out, double *__restrict__ nbar,
-    int64_t *__restrict__ counters)
+    int64_t item0, const double *__restrict__ V, int32_t *__restrict__ n_out,
+    double *__restrict__ nbar, int64_t *__restrict__ counters)
 {
     __shared__ DiagLds<NM> L;
     const int lane = threadIdx.x;
-    const int64_t item = blockIdx.x;
+    const int64_t item = item0 + blockIdx.x;
     const int d = __builtin_amdgcn_readfirstlane(owner[item]);
     const BatchHdr h = hdr[d];
     const DiagRec *dr = recs + d;
@@ -526,11 +526,17 @@ hipError_t launch_batch(const BatchHdr *hdr, const DiagRec *recs, const double *
                         const int32_t *owner, int64_t tiles, const double *V, int32_t *n_out,
                         double *nbar, int64_t *counters, int max_dot, hipStream_t s)
 {
-    if (tiles < 1 || tiles > INT32_MAX) return hipErrorInvalidValue;
+    if (tiles < 1) return hipErrorInvalidValue;
+    // (a launch holds fewer than 2^32 threads)
+    constexpr int64_t kMostItems = (int64_t)1 << 25;
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64), 0, s, hdr, recs, mats, owner,
-                           V, n_out, nbar, counters);
-        return hipGetLastError();
+        for (int64_t item0 = 0; item0 < tiles; item0 += kMostItems) {
+            const int64_t items = tiles - item0 < kMostItems ? tiles - item0 : kMostItems;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(64), 0, s, hdr, recs, mats,
+                               owner, item0, V, n_out, nbar, counters);
+            if (const hipError_t e = hipGetLastError()) return e;
+        }
+        return hipSuccess;
     };
     return max_dot <= 4 ? go(k_batch<4>) : max_dot <= 8 ? go(k_batch<8>) : go(k_batch<16>);
 }

@@ -187,3 +187,28 @@ def test_counters_start_at_zero(qa, count):
     big.run(stats=True)
     assert b.run(stats=True) == first
     assert first["pixels"] == 81 * count and first["candidates"] >= first["pixels"]
+
+
+def test_more_pixels_than_threads_of_a_launch(qa):
+    """2^32 pixels and more (a launch holds fewer than 2^32 threads): 4097 sweeps of a
+    single dot of 1024 x 1024 pixels; diagrams from either end and the middle against
+    calls of their own."""
+    side, count = 1024, 4097
+    rng = np.random.default_rng(77)
+    V = np.broadcast_to(np.zeros((1, 1)), (side * side, 1))  # (a sweep's are not read)
+    ds = []
+    for i in range(count):
+        sweep = dict(v0=[rng.uniform(0.0, 1.0)], e1=[1.0], e2=[rng.uniform(-0.5, 0.5)],
+                     a0=-2.0, a1=6.0, nx=side, b0=-1.0, b1=1.0, ny=side)
+        ds.append(W.Diagram(np.array([[rng.uniform(0.8, 1.2)]]), np.array([[1.0]]), V, sweep=sweep))
+    b = qa.Batch(ds, sweeps=True)
+    st = b.run(with_nbar=False, stats=True)
+    assert st["pixels"] == b.pixels == count << 20 and st["qp_failures"] == 0
+    for i in (0, 1, 2047, 2048, 4094, 4095, 4096):
+        d = ds[i]
+        alone = qa.ground_state_grid(d.cdd, d.cgd, d.sweep)
+        o = int(b.out_offsets[i])
+        assert torch.equal(b.n[o:o + (1 << 20)].view(-1, 1), alone), i
+    del b
+    torch.cuda.empty_cache()
+    qa.release()
