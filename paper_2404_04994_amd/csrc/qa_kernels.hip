@@ -313,7 +313,8 @@ static_assert(kSetupThreads >= kMaxDot * kMaxDot, "C_dd staging: one entry per t
 
 template <int NM, bool CLOSED, bool ARGS>
 __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict__ dr,
-                                                         const double *__restrict__ V, int64_t P,
+                                                         const double *__restrict__ V,
+                                                         const uint32_t first, const uint32_t P,
                                                          PixRec *__restrict__ pr,
                                                          int64_t *__restrict__ counters,
                                                          int32_t *__restrict__ bstats,
@@ -359,7 +360,8 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
     // wave are adjacent pixels (similar active sets, so the union of their QP
     // pivots stays small) while the waves of one block come from across the
     // sweep, so the QP-heavy regions are shared out among the blocks
-    const int64_t p = ((int64_t)(tp / kWave) * gridDim.x + blockIdx.x) * (kWave / NM) +
+    // (pixels first .. P - 1; wave 0's own p is not used)
+    const int64_t p = first + ((int64_t)(tp / kWave) * gridDim.x + blockIdx.x) * (kWave / NM) +
                       (tp & (kWave - 1)) / NM;
     const int64_t pc = p < P ? p : P - 1;  // groups past the end repeat the last pixel
     const bool is_dot = dot < n;
@@ -811,21 +813,29 @@ hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int
 {
     if (split == kBoundLow6 && (!rt || n_dot < 9)) return hipErrorInvalidValue;
     if (n_out && n_dot > 8) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)setup_blocks(P, n_dot)), block(kSetupThreads);
-    const auto go = [&](auto kernel, const auto &src) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, dr, V, P, pr, counters, bstats, x_out,
-                           flags_out, (int)split, rt, n_out, src);
+    // whole blocks' pixels at a time: a launch holds fewer than 2^32 threads
+    constexpr int64_t kMostBlocks = (int64_t)1 << 22;
+    const auto go = [&](auto nm, auto kernel, const auto &src) {
+        const int64_t most = kMostBlocks * (kSetupPixThreads / decltype(nm)::value);
+        for (int64_t first = 0; first < P; first += most) {
+            const int64_t pixels = P - first < most ? P - first : most;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)setup_blocks(pixels, n_dot)),
+                               dim3(kSetupThreads), 0, s, dr, V, (uint32_t)first,
+                               (uint32_t)(first + pixels), pr, counters,
+                               bstats + kBstatWords * setup_blocks(first, n_dot) * (first > 0),
+                               x_out, flags_out, (int)split, rt, n_out, src);
+            if (const hipError_t e = hipGetLastError()) return e;
+        }
+        return hipSuccess;
     };
     if (in) {
-        if (closed) QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, true, true>, *in)));
-        else QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, false, true>, *in)));
-        return hipGetLastError();
+        if (closed) QA_DISPATCH_NM(n_dot, return go(std::integral_constant<int, NM_>{}, k_setup<NM_, true, true>, *in));
+        QA_DISPATCH_NM(n_dot, return go(std::integral_constant<int, NM_>{}, k_setup<NM_, false, true>, *in));
     }
     VGrid vg{};
     if (sweep) vg = *sweep;
-    if (closed) QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, true, false>, vg)));
-    else QA_DISPATCH_NM(n_dot, (go(k_setup<NM_, false, false>, vg)));
-    return hipGetLastError();
+    if (closed) QA_DISPATCH_NM(n_dot, return go(std::integral_constant<int, NM_>{}, k_setup<NM_, true, false>, vg));
+    QA_DISPATCH_NM(n_dot, return go(std::integral_constant<int, NM_>{}, k_setup<NM_, false, false>, vg));
 }
 
 // ---------------------------------------------------------------------------
