@@ -89,7 +89,8 @@ __device__ __forceinline__ double dppd(double x)
 // acc + sum_q t_q x(lane q of the row), fused multiply-adds in increasing q, each with
 // the broadcast as its operand (5.7 cycles; a move and an fma take 10).  The leading
 // wait is what a lane exchange needs after x is written, which the compiler does not
-// see inside the block.
+// see inside the block.  (Early clobber: acc is written before the last inputs are read,
+// and an input of the same value could share its register otherwise; row_axpy8 alike.)
 __device__ __forceinline__ double row_dot16(double acc, double x, const double (&t)[16])
 {
     asm("s_nop 1\n\t"
@@ -109,7 +110,7 @@ __device__ __forceinline__ double row_dot16(double acc, double x, const double (
         "v_fmac_f64_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n\t"
-        : "+v"(acc)
+        : "+&v"(acc)
         : "v"(x), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
           "v"(t[7]), "v"(t[8]), "v"(t[9]), "v"(t[10]), "v"(t[11]), "v"(t[12]), "v"(t[13]),
           "v"(t[14]), "v"(t[15]));
@@ -128,8 +129,8 @@ __device__ __forceinline__ void row_axpy8(double *r, double f)
         "v_fmac_f64_dpp %5, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %6, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %7, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-        : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]),
-          "+v"(r[7])
+        : "+&v"(r[0]), "+&v"(r[1]), "+&v"(r[2]), "+&v"(r[3]), "+&v"(r[4]), "+&v"(r[5]),
+          "+&v"(r[6]), "+&v"(r[7])
         : "v"(f), "n"(K));
 }
 
