@@ -38,9 +38,10 @@ PER_FILE = {
     "qa_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # energies are finite: fmin/fmax without NaN canonicalisation
     "qa_batch.hip": ["-fno-honor-nans"],
-    "qa_rows.hip": ["-fno-honor-nans"],
     # results of the matrix products feed vector operations: no accumulator copies
-    "qa_soft.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    # (like qa_rows.hip with NaNs honoured: both say what voltages that are not
+    # numbers give)
+    "qa_soft.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     # the first kernel arguments arrive in SGPRs at wave start (no scalar load
     # before the first address): the short softargmin and adjoint kernels
     # here gain about 0.2 us each

@@ -47,18 +47,30 @@ __device__ __forceinline__ void write_lane(uint32_t &v, uint32_t x)
     asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(L));
 }
 
+// The smaller of two numbers, as the hardware forms it: the other one where one is not a
+// number.  (fmin puts an instruction before it for every operand that came through
+// integer operations, in case it is a signalling NaN, which no result of arithmetic is.)
+// The wait is what a lane exchange needs after its source is written, which the compiler
+// does not see inside the block.
+__device__ __forceinline__ double num_min(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // minimum over the 64 lanes
 __device__ __forceinline__ double wave_min_d(double x)
 {
-    x = fmin(x, dppd<kDppXor1>(x));
-    x = fmin(x, dppd<kDppXor2>(x));
-    x = fmin(x, dppd<kDppHalfMirror>(x));
-    x = fmin(x, dppd<kDppMirror>(x));
+    x = num_min(x, dppd<kDppXor1>(x));
+    x = num_min(x, dppd<kDppXor2>(x));
+    x = num_min(x, dppd<kDppHalfMirror>(x));
+    x = num_min(x, dppd<kDppMirror>(x));
     auto swap_min = [&](auto swap) {
         const uint64_t u = (uint64_t)__double_as_longlong(x);
         const auto lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32));
-        x = fmin(__longlong_as_double((long long)((uint64_t)lo[0] | ((uint64_t)hi[0] << 32))),
-                 __longlong_as_double((long long)((uint64_t)lo[1] | ((uint64_t)hi[1] << 32))));
+        x = num_min(__longlong_as_double((long long)((uint64_t)lo[0] | ((uint64_t)hi[0] << 32))),
+                    __longlong_as_double((long long)((uint64_t)lo[1] | ((uint64_t)hi[1] << 32))));
     };
     swap_min([](uint32_t v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
     swap_min([](uint32_t v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
@@ -265,10 +277,11 @@ struct RowPixel {
     }
 
     // the energies of those rows (relative to U(n0); kBarred outside a closed set,
-    // above 2^99 where a fixed dot is raised): f(row, energy of the lane's state)
-    template <typename F>
+    // above 2^99 where a fixed dot is raised): to(row, energy of the lane's state), or two
+    // rows at once
+    template <typename To>
     __device__ __forceinline__ void scan(const PixRec *r, const RowConst &c, const RowLds &t,
-                                         uint32_t kset, uint32_t mlo, uint32_t mhi, F &&f) const
+                                         uint32_t kset, uint32_t mlo, uint32_t mhi, To &to) const
     {
         constexpr bool CLOSED = MODE == kModeClosed;
         const int lane = threadIdx.x & 63;
@@ -298,14 +311,73 @@ struct RowPixel {
                 mask ^= 1ull << c1;
                 const double t0 = t.T[c0][lane], t1 = t.T[c1][lane];
                 const double e0 = energy(c0, t0), e1 = energy(c1, t1);
-                f(kk * 64 + c0, e0);
-                f(kk * 64 + c1, e1);
+                to(kk * 64 + c0, e0, kk * 64 + c1, e1);
             }
             if (mask) {
                 const int c0 = __builtin_ctzll(mask);
-                f(kk * 64 + c0, energy(c0, t.T[c0][lane]));
+                to(kk * 64 + c0, energy(c0, t.T[c0][lane]));
             }
         }
+    }
+};
+
+// A lane's two smallest energies, the row in the low ten bits of the mantissa.  The
+// comparisons are the hardware's, which take the other operand where one is not a number;
+// fmin and fmax put an instruction before them for an energy whose low bits were
+// replaced, in case it is a signalling NaN (no result of arithmetic is).
+struct RowMins {
+    double m1 = kBarred, m2 = kBarred;
+    uint32_t keep;
+    __device__ __forceinline__ double coded(int row, double e) const
+    {
+        const uint64_t u = (uint64_t)__double_as_longlong(e);
+        const uint32_t lo = ((uint32_t)u & keep) | (uint32_t)row;
+        return __longlong_as_double((long long)((u & 0xFFFFFFFF00000000ull) | lo));
+    }
+    static __device__ __forceinline__ double lower(double a, double b)
+    {
+        double r;
+        asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+        return r;
+    }
+    static __device__ __forceinline__ double upper(double a, double b)
+    {
+        double r;
+        asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+        return r;
+    }
+    __device__ __forceinline__ void operator()(int row, double e)
+    {
+        const double x = coded(row, e), t = upper(m1, x);
+        m1 = lower(m1, x);
+        m2 = lower(m2, t);
+    }
+    __device__ __forceinline__ void operator()(int row0, double e0, int row1, double e1)
+    {
+        const double x = coded(row0, e0), y = coded(row1, e1);
+        const double lo = lower(x, y), hi = upper(x, y);
+        m2 = lower(m2, hi);
+        const double t = upper(m1, lo);
+        m1 = lower(m1, lo);
+        m2 = lower(m2, t);
+    }
+};
+
+// The same with the energies as they are and the lexicographically smallest state of the
+// smallest energy (as brev(state)).
+struct RowTies {
+    double b1 = kBarred, b2 = kBarred;
+    uint32_t best = 0xFFFFFFFFu;
+    __device__ __forceinline__ void operator()(int row, double e)
+    {
+        const uint32_t at = __brev((threadIdx.x & 63) | ((uint32_t)row << 6));
+        if (e < b1 || (e == b1 && at < best)) { b2 = b1; b1 = e; best = at; }
+        else b2 = fmin(b2, e);
+    }
+    __device__ __forceinline__ void operator()(int row0, double e0, int row1, double e1)
+    {
+        (*this)(row0, e0);
+        (*this)(row1, e1);
     }
 };
 
@@ -378,7 +450,9 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
     }
     if (threadIdx.x < 3) sc[threadIdx.x] = 0;
     __syncthreads();
-    int64_t ngap = 0, nrows = 0, ncand = 0;
+    // (a wave takes at most 2^31 / 6144 pixels, a lane holds at most 64 rows of one)
+    int32_t ngap = 0, nrows = 0;
+    int64_t ncand = 0;
     const PixRec *r = &T.rec[wv];
     uint32_t keep = ~1023u;
     asm("" : "+v"(keep));  // a register: with a literal the and-or is two instructions
@@ -407,14 +481,10 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         }
         nrows += __popc(mlo) + __popc(mhi);  // (a lane's share: summed at the end)
         row_priority(mlo, mhi, p + nwaves < P);
-        double m1 = kBarred, m2 = kBarred;
-        px.scan(r, c, T, kset, mlo, mhi, [&](int row, double e) {
-            const uint64_t u = (uint64_t)__double_as_longlong(e);
-            const uint32_t lo = ((uint32_t)u & keep) | (uint32_t)row;
-            const double x = __longlong_as_double((long long)((u & 0xFFFFFFFF00000000ull) | lo));
-            m2 = fmin(m2, fmax(m1, x));
-            m1 = fmin(m1, x);
-        });
+        RowMins mins;
+        mins.keep = keep;
+        px.scan(r, c, T, kset, mlo, mhi, mins);
+        const double m1 = mins.m1, m2 = mins.m2;
         const double e1 = wave_min_d(m1);
         const unsigned long long hit = __ballot(m1 == e1);
         const int win = hit ? __builtin_ctzll(hit) : 0;
@@ -422,15 +492,12 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         uint32_t s = (e1 < 0x1p99) ? (uint32_t)win | ((code & 1023u) << 6) : 0u;
         // a runner-up that may be nearer than 1e-9 or the smaller one (both energies are
         // off by 2^-42 of themselves): another lane's best or some lane's second
-        const double near = fma(0x1p-40, fabs(e1), 2e-9);
-        if (__popcll(__ballot(m1 - e1 < near)) > 1 || __ballot(m2 - e1 < near)) {
-            double b1 = kBarred, b2 = kBarred;
-            uint32_t best = 0xFFFFFFFFu;  // brev(state), the smallest at b1
-            px.scan(r, c, T, kset, mlo, mhi, [&](int row, double e) {
-                const uint32_t at = __brev((uint32_t)lane | ((uint32_t)row << 6));
-                if (e < b1 || (e == b1 && at < best)) { b2 = b1; b1 = e; best = at; }
-                else b2 = fmin(b2, e);
-            });
+        const double near = fma(0x1p-40, fabs(e1), e1 + 2e-9);
+        if (__popcll(__ballot(m1 < near)) > 1 || __ballot(m2 < near)) {
+            RowTies ties;
+            px.scan(r, c, T, kset, mlo, mhi, ties);
+            double b1 = ties.b1, b2 = ties.b2;
+            uint32_t best = ties.best;
             for (int off = 32; off >= 1; off >>= 1) {
                 const double o1 = __shfl_xor(b1, off), o2 = __shfl_xor(b2, off);
                 const uint32_t oa = __shfl_xor(best, off);
@@ -438,14 +505,14 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
                 else b2 = fmin(b2, o1);
             }
             if (b1 < 0x1p99) s = __brev(best);
-            if (b2 - b1 < 1e-9) ++ngap;
+            if (b1 < 0x1p99 && b2 - b1 < 1e-9) ++ngap;
         }
         if (lane < n) n_out[p * n + lane] = (int32_t)r->n0[lane & 15] + (int32_t)(s >> lane & 1u);
     }
-    nrows = (int64_t)wave_sum((double)nrows);
+    const int64_t rows = (int64_t)wave_sum((double)nrows);
     if (lane == 0) {
         if (ngap) atomicAdd(&sc[0], (unsigned long long)ngap);
-        if (nrows) atomicAdd(&sc[1], (unsigned long long)nrows);
+        if (rows) atomicAdd(&sc[1], (unsigned long long)rows);
         if (ncand) atomicAdd(&sc[2], (unsigned long long)ncand);
     }
     __syncthreads();

@@ -265,7 +265,8 @@ __device__ __forceinline__ void soft_const(const RowTab *__restrict__ rt, const 
     }
 }
 
-// doubles as integers of the same order (no NaN)
+// doubles as integers of the same order (energies that are not numbers, all of a pixel's
+// then, come out as classes without a smallest energy: no weights, charges 0 / 0)
 __device__ __forceinline__ unsigned long long ordered(double x)
 {
     const long long u = __double_as_longlong(x);
