@@ -308,10 +308,11 @@ __device__ __forceinline__ double soft_factors(const double *g0, uint32_t fm, in
     if constexpr (!CLOSED) {
         const double r1 = row_min_d(fmin(fmin(e1[0], e1[1]), fmin(e1[2], e1[3])));
         const double r2 = row_min_d(fmin(fmin(e2[0], e2[1]), fmin(e2[2], e2[3])));
+        const double rf = r2 < kNoState ? r2 : 0.0;  // (none of the column's states: all zero)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             f1[i] = exp_neg((r1 - e1[i]) * ikT);
-            f2[i] = r2 < kNoState ? exp_neg((r2 - e2[i]) * ikT) : 0.0;
+            f2[i] = exp_neg((rf - e2[i]) * ikT);
             if (i & 1) __builtin_amdgcn_sched_barrier(0);
         }
         return r1 + r2;
