@@ -279,7 +279,7 @@ struct RowPixel {
     // the energies of those rows (relative to U(n0); kBarred outside a closed set,
     // above 2^99 where a fixed dot is raised): to(row, energy of the lane's state), or two
     // rows at once
-    template <typename To>
+    template <bool FOUR, typename To>
     __device__ __forceinline__ void scan(const PixRec *r, const RowConst &c, const RowLds &t,
                                          uint32_t kset, uint32_t mlo, uint32_t mhi, To &to) const
     {
@@ -303,7 +303,25 @@ struct RowPixel {
                 if (!CLOSED) return e;
                 return pcl == left - __popc((uint32_t)c6) ? e : kBarred;
             };
-            // two rows at a time: their table reads and sums overlap
+            // Four rows at a time, then two: their table reads and sums overlap.  (A wave
+            // that is left alone with hundreds of rows waits for each step; the second
+            // pass over ties stays at two for its registers.)
+            while (FOUR && __popcll(mask) >= 4) {
+                const int c0 = __builtin_ctzll(mask);
+                mask ^= 1ull << c0;
+                const int c1 = __builtin_ctzll(mask);
+                mask ^= 1ull << c1;
+                const int c2 = __builtin_ctzll(mask);
+                mask ^= 1ull << c2;
+                const int c3 = __builtin_ctzll(mask);
+                mask ^= 1ull << c3;
+                const double t0 = t.T[c0][lane], t1 = t.T[c1][lane];
+                const double t2 = t.T[c2][lane], t3 = t.T[c3][lane];
+                const double e0 = energy(c0, t0), e1 = energy(c1, t1);
+                const double e2 = energy(c2, t2), e3 = energy(c3, t3);
+                to(kk * 64 + c0, e0, kk * 64 + c1, e1);
+                to(kk * 64 + c2, e2, kk * 64 + c3, e3);
+            }
             while (mask & (mask - 1)) {
                 const int c0 = __builtin_ctzll(mask);
                 mask ^= 1ull << c0;
@@ -483,7 +501,7 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         row_priority(mlo, mhi, p + nwaves < P);
         RowMins mins;
         mins.keep = keep;
-        px.scan(r, c, T, kset, mlo, mhi, mins);
+        px.template scan<PRUNED || TAIL>(r, c, T, kset, mlo, mhi, mins);
         const double m1 = mins.m1, m2 = mins.m2;
         const double e1 = wave_min_d(m1);
         const unsigned long long hit = __ballot(m1 == e1);
@@ -495,7 +513,7 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         const double near = fma(0x1p-40, fabs(e1), e1 + 2e-9);
         if (__popcll(__ballot(m1 < near)) > 1 || __ballot(m2 < near)) {
             RowTies ties;
-            px.scan(r, c, T, kset, mlo, mhi, ties);
+            px.template scan<false>(r, c, T, kset, mlo, mhi, ties);
             double b1 = ties.b1, b2 = ties.b2;
             uint32_t best = ties.best;
             for (int off = 32; off >= 1; off >>= 1) {
