@@ -85,10 +85,11 @@ typedef enum { QA_OPEN = 0, QA_CLOSED = 1 } qa_mode;
  * The integer result is the same for all four: the near-tie re-score
  * replaces the approximate argmin by the FP64 one whenever the approximate
  * runner-up lies within the certified error band.  The matrix-core forms run
- * where they are the faster ones: the split-BF16 forms over the dense box
- * (t = 1, open) of 16 dots and at most 16000 pixels, and every matrix-core
- * form (n_dot >= 9: dense boxes, thresholded sub-boxes, closed subsets) when
- * all candidate energies are asked for (QA_FLAG_EXHAUSTIVE).  Elsewhere the
+ * where they are the faster ones: the split-BF16 forms over open sets of 16 dots
+ * (the dense box at up to 48000 pixels, thresholded sub-boxes at up to 16000) and
+ * the dense box of 15 (24000), and every matrix-core form (n_dot >= 9: dense boxes,
+ * thresholded sub-boxes, closed subsets) when all candidate energies are asked for
+ * (QA_FLAG_EXHAUSTIVE).  Elsewhere the
  * FP64 form runs regardless of the request. */
 typedef enum {
     QA_PREC_FP64 = 0,

@@ -378,19 +378,28 @@ int scorer_mode(const qa_problem *pb)
 //   kTable       N <= 8: the whole-box table (FP64), inside the setup kernel.
 //   kRows        N >= 9: FP64 rows in bound order, whatever precision is asked
 //                for (all four return the same states).
-//   kMatrixBound the split-BF16 matrix-core search in bound order, where it is
-//                the faster one: dense boxes of 16 dots and few pixels, when the
-//                caller asks for it.  Scorer and setup, BF16x3 / rows, us, 16
-//                dots: 4x4 array 21.5 / 23.4 at 10^4 pixels, 30.2 / 30.6 at
-//                1.6*10^4; random capacitances 28.3 / 39.9, 35.9 / 47.1.  At
-//                2*10^5 (both with a setup some 40 us slower than now) 264 / 216
-//                and 319 / 296; 13 dots 29.0 / 25.7 at 10^4.  Closed and
-//                thresholded sets and the FP32 form measured slower than rows
-//                everywhere (16 dots, 10^4: closed 52.6 / 48.7, t = 1/2
-//                23.2 / 19.8, FP32 dense 32.1 / 24.1; 12 dots 26.7 / 18.7).
+//   kMatrixBound the split-BF16 matrix-core search in bound order, when the caller
+//                asks for it and it is the faster one: open sets of 16 dots, or 15
+//                dense, up to a number of pixels (kMatrixBoundPixels).  Its tiles of
+//                16 rows of 256 states end a call of few pixels sooner, where single
+//                pixels leave hundreds of rows; from some number of pixels on all
+//                pixels' instructions count, of which the rows take fewer.  Rows /
+//                matrix, us a call, means over five sets of random capacitances and
+//                five 4x4 arrays:
+//                16 dense     10^4 41.1 / 29.5, 34.1 / 26.6; 4.8*10^4 96.8 / 85.8,
+//                             85.2 / 82.0; 6.4*10^4 110.6 / 106.9, 103.1 / 104.0
+//                15 dense     10^4 28.4 / 26.0, 26.7 / 25.4; 2.4*10^4 47.8 / 44.3,
+//                             44.8 / 44.2; 3.2*10^4 57.8 / 57.4, 52.9 / 56.6
+//                14 dense     10^4 25.1 / 24.6, 22.8 / 24.3 (13: 21.7 / 23.3)
+//                16 t = 1/2   10^4 33.9 / 32.4, 28.7 / 27.9; 1.6*10^4 42.2 / 41.9,
+//                             38.4 / 37.1; 2.4*10^4 51.0 / 51.2, 48.2 / 49.7
+//                15 t = 1/2   10^4 25.8 / 27.9, 25.6 / 26.1
+//                (eight sets each; single sets of 16 dots at t = 1/3 had lost up to
+//                a third by rows).  Closed sets measured slower than rows
+//                everywhere (16 dots, 10^4 pixels 52.6 / 48.7 with the older setup).
 //   kMatrixAll, kFp64All  every energy of the set (QA_FLAG_EXHAUSTIVE).
 enum class Scorer { kTable, kRows, kMatrixBound, kMatrixAll, kFp64All };
-constexpr int64_t kMatrixBoundPixels = 16000;
+constexpr int64_t kMatrixBoundPixels[2][2] = {{24000, 0}, {48000, 16000}};  // [15, 16][dense, t < 1]
 
 Scorer scorer_of(const qa_problem *pb, int64_t P)
 {
@@ -398,7 +407,8 @@ Scorer scorer_of(const qa_problem *pb, int64_t P)
     if (pb->flags & QA_FLAG_EXHAUSTIVE)
         return pb->precision == QA_PREC_FP64 ? Scorer::kFp64All : Scorer::kMatrixAll;
     const bool split_bf16 = pb->precision == QA_PREC_BF16X3 || pb->precision == QA_PREC_BF16X2;
-    if (split_bf16 && pb->n_dot == 16 && scorer_mode(pb) == 0 && P <= kMatrixBoundPixels)
+    const int mode = scorer_mode(pb);
+    if (split_bf16 && pb->n_dot >= 15 && mode <= 1 && P <= kMatrixBoundPixels[pb->n_dot - 15][mode])
         return Scorer::kMatrixBound;
     return Scorer::kRows;
 }

@@ -436,11 +436,10 @@ hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int
 // mode as for launch_score_mfma
 hipError_t launch_rows_gs(const RowTab *rt, const PixRec *pr, int64_t P, int mode, int32_t *n_out,
                           int64_t *counters, int n_dot, hipStream_t s);
-// the same in the table form (n_dot <= 8; the whole-box table from the setup)
 // matrix-core scorer at T = 0; mode 0: the dense box, 1: the sub-box of each
 // pixel's free dots (thresholded), 2: closed arrays (subsets of the free
 // dots with k raised); near ties re-scored in FP64 inside the kernel.  Every
-// state of the set, or (exhaustive false: mode 0, N >= 13, split BF16, setup
+// state of the set, or (exhaustive false: modes 0 and 1, N >= 13, split BF16, setup
 // split kBoundLow8) searched in bound order.
 hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int prec, int mode,
                              bool exhaustive, int32_t *n_out, int64_t *counters, int n_dot,

@@ -558,8 +558,8 @@ __global__ __launch_bounds__(256, 3) void k_score_mfma(const DiagRec *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// Bound-ordered search of the dense box of N >= 13 dots (more than one row
-// tile) in the split-BF16 forms.
+// Bound-ordered search of the dense box and (MODE kPruned) of the thresholded
+// sub-boxes of N >= 13 dots (more than one row tile) in the split-BF16 forms.
 //
 // The argmin over the 2^N states of the box is found without scoring all of
 // them.  With y = n0 - x_u (so g = A y and U(n0 + b) - U(n0) = b^T g +
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256, 3) void k_score_mfma(const DiagRec *__restrict
 // the column operands sit in an LDS table (one read per product) so that
 // the registers allow four or five waves.
 // ---------------------------------------------------------------------------
-template <int PREC>
+template <int PREC, int MODE>
 __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restrict__ dr,
                                                      const PixRec *__restrict__ pr, int64_t P,
                                                      int32_t *__restrict__ n_out,
@@ -612,7 +612,8 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
     __shared__ uint8_t sList[4][256];            // per wave: high index of every scored row
     __shared__ uint32_t sBand[4][128];           // per wave: near-tie states to re-score
     __shared__ uint4 sB[16][64];                 // column operands: [column tile][lane]
-    __shared__ unsigned long long sflag, sgap, srows;
+    __shared__ unsigned long long sflag, sgap, srows, scand;
+    constexpr bool PRUNED = MODE == kPruned;
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int q = lane >> 4;
@@ -642,6 +643,7 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
     double gnext = pr[w0].g0[li];
     int nnext = pr[w0].n0[li];
     float snext = rec_f(w0);
+    uint32_t fnext = PRUNED ? pr[w0].free : 0u;
     float egnext = pr[w0].eg;
     {
         // the diagram's tables, one entry per thread (the blocks are 256
@@ -665,7 +667,7 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         sHs[e] = hs;
         sHlo[e] = hl;
     }
-    if (threadIdx.x == 0) { sflag = 0; sgap = 0; srows = 0; }
+    if (threadIdx.x == 0) { sflag = 0; sgap = 0; srows = 0; scand = 0; }
     __syncthreads();
 
     // pixel-independent column operands (as in the dense scorer), from the
@@ -705,7 +707,7 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         csent = make_uint2(pack2(c1, c2), pack2(cr - c2, 1.0f));
     }
 
-    int64_t nflag = 0, ngap = 0, nrows = 0;
+    int64_t nflag = 0, ngap = 0, nrows = 0, ncand = 0;
     uint8_t *list = sList[wv];
     double *g64 = sG64[wv];
     float *ptab = sPt[wv];
@@ -714,20 +716,26 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         const double gcur = gnext;
         const int ncur = nnext;
         const float scur = snext;
-        // the guess of the pixel (wave-uniform)
+        // the free dots and the guess of the pixel (wave-uniform)
+        const uint32_t F = PRUNED ? __builtin_amdgcn_readfirstlane(fnext) : 0xFFFFu;
         const float egf = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(egnext)));
         if (p + nwaves < P) {
             gnext = pr[p + nwaves].g0[li];
             nnext = pr[p + nwaves].n0[li];
             snext = rec_f(p + nwaves);
+            if (PRUNED) fnext = pr[p + nwaves].free;
             egnext = pr[p + nwaves].eg;
         }
-        // g0 beyond n is zero in the record
+        // g0 beyond n is zero in the record.  Thresholded sets: a fixed dot's entry
+        // carries the penalty 2^100 (states raising it never win; the others score as
+        // in the dense form), the error bound takes the unpenalised values.
         const float gl = (float)gcur;
+        const float glp = (PRUNED && !(F >> li & 1u)) ? 0x1p100f : gl;
         float g[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            g[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gl), i));
+            g[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(glp), i));
+        if (PRUNED) ncand += 1ll << __popc(F & ((1u << n) - 1u));
         // sum |g_i| (every 16-lane row holds g0_0..15)
         const float gabs = __int_as_float(__builtin_amdgcn_readfirstlane(
             __float_as_int(row_sumf(fabsf(gl)))));
@@ -765,7 +773,9 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
             const int rt = q + 4 * e4;
             const int chi = rt * 16 + mrow;
             const float R = e4 == 0 ? Rb : Rb + (e4 == 1 ? sb[6] : (e4 == 2 ? sb[7] : s67));
-            lb[e4] = rt < nrt ? R + sHs[chi] : INFINITY;
+            // (thresholded: none that raises a fixed high dot)
+            const bool ok = rt < nrt && (!PRUNED || !((uint32_t)chi & ~(F >> 8)));
+            lb[e4] = ok ? R + sHs[chi] : INFINITY;
         }
         // b_hi^T g_hi over the low four and the high four bits of the high
         // index (lanes 0..15 and 16..31), for the constant chunks
@@ -851,6 +861,8 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
                 gb = g[2 * d + 1];
             }
 
+        // column tiles (low dots 4..7) that raise no fixed dot
+        auto ct_ok = [&](int ct) { return !PRUNED || !(((uint32_t)ct << 4) & ~F & 0xF0u); };
         // C(c_hi) in FP32: the same sums as b_hi^T g_hi + table
         auto cconst = [&](int chi) { return (ptab[chi & 15] + ptab[16 + (chi >> 4)]) + sH[chi]; };
         // The A operand of tile t (row r of the tile is high index
@@ -926,7 +938,10 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         auto group = [&](const Pack8 &a, auto cgc, f32x4_t (&d)[4]) {
             constexpr int cg = decltype(cgc)::value;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) d[k] = tile(a, 4 * cg + k);
+            for (int k = 0; k < 4; ++k) {
+                if (ct_ok(4 * cg + k)) d[k] = tile(a, 4 * cg + k);
+                else d[k] = f32x4_t{INFINITY, INFINITY, INFINITY, INFINITY};
+            }
         };
         // Per lane: the three smallest group minima b1 <= b2 <= b3 and the
         // group codes 4 t + cg of the first two (a1, a2), a group being the
@@ -941,6 +956,7 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
                 float m = INFINITY;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
+                    if (!ct_ok(4 * cg + k)) continue;
                     const f32x4_t d = tile(a, 4 * cg + k);
                     m = __builtin_fminf(m, __builtin_fminf(d[0], d[1]));
                     m = __builtin_fminf(m, __builtin_fminf(d[2], d[3]));
@@ -1101,6 +1117,7 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         // the in-band states of column tile ct of row tile a = tile t
         // into the band list
         auto gather = [&](int t, const Pack8 &a, int ct) {
+            if (!ct_ok(ct)) return;
             const f32x4_t d = tile(a, ct);
             const float dm = fminf(fminf(d[0], d[1]), fminf(d[2], d[3]));
             if (!__ballot(dm <= thr)) return;
@@ -1184,13 +1201,15 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
         if (nflag) atomicAdd(&sflag, (unsigned long long)nflag);
         if (ngap) atomicAdd(&sgap, (unsigned long long)ngap);
         if (nrows) atomicAdd(&srows, (unsigned long long)nrows);
+        if (ncand) atomicAdd(&scand, (unsigned long long)ncand);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         block_add_counter(counters, C_NEAR_TIE, (int64_t)sflag);
         block_add_counter(counters, C_GAP_1E9, (int64_t)sgap);
         block_add_counter(counters, C_SCORED, (int64_t)srows << 8);  // 256 states per row
-        if (blockIdx.x == 0) block_add_counter(counters, C_CANDIDATES, P << n);
+        if (PRUNED) block_add_counter(counters, C_CANDIDATES, (int64_t)scand);  // summed per pixel
+        else if (blockIdx.x == 0) block_add_counter(counters, C_CANDIDATES, P << n);
     }
 }
 
@@ -1199,9 +1218,9 @@ __global__ __launch_bounds__(256, 4) void k_score_bound(const DiagRec *__restric
 template <typename Kernel>
 static int resident_blocks(Kernel kernel, int slot)
 {
-    static int cache[11][64];
+    static int cache[13][64];
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || slot < 0 || slot >= 11) return 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || slot < 0 || slot >= 13) return 0;
     int &c = cache[slot][dev];
     if (c) return c;
     int cus = 0, per_cu = 0;
@@ -1235,11 +1254,15 @@ hipError_t launch_score_mfma(const DiagRec *dr, const PixRec *pr, int64_t P, int
     if (n_dot < 9 || n_dot > 16 || mode < kDense || mode > kClosed) return hipErrorInvalidValue;
     if (P <= 0) return hipSuccess;
     if (!exhaustive) {
-        if (n_dot < 13 || mode != kDense) return hipErrorInvalidValue;
-        if (prec == kPrecX3)
-            return launch_persistent(k_score_bound<kPrecX3>, 9, dr, pr, P, n_out, counters, s);
-        if (prec == kPrecX2)
-            return launch_persistent(k_score_bound<kPrecX2>, 10, dr, pr, P, n_out, counters, s);
+        if (n_dot < 13) return hipErrorInvalidValue;
+#define QA_BOUND_CASE(PR, MD, SLOT)                                                             \
+    if (prec == PR && mode == MD)                                                               \
+        return launch_persistent(k_score_bound<PR, MD>, SLOT, dr, pr, P, n_out, counters, s);
+        QA_BOUND_CASE(kPrecX3, kDense, 9)
+        QA_BOUND_CASE(kPrecX2, kDense, 10)
+        QA_BOUND_CASE(kPrecX3, kPruned, 11)
+        QA_BOUND_CASE(kPrecX2, kPruned, 12)
+#undef QA_BOUND_CASE
         return hipErrorInvalidValue;
     }
 #define QA_SCORER_CASE(PR, MD, SLOT)                                                            \
