@@ -441,10 +441,12 @@ void chol_inverse(int n, const double *C, double *R, double *A);
 // Whether the softargmin of N >= 9 dots may run as matrix products: the factor
 // that couples dots 0..5 to dots 6..11, exp(-T'/kT) with |T'| <= 1/4 sum|A_ij|,
 // has to stay within exp(+-300) (qa_soft.hip).  That holds down to kT of about
-// 0.002 for arrays of capacitance 1; below, every candidate is walked.
+// 0.002 for arrays of capacitance 1; below, every candidate is walked.  (So it is at
+// temperatures whose reciprocal is near the ends of the range: the energy 2^1000 of a state
+// outside the set has to stay large over kT, also where nothing couples the dots.)
 bool soft_mm_range(const qa_problem *pb)
 {
-    if (pb->n_dot < 9) return false;
+    if (pb->n_dot < 9 || pb->kT < 1e-290 || pb->kT > 1e290) return false;
     const int n = pb->n_dot;
     double R[QA_MAX_DOT * QA_MAX_DOT], A[QA_MAX_DOT * QA_MAX_DOT], t = 0.0;
     chol_inverse(n, pb->cdd, R, A);
