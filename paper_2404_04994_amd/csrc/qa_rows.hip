@@ -168,9 +168,9 @@ struct RowPixel {
         ch = c.hhi;
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
-            // raising a fixed low dot costs 2^100: such a state never wins, the
+            // raising a fixed low dot costs 2^500: such a state never wins, the
             // others are exact (a zero bit times the penalty)
-            const double gi = (PRUNED && !(free >> i & 1u)) ? 0x1p100 : r->g0[i];
+            const double gi = (PRUNED && !(free >> i & 1u)) ? 0x1p500 : r->g0[i];
             lg = fma(c.bit[i], gi, lg);
             ch = fma(c.bit[i], r->g0[6 + i], ch);
         }
@@ -277,7 +277,7 @@ struct RowPixel {
     }
 
     // the energies of those rows (relative to U(n0); kBarred outside a closed set,
-    // above 2^99 where a fixed dot is raised): to(row, energy of the lane's state), or two
+    // above 2^499 where a fixed dot is raised): to(row, energy of the lane's state), or two
     // rows at once
     template <bool FOUR, typename To>
     __device__ __forceinline__ void scan(const PixRec *r, const RowConst &c, const RowLds &t,
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
         const unsigned long long hit = __ballot(m1 == e1);
         const int win = hit ? __builtin_ctzll(hit) : 0;
         const uint32_t code = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)__double_as_longlong(e1));
-        uint32_t s = (e1 < 0x1p99) ? (uint32_t)win | ((code & 1023u) << 6) : 0u;
+        uint32_t s = (e1 < 0x1p499) ? (uint32_t)win | ((code & 1023u) << 6) : 0u;
         // a runner-up that may be nearer than 1e-9 or the smaller one (both energies are
         // off by 2^-42 of themselves): another lane's best or some lane's second
         const double near = fma(0x1p-40, fabs(e1), e1 + 2e-9);
@@ -522,8 +522,8 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
                 if (o1 < b1 || (o1 == b1 && oa < best)) { b2 = fmin(b1, o2); b1 = o1; best = oa; }
                 else b2 = fmin(b2, o1);
             }
-            if (b1 < 0x1p99) s = __brev(best);
-            if (b1 < 0x1p99 && b2 - b1 < 1e-9) ++ngap;
+            if (b1 < 0x1p499) s = __brev(best);
+            if (b1 < 0x1p499 && b2 - b1 < 1e-9) ++ngap;
         }
         if (lane < n) n_out[p * n + lane] = (int32_t)r->n0[lane & 15] + (int32_t)(s >> lane & 1u);
     }

@@ -52,3 +52,18 @@ def test_exact_ties_of_large_energies(qa, n_dot, k, precision):
     n = qa.ground_state(cdd, np.eye(n_dot), torch.as_tensor(V).cuda(), closed=True, nhat=k,
                         precision=precision).cpu().numpy()
     assert (n == (np.arange(n_dot) >= n_dot - k)).all()
+
+
+@pytest.mark.parametrize("scale", [1e-29, 1e-33, 1e-37])
+@pytest.mark.parametrize("closed,t", [(False, 1.0), (False, 0.6), (True, 1.0), (True, 0.6)])
+@pytest.mark.parametrize("n_dot", [9, 12, 16])
+def test_far_units(qa, n_dot, closed, t, scale):
+    """FP64 scoring does not mind the unit of capacitance: the states of the same diagram
+    at capacitance 1 (x_u is the same, all energies scale alike)."""
+    rng = np.random.default_rng(40 + n_dot)
+    cdd = np.full((n_dot, n_dot), -0.04) + np.diag(rng.uniform(1.0, 1.4, n_dot))
+    V = torch.as_tensor(rng.uniform(-0.5, 3.0, (300, n_dot))).cuda()
+    kw = dict(closed=closed, nhat=n_dot if closed else 0, t=t)
+    ref = qa.ground_state(cdd, np.eye(n_dot), V, **kw)
+    n = qa.ground_state(cdd * scale, np.eye(n_dot), V, **kw)
+    assert torch.equal(n, ref)
