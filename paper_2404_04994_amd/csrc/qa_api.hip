@@ -455,53 +455,63 @@ bool soft_mm_range(const qa_problem *pb)
     return 0.25 * t <= 300.0 * pb->kT;
 }
 
-// whether the setup of such a call writes the row tables
-bool writes_row_tables(const qa_problem *pb, bool soft, int64_t P)
+// What a call runs after its setup (found once per call: soft_mm_range inverts C_dd).
+struct Route {
+    Scorer sc;         // the T = 0 scorer
+    bool soft, mm;     // the softargmin instead, and as matrix products
+    BoundSplit split;  // the bound terms of the setup
+    bool rows;         // the setup writes the row tables
+};
+Route route_of(const qa_problem *pb, int64_t P, bool soft)
 {
-    return soft ? soft_mm_range(pb) : scorer_split(scorer_of(pb, P)) == kBoundLow6;
+    Route r;
+    r.sc = scorer_of(pb, P);
+    r.soft = soft;
+    r.mm = soft && soft_mm_range(pb);
+    r.split = soft ? kBoundNone : scorer_split(r.sc);
+    r.rows = r.mm || r.split == kBoundLow6;
+    return r;
 }
 
 // The device work of one single-diagram call on stream s, with the inputs
 // already in dr or in `in`: prologue, setup and QP in one kernel, then either the T = 0
-// scoring (n_out) or the softargmin (nbar, saved).  pr holds P pixel records,
+// scoring (n_out) or the softargmin (nbar, saved), as `route` says.  pr holds P pixel records,
 // bstats kBstatWords * setup_blocks(P, n_dot) counts.  ev: optional stage events.
 qa_status enqueue_path(DiagRec *dr, RowTab *rt, PixRec *pr, int64_t *counters, int32_t *bstats,
-                       hipStream_t s, const qa_problem *pb, const double *V, int64_t P, int32_t *n_out,
-                       double *nbar, SavedRec *saved, std::array<hipEvent_t, 4> *ev,
-                       const VGrid *sweep = nullptr, const SetupIn *in = nullptr)
+                       hipStream_t s, const qa_problem *pb, const Route &route, const double *V,
+                       int64_t P, int32_t *n_out, double *nbar, SavedRec *saved,
+                       std::array<hipEvent_t, 4> *ev, const VGrid *sweep = nullptr,
+                       const SetupIn *in = nullptr)
 {
     const bool closed = pb->mode == QA_CLOSED;
-    const Scorer sc = scorer_of(pb, P);
     if (ev) QA_HIP(hipEventRecord((*ev)[0], s));
-    const bool mm = nbar && soft_mm_range(pb);
-    const BoundSplit split = nbar ? kBoundNone : scorer_split(sc);
-    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed, split,
-                        mm || split == kBoundLow6 ? rt : nullptr, s, nullptr, nullptr, sweep, in,
-                        !nbar && sc == Scorer::kTable ? n_out : nullptr));
+    QA_HIP(launch_setup(dr, V, P, pr, counters, bstats, pb->n_dot, closed, route.split,
+                        route.rows ? rt : nullptr, s, nullptr, nullptr, sweep, in,
+                        !route.soft && route.sc == Scorer::kTable ? n_out : nullptr));
     if (ev) QA_HIP(hipEventRecord((*ev)[1], s));
-    if (mm)
+    if (route.mm)
         QA_HIP(launch_soft_mm(dr, rt, pr, P, nbar, saved, pb->n_dot, closed, s));
-    else if (nbar)
+    else if (route.soft)
         QA_HIP(launch_soft_fwd(dr, pr, P, nbar, saved, counters, pb->n_dot, s));
-    else if (sc != Scorer::kTable)
-        QA_HIP(launch_scorer(sc, dr, rt, pr, counters, pb, P, n_out, s));
+    else if (route.sc != Scorer::kTable)
+        QA_HIP(launch_scorer(route.sc, dr, rt, pr, counters, pb, P, n_out, s));
     if (ev) QA_HIP(hipEventRecord((*ev)[2], s));
     if (ev) QA_HIP(hipEventRecord((*ev)[3], s));
     return QA_OK;
 }
 
 // the same on a workspace's buffers
-qa_status enqueue_single(Workspace *w, hipStream_t s, const qa_problem *pb, const double *V,
-                         int64_t P, int32_t *n_out, double *nbar, SavedRec *saved,
+qa_status enqueue_single(Workspace *w, hipStream_t s, const qa_problem *pb, const Route &route,
+                         const double *V, int64_t P, int32_t *n_out, double *nbar, SavedRec *saved,
                          std::array<hipEvent_t, 4> *ev, const VGrid *sweep = nullptr,
                          const SetupIn *in = nullptr)
 {
-    qa_status st = enqueue_path(w->dr, w->rt, w->pr, w->counters, w->bstats, s, pb, V, P, n_out, nbar,
-                                saved, ev, sweep, in);
+    qa_status st = enqueue_path(w->dr, w->rt, w->pr, w->counters, w->bstats, s, pb, route, V, P,
+                                n_out, nbar, saved, ev, sweep, in);
     if (!st) {
         // (the kernel that scores as well leaves no tables)
-        w->dr_derived = nbar || pb->n_dot > 8;
-        if (writes_row_tables(pb, nbar != nullptr, P)) w->rt_derived = true;
+        w->dr_derived = route.soft || pb->n_dot > 8;
+        if (route.rows) w->rt_derived = true;
     }
     return st;
 }
@@ -516,23 +526,25 @@ qa_status run_single(Workspace *w, const qa_problem *pb, const double *V, int64_
     // (a scoring setup kernel, N <= 8 at T = 0, writes no pixel records)
     if ((st = grow_single(w, P, nbar || pb->n_dot > 8 ? P : 1))) return st;
     w->bstats_used = setup_blocks(P, pb->n_dot);
+    const Route route = route_of(pb, P, nbar != nullptr);
     std::array<hipEvent_t, 4> *ev = timing_slot(w);
     if (ev || !g_graphs || sweep) {
         SetupIn in;
         const bool same = same_inputs(w, pb);
         if (same || !setup_in(pb, sweep, &in)) {
             if ((st = upload_diag(w, pb))) return st;
-            return enqueue_single(w, w->stream, pb, V, P, n_out, nbar, saved, ev, sweep);
+            return enqueue_single(w, w->stream, pb, route, V, P, n_out, nbar, saved, ev, sweep);
         }
         // (forgotten first: a failed launch leaves a record of neither problem)
         w->dr_inputs.clear();
         w->dr_derived = w->rt_derived = false;
-        st = enqueue_single(w, w->stream, pb, V, P, n_out, nbar, saved, ev, sweep, &in);
+        st = enqueue_single(w, w->stream, pb, route, V, P, n_out, nbar, saved, ev, sweep, &in);
         if (!st) w->dr_inputs.swap(w->key);
         return st;
     }
     if ((st = upload_diag(w, pb))) return st;
-    const int path = nbar ? 2 + soft_mm_range(pb) : 10 + 16 * (int)scorer_of(pb, P) + 3 * pb->precision + scorer_mode(pb);
+    const int path = route.soft ? 2 + route.mm
+                                : 10 + 16 * (int)route.sc + 3 * pb->precision + scorer_mode(pb);
     std::vector<int64_t> key = {pb->n_dot, pb->mode, path, pb->flags, P, (int64_t)(uintptr_t)V,
                                 (int64_t)(uintptr_t)n_out, (int64_t)(uintptr_t)nbar,
                                 (int64_t)(uintptr_t)saved, (int64_t)(uintptr_t)w->dr,
@@ -549,7 +561,7 @@ qa_status run_single(Workspace *w, const qa_problem *pb, const double *V, int64_
         if (!w->cap_stream) QA_HIP(hipStreamCreateWithFlags(&w->cap_stream, hipStreamNonBlocking));
         hipGraph_t g;
         QA_HIP(hipStreamBeginCapture(w->cap_stream, hipStreamCaptureModeThreadLocal));
-        st = enqueue_single(w, w->cap_stream, pb, V, P, n_out, nbar, saved, nullptr);
+        st = enqueue_single(w, w->cap_stream, pb, route, V, P, n_out, nbar, saved, nullptr);
         hipError_t ec = hipStreamEndCapture(w->cap_stream, &g);
         if (st) return st;
         if (ec != hipSuccess)
@@ -777,8 +789,8 @@ qa_status qa_ground_state_noalloc(const qa_problem *prob, const double *V_dev, i
     SetupIn in;
     const bool args = setup_in(prob, nullptr, &in);
     if (!args && (st = put_inputs(dr, prob, s))) return st;
-    return enqueue_path(dr, rt, pr, counters, bstats, s, prob, V_dev, P, n_out_dev, nullptr, nullptr,
-                        nullptr, nullptr, args ? &in : nullptr);
+    return enqueue_path(dr, rt, pr, counters, bstats, s, prob, route_of(prob, P, false), V_dev, P,
+                        n_out_dev, nullptr, nullptr, nullptr, nullptr, args ? &in : nullptr);
 }
 
 qa_status qa_ground_state_grid(const qa_problem *prob, const qa_grid *grid, int32_t *n_out_dev,
@@ -1180,7 +1192,8 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
     w->bstats_used = setup_blocks(P, prob->n_dot);
     const hipStream_t s = w->stream;
     // one whole call first: the records the repeated launches read
-    if ((st = enqueue_single(w, s, prob, V_dev, P, n_out_dev, nullptr, nullptr, nullptr)))
+    const Route route = route_of(prob, P, false);
+    if ((st = enqueue_single(w, s, prob, route, V_dev, P, n_out_dev, nullptr, nullptr, nullptr)))
         return st;
     hipEvent_t ev[3] = {};
     for (auto &e : ev) QA_HIP(hipEventCreate(&e));
@@ -1188,13 +1201,11 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
         for (auto &e : ev) (void)hipEventDestroy(e);
         return r;
     };
-    const Scorer sc = scorer_of(prob, P);
-    int32_t *const scored = sc == Scorer::kTable ? n_out_dev : nullptr;
+    int32_t *const scored = route.sc == Scorer::kTable ? n_out_dev : nullptr;
     auto setup = [&](int32_t *n_out) {
         return launch_setup(w->dr, V_dev, P, w->pr, w->counters, w->bstats, prob->n_dot,
-                            prob->mode == QA_CLOSED, scorer_split(sc),
-                            scorer_split(sc) == kBoundLow6 ? w->rt : nullptr, s, nullptr, nullptr,
-                            nullptr, nullptr, n_out) == hipSuccess;
+                            prob->mode == QA_CLOSED, route.split, route.rows ? w->rt : nullptr, s,
+                            nullptr, nullptr, nullptr, nullptr, n_out) == hipSuccess;
     };
     // reps setup launches, then reps (setup, scorer) pairs: the scorer of a
     // pair reads what its setup has just written, as in a call
@@ -1204,7 +1215,7 @@ qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P
     if (hipEventRecord(ev[1], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
     for (int r = 0; r < reps; ++r) {
         if (!setup(scored)) return done(fail(QA_E_DEVICE, "setup launch failed"));
-        if (!scored && launch_scorer(sc, w->dr, w->rt, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
+        if (!scored && launch_scorer(route.sc, w->dr, w->rt, w->pr, w->counters, prob, P, n_out_dev, s) != hipSuccess)
             return done(fail(QA_E_DEVICE, "scorer launch failed"));
     }
     if (hipEventRecord(ev[2], s) != hipSuccess) return done(fail(QA_E_DEVICE, "event record failed"));
