@@ -321,6 +321,8 @@ qa_status qa_timing_sum(void *hip_stream, double *ms_out, int64_t *calls_out);
  * setup kernel (first interval / reps), ms_out[1] the T = 0 scorer the
  * problem selects (second interval less the first, / reps), i.e. the
  * scorer as it runs in a call, right after the setup that wrote its inputs.
+ * Up to 8 dots the setup kernel scores as well: ms_out[0] is both, and
+ * ms_out[1] is 0.
  * No events separate the launches, so each mean includes the dispatch gap
  * between back-to-back launches.  reps in [1, 100000]; P >= 1. */
 qa_status qa_time_kernels(const qa_problem *prob, const double *V_dev, int64_t P,

@@ -531,7 +531,8 @@ def timing_sum(stream=None):
 def time_kernels(cdd, cgd, V, out, reps, t=1.0, precision="fp64", exhaustive=False, stream=None):
     """qa_time_kernels: mean ms per launch of (the setup kernel, the scorer),
     each over `reps` back-to-back launches between HIP events on the stream;
-    `out` (int32 (P, N)) receives the ground state."""
+    `out` (int32 (P, N)) receives the ground state.  Up to 8 dots one kernel
+    does both: (its time, 0)."""
     pb, keep = make_problem(cdd, cgd, False, 0, 0.0, t, precision,
                             FLAG_EXHAUSTIVE if exhaustive else 0)
     V = _device_V(V, pb.n_gate)
