@@ -267,29 +267,34 @@ constexpr size_t kDiagInputBytes = offsetof(DiagRec, one_c);
 
 struct alignas(64) PixRec {  // 256 bytes, two 128-byte lines
     double g0[kMaxDot];   // A (n0 - x_u)
-    double u0;            // U(n0)
-    int16_t n0[kMaxDot];  // base state of the candidate set
+    union {
+        double u0;        // U(n0): setups without a bound (BoundSplit), for the softargmin
+                          // and the scorers of every energy
+        struct {          // setups with one, for the searches in bound order
+            float eg;     // U(n0 + guess) - U(n0), from FP64; the guess is a state of the
+                          // candidate set: the free dots whose x* rounds up, then the best
+                          // single flip of a free dot if it lowers the energy (closed: the
+                          // k free dots with the largest fractional parts)
+            float slack;  // margin of the row kernels' bound test (see the setup)
+        };
+    };
+    int32_t n0[kMaxDot];  // base state of the candidate set
     uint32_t free;        // dots that take both roundings
     int32_t k;            // closed: number of raised free dots; -1 open
-    int32_t flags;        // bit0 QP path, bit1 QP failure, bit2 threshold doubled
-    uint32_t guess;       // a state of the candidate set: the free dots whose x* rounds up,
-                          // then the best single flip of a free dot if it lowers the energy
-                          // (closed: the k free dots with the largest fractional parts)
     // lower bound of the states of a high part b_hi (N >= 9):
     // K + b_hi^T s + 1/2 b_hi^T S b_hi, s = S (n0 - x_u)_hi; the high part is
     // dots 8..N-1 or 6..N-1, as the setup was asked for (BoundSplit)
     float s[10];
     float K;
     float mu;             // closed: -1^T A_LL^{-1} g_lo (the low sum of the free minimiser)
-    float eg;             // N = 16 lanes: U(n0 + guess) - U(n0), from FP64
-    float slack;          // margin of the row kernels' bound test (see the setup)
 };
+static_assert(sizeof(PixRec) == 256, "two lines");
 
 struct alignas(8) SavedRec {
     double emin;          // reference energy (N <= 8: the smallest candidate energy)
     double Z;             // sum exp(-(E - emin)/kT)
     double nb[kMaxDot];   // <n> - n0 = sum_s pi_s 1_s (zero beyond n)
-    int16_t n0[kMaxDot];
+    int32_t n0[kMaxDot];
     uint32_t free;
     int32_t k;
 };

@@ -726,19 +726,20 @@ __global__ __launch_bounds__(kSetupThreads, 4) void k_setup(DiagRec *__restrict_
             if (!(NM <= 8 && n_out)) {
                 for (int q = dot; q < kMaxDot; q += NM) {
                     o->g0[q] = (q < NM) ? g0 : 0.0;
-                    o->n0[q] = (int16_t)((q < NM) ? n0 : 0);
+                    o->n0[q] = (q < NM) ? n0 : 0;
                 }
                 if (NM == 16 && split != kBoundNone && dot >= split) o->s[dot - split] = (float)sv;
                 if (dot == 0) {
-                    o->K = (float)Kb;
-                    o->mu = (float)mu;
-                    o->eg = (float)eg;
-                    o->slack = slack;
-                    o->u0 = u0;
+                    if (NM == 16 && split != kBoundNone) {
+                        o->K = (float)Kb;
+                        o->mu = (float)mu;
+                        o->eg = (float)eg;
+                        o->slack = slack;
+                    } else {
+                        o->u0 = u0;
+                    }
                     o->free = fm;
                     o->k = k;
-                    o->flags = flags | cflags;
-                    o->guess = gm;
                 }
             }
             if (dot == 0) {
@@ -900,7 +901,7 @@ __global__ __launch_bounds__(256) void k_score_fp64(const DiagRec *__restrict__ 
         }
         scored = (int64_t)group_sum<LG>((double)scored);
         if (lane == 0) {
-            for (int i = 0; i < n; ++i) n_out[p * n + i] = (int32_t)r->n0[i] + (int32_t)(s1 >> i & 1u);
+            for (int i = 0; i < n; ++i) n_out[p * n + i] = r->n0[i] + (int32_t)(s1 >> i & 1u);
             if (e2 - e1 < 1e-9) atomicAdd(&sc[0], 1ull);
             atomicAdd(&sc[1], (unsigned long long)scored);
         }

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kRowThreads, MODE == kModeClosed ? 4 : 6) void k_ro
             if (b1 < 0x1p499) s = __brev(best);
             if (b1 < 0x1p499 && b2 - b1 < 1e-9) ++ngap;
         }
-        if (lane < n) n_out[p * n + lane] = (int32_t)r->n0[lane & 15] + (int32_t)(s >> lane & 1u);
+        if (lane < n) n_out[p * n + lane] = r->n0[lane & 15] + (int32_t)(s >> lane & 1u);
     }
     const int64_t rows = (int64_t)wave_sum((double)nrows);
     if (lane == 0) {
