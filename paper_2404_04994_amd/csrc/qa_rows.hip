@@ -427,13 +427,18 @@ __device__ __forceinline__ int row_count(uint32_t mlo, uint32_t mhi)
 // instructions, a row is 12.  On arrays the kernel's tail are pixels with a poor guess:
 // over 1500 pixels of a 16-dot array up to 686 rows by the guess, 84 by this row and
 // 68 by the minimum itself (random capacitances: 231, 231 and 218, the bound is loose).
-// The form with this step (TAIL) is for dense boxes of up to kTailPixels, where the
-// kernel ends with such pixels: calls of 10^4 pixels on three arrays 24.3, 36.3 and
-// 37.5 us without it, 24.4, 28.9 and 30.1 us with it; of 6*10^5 pixels, where all
-// pixels' instructions count, 634, 742 and 785 us without, 671, 769 and 812 us with it.
-// Thresholded sets: 17.5, 16.8, 22.0 us without, 18.0, 17.2, 21.4 us with it.
+// The form with this step (TAIL) is for dense boxes of 14 dots and more and few pixels,
+// where the kernel ends with such pixels; from some number of pixels on all pixels'
+// instructions count.  Without / with it, us a call, means over six arrays and six sets
+// of random capacitances:
+//     16 dots  10^4 37.4 / 32.7, 45.0 / 42.5; 2.5*10^4 60.2 / 55.0, 63.9 / 63.1;
+//              5*10^4 89.6 / 88.2, 95.7 / 100.4
+//     14 dots  10^4 23.8 / 23.1, 24.9 / 25.2; 2.5*10^4 39.6 / 39.7, 40.7 / 42.2
+//     12 dots  10^4 19.1 / 19.2, 18.6 / 18.8; 9 dots 16.9 / 17.3, 16.6 / 17.1
+// Thresholded sets are slower with it throughout (16 dots, 10^4 pixels, t = 1/2 34.3 /
+// 40.7 random, 30.0 / 34.0 arrays: their guess is not what leaves the rows).
 constexpr int kManyRows = 64;
-constexpr int64_t kTailPixels = 50000;
+constexpr int64_t kTailPixels = 12500;  // per dot above 13
 
 // T = 0 argmin (Eq. argmin) over each pixel's candidate set: a wave per pixel,
 // one lane per low state, over the rows the bound leaves.  Each lane keeps its
@@ -574,7 +579,7 @@ hipError_t launch_rows_gs(const RowTab *rt, const PixRec *pr, int64_t P, int mod
         return hipGetLastError();
     };
     if (mode == kModeDense)
-        return P <= kTailPixels ? go(k_rows_gs<kModeDense, true>, 3)
+        return P <= kTailPixels * (n_dot - 13) ? go(k_rows_gs<kModeDense, true>, 3)
                                 : go(k_rows_gs<kModeDense, false>, mode);
     if (mode == kModePruned) return go(k_rows_gs<kModePruned, false>, mode);
     return go(k_rows_gs<kModeClosed, false>, mode);

@@ -108,3 +108,16 @@ def test_pixels_of_many_rows(qa, n_dot, seed):
     assert torch.equal(few, every)
     assert torch.equal(many, few.repeat(17, 1))
     assert st["scored"] <= se["scored"] == 3000 << n_dot
+
+
+@pytest.mark.parametrize("n_dot,limit", [(14, 12500), (15, 25000), (16, 37500)])
+def test_on_both_sides_of_the_tail_limit(qa, n_dot, limit):
+    """The dense form that looks for a better guess, for as many pixels as it is used for,
+    and the one without, for one more: the states of computing every energy."""
+    cdd, cgd = sub_array(n_dot, 12)
+    V = torch.as_tensor(np.random.default_rng(n_dot).uniform(-2.0, 8.0, (1250, n_dot))).cuda()
+    every = qa.ground_state(cdd, cgd, V, exhaustive=True)
+    few = qa.ground_state(cdd, cgd, V.repeat(limit // 1250, 1))
+    more = qa.ground_state(cdd, cgd, torch.cat([V.repeat(limit // 1250, 1), V[:1]]))
+    assert torch.equal(few, every.repeat(limit // 1250, 1))
+    assert torch.equal(more[:limit], few) and torch.equal(more[limit:], every[:1])
