@@ -362,7 +362,7 @@ qa_status grow_single(Workspace *w, int64_t P, int64_t records)
     if (w->dr != dr0) w->dr_inputs.clear();
     if ((st = grow(w, w->rt, w->rt_cap, 1))) return st;
     if ((st = grow(w, w->pr, w->pr_cap, records))) return st;
-    // four counts per setup block; N = 16 has the most blocks
+    // kBstatWords counts per setup block; N = 16 has the most blocks
     if ((st = grow(w, w->bstats, w->bstats_cap, kBstatWords * setup_blocks(P, kMaxDot)))) return st;
     return QA_OK;
 }
@@ -638,7 +638,7 @@ qa_status backward(const qa_problem *prob, const double *V_dev, const VGrid *vg,
     // it also clears the accumulators when they are not known to be zero
     const int64_t nzero = w->acc_zero ? 0 : nacc;
     if (!w->dr_derived) {
-        QA_HIP(launch_prep(w->dr, 1, nullptr, w->stream, nzero ? w->acc : nullptr, nzero));
+        QA_HIP(launch_prep(w->dr, w->stream, nzero ? w->acc : nullptr, nzero));
         w->dr_derived = true;
     } else if (nzero) {
         QA_HIP(launch_zero_i64(reinterpret_cast<int64_t *>(w->acc), (int)nzero, w->stream));
@@ -1025,14 +1025,6 @@ qa_status enqueue_batch(Workspace *w, hipStream_t s, int32_t n_diag, const Batch
                         w->counters, plan.max_dot, s));
     return QA_OK;
 }
-
-}  // namespace
-
-extern "C" {
-
-}  // extern "C"
-
-namespace {
 
 // a batch of explicit-voltage diagrams (grids NULL) or of sweeps
 qa_status batched(const qa_problem *probs, int32_t n_diag, const double *V_dev,

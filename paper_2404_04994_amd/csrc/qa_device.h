@@ -198,11 +198,6 @@ __device__ __forceinline__ bool qp_solve(const double *__restrict__ K, double to
 // group.  With y = A 1_s maintained incrementally,
 //   U(n0 + 1_s) = U(n0) + sum_{i in s} (g0_i + y_i / 2)      (Eq. free_energy)
 // ---------------------------------------------------------------------------
-struct WalkState {
-    uint32_t s;
-    int pc;
-};
-
 template <int NM>
 __device__ __forceinline__ double walk_energy(const double (&g0)[NM], const double (&y)[NM],
                                               double u0, uint32_t s)

@@ -412,10 +412,9 @@ constexpr int64_t setup_blocks_max(int64_t P)
 hipError_t launch_zero_i64(int64_t *p, int n, hipStream_t s);
 // one chunk of a diagram's inputs into dr
 hipError_t launch_put_inputs(DiagRec *dr, const InputChunk &c, hipStream_t s);
-// prologue of n_diag diagrams; also zeroes the kCounterWords counters and
-// the nzero doubles at zero when given
-hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s,
-                       double *zero = nullptr, int64_t nzero = 0);
+// prologue of a diagram whose setup has not run (the adjoint by itself); also zeroes the
+// nzero doubles at zero when given
+hipError_t launch_prep(DiagRec *dr, hipStream_t s, double *zero = nullptr, int64_t nzero = 0);
 // prologue (every block; block 0 also stores A and the tables into dr and
 // clears the kCounterWords counters) and setup of every pixel; the per-block
 // counts {pixels, QP, doubled, QP failures, gaps below 1e-9, candidates} go to
@@ -434,7 +433,7 @@ hipError_t launch_setup(DiagRec *dr, const double *V, int64_t P, PixRec *pr, int
                         hipStream_t s, double *x_out = nullptr, int32_t *flags_out = nullptr,
                         const VGrid *grid = nullptr,
                         const SetupIn *in = nullptr, int32_t *n_out = nullptr);
-// T = 0 argmin in FP64 over the candidate set of every pixel
+// T = 0 argmin in FP64 over the candidate set of every pixel, every energy (N >= 9)
 hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                              int64_t *counters, int n_dot, hipStream_t s);
 // the same for N >= 9 in bound order (qa_rows.hip; setup split kBoundLow6);

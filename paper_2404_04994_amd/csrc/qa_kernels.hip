@@ -65,28 +65,24 @@ hipError_t launch_put_inputs(DiagRec *dr, const InputChunk &c, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------
-// K0: per-diagram prologue, one 256-thread block per diagram
+// K0: the prologue of a diagram by itself, one 256-thread block
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kPrepThreads) void k_prep(DiagRec *dr_all, int64_t *counters,
-                                                      double *zero, int64_t nzero)
+__global__ __launch_bounds__(kPrepThreads) void k_prep(DiagRec *dr, double *zero, int64_t nzero)
 {
     __shared__ double sCdd[kMaxDot * kMaxDot];
     __shared__ double M[kMaxDot * kMaxDot];
     __shared__ double cvec[kMaxDot];
     __shared__ double red[8];
-    // the call's counters (and accumulators) start at zero: no separate
-    // memset or fill kernel in the launch sequence
-    if (counters && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < kCounterWords; i += blockDim.x) counters[i] = 0;
-    if (zero && blockIdx.x == 0)
+    // the adjoint's accumulators start at zero: no separate memset or fill kernel in
+    // the launch sequence
+    if (zero)
         for (int64_t i = threadIdx.x; i < nzero; i += blockDim.x) zero[i] = 0.0;
-    prep_body(dr_all + blockIdx.x, sCdd, M, cvec, red);
+    prep_body(dr, sCdd, M, cvec, red);
 }
 
-hipError_t launch_prep(DiagRec *dr, int n_diag, int64_t *counters, hipStream_t s, double *zero,
-                       int64_t nzero)
+hipError_t launch_prep(DiagRec *dr, hipStream_t s, double *zero, int64_t nzero)
 {
-    hipLaunchKernelGGL(k_prep, dim3(n_diag), dim3(kPrepThreads), 0, s, dr, counters, zero, nzero);
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(kPrepThreads), 0, s, dr, zero, nzero);
     return hipGetLastError();
 }
 
@@ -913,17 +909,6 @@ __global__ __launch_bounds__(256) void k_score_fp64(const DiagRec *__restrict__ 
     }
 }
 
-#define QA_DISPATCH_GROUP(n, CALL)                                              \
-    do {                                                                        \
-        if ((n) == 1) { constexpr int LG_ = 1, NM_ = 2; CALL; }                 \
-        else if ((n) == 2) { constexpr int LG_ = 2, NM_ = 2; CALL; }            \
-        else if ((n) == 3) { constexpr int LG_ = 3, NM_ = 4; CALL; }            \
-        else if ((n) == 4) { constexpr int LG_ = 4, NM_ = 4; CALL; }            \
-        else if ((n) == 5) { constexpr int LG_ = 5, NM_ = 8; CALL; }            \
-        else if ((n) <= 8) { constexpr int LG_ = 6, NM_ = 8; CALL; }            \
-        else { constexpr int LG_ = 6, NM_ = 16; CALL; }                         \
-    } while (0)
-
 // table form (n <= 8): groups of up to 16 lanes, CPL candidates per lane
 #define QA_DISPATCH_TAB(n, CALL)                                                 \
     do {                                                                         \
@@ -949,9 +934,9 @@ static unsigned group_blocks(int64_t items, int lg, int64_t cap)
 hipError_t launch_score_fp64(const DiagRec *dr, const PixRec *pr, int64_t P, int32_t *n_out,
                              int64_t *counters, int n_dot, hipStream_t s)
 {
-    QA_DISPATCH_GROUP(n_dot, hipLaunchKernelGGL((k_score_fp64<LG_, NM_>),
-                                                dim3(group_blocks(P, LG_, 8192)), dim3(256), 0, s,
-                                                dr, pr, P, n_out, counters));
+    if (n_dot < 9) return hipErrorInvalidValue;  // (scored by the setup kernel)
+    hipLaunchKernelGGL((k_score_fp64<6, 16>), dim3(group_blocks(P, 6, 8192)), dim3(256), 0, s, dr,
+                       pr, P, n_out, counters);
     return hipGetLastError();
 }
 
