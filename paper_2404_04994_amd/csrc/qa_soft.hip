@@ -35,7 +35,7 @@
 // wave and set of columns beside 32 products of 64 cycles) at two waves per SIMD,
 // which is what the registers allow; launch and prologue latency for few
 // pixels.  Measured against the walk over the candidates (one wave per pixel):
-// 16 dots, 10^4 pixels 10900 -> 105 us; 12 dots, 4096 pixels 400 -> 9.9 us; error
+// 16 dots, 10^4 pixels 10900 -> 110 us; 12 dots, 4096 pixels 400 -> 9.7 us; error
 // against 64 bits 3.3e-15 -> 1.8e-15 (16 dots, kT = 0.01).
 #include "qa_device.h"
 
@@ -550,7 +550,7 @@ hipError_t launch_soft_mm(const DiagRec *dr, const RowTab *rt, const PixRec *pr,
 // one more matrix product with the pixels as inner dimension, kept in registers
 // (wave w: 16 low states by 64 middle states).  The outer products of dL/dA and
 // dL/dC_gd run over the pixels the same way.  Against the walk over the
-// candidates, 12 dots and 4096 pixels: 337 -> 25 us.  That is one set of pixels a
+// candidates, 12 dots and 4096 pixels: 337 -> 23 us.  That is one set of pixels a
 // block: a serial chain through eight barriers at one wave a SIMD, where the products
 // alone would take 5 us.  (The pair sums at the end had taken 8 us of 36 as a loop
 // that waited for each read.)
